@@ -164,8 +164,12 @@ int ozaki_get_split(void);
  * Argument numbers as ozaki_dgemm, with moduli 14 (OZAKI2_MODULI_MIN ..
  * OZAKI2_MODULI_MAX, and -14 also when beta < 1: too few moduli for K').
  * K' above OZAKI2_K_MAX (exact INT32 sums) returns -5. The workspace holds
- * the residue planes (see ozaki2_workspace_bytes); the modular products and
- * the rebuild run in one fused kernel and never leave the chip.
+ * the residue planes (see ozaki2_workspace_bytes). Where it goes on behind them
+ * (the library's own does: one byte per modulus and output entry, at most 1
+ * GiB or one strip of 256 columns), the modular products leave the chip there
+ * as residue bytes, a strip of columns at a time, and a second kernel rebuilds
+ * C; a caller's workspace of just ozaki2_workspace_bytes takes one fused kernel
+ * that is about half as fast. The results are the same bit for bit.
  */
 #define OZAKI2_MODULI_MIN 2
 #define OZAKI2_MODULI_MAX 20

@@ -24,28 +24,53 @@
 // Complex data is one real product with the contraction interleaved (K' = 2k):
 // A' rows (Re, Im), B' rows 2j = (Re, -Im) and 2j+1 = (Im, Re) of column j.
 #include "ozaki2_crt.hpp"
+#include "ozaki_split_tile.hpp"
 
 namespace oz {
 namespace crt {
 
 // ---------------------------------------------------------------- residues
-// Residue tile: 16 view rows x 128 contraction entries of X' (64 complex
-// elements); for complex B the 16 view rows (columns j) give the 32 X' rows
-// 2j = (Re, -Im) and 2j+1 = (Im, Re). A thread converts 8 consecutive entries
-// of one row, so the 16 threads of a row write its 128 residue bytes of one
-// modulus as one full 128-byte line. In LDS entry e of a row sits at
-// e + e / 8 (one pad double per 8), which spreads the 16 threads of a row
-// over distinct banks.
-constexpr int kResRows = 16;
-constexpr int kResEntries = 128;
-constexpr int kResPitch = kResEntries + kResEntries / 8 + 1;  // doubles per LDS row
-constexpr int kResTileDoubles = kResRows * kResPitch;
-__device__ __forceinline__ int res_slot(int e) { return e + (e >> 3); }
+// What the residue of modulus k needs: m_k, 1 / m_k, the residues of 256^b mod
+// m_k, b = 0..7, as the bytes of two words (balanced and in [0, m_k)), and
+// -2^64 mod m_k.
+struct ResConst {
+  float rm, fm;
+  int w0, w1;
+  unsigned u0, u1;
+  int c64;
+};
+struct ResTable {
+  ResConst c[kModMax];
+};
+constexpr ResTable make_res_table() {
+  ResTable t{};
+  for (int k = 0; k < kModMax; ++k) {
+    const int m = kT.m[k];
+    t.c[k].rm = 1.0f / (float)m;
+    t.c[k].fm = (float)m;
+    unsigned w[2] = {0, 0}, u[2] = {0, 0};
+    int x = bal_c(1, m);
+    for (int b = 0; b < 8; ++b) {
+      w[b >> 2] |= (unsigned)(x & 0xff) << (8 * (b & 3));
+      u[b >> 2] |= (unsigned)(x < 0 ? x + m : x) << (8 * (b & 3));
+      x = bal_c(x * 256, m);
+    }
+    t.c[k].w0 = (int)w[0];
+    t.c[k].w1 = (int)w[1];
+    t.c[k].u0 = u[0];
+    t.c[k].u1 = u[1];
+    t.c[k].c64 = x <= 0 ? -x : m - x;
+  }
+  return t;
+}
+__constant__ ResTable kRes = make_res_table();
 
-// trunc(x 2^(beta - e)) as five signed 13-bit pieces: x' = sum_t a_t 2^(13 t)
-// with every a_t carrying the sign of x (|x'| < 2^63, so a_4 < 2^11).
-constexpr int kPieces = 5;
-__device__ __forceinline__ void to_pieces(double x, int e, int beta, int (&a)[kPieces]) {
+// X = trunc(x 2^(beta - e)) as eight base-256 digits, byte b the digit of 256^b.
+// beta <= 62: signed digits; |X| < 2^62, so X + 0x80...80 lies in (0, 2^64) and
+// its bytes less 128 are the digits. BIG (beta = 63, |X| < 2^63, which signed
+// digits do not cover): the plain bytes of X modulo 2^64.
+template <bool BIG>
+__device__ __forceinline__ uint64_t digit_bytes(double x, int e, int beta) {
   const Sig s = decompose(x, e);
   const int sh = s.sh0 + beta;
   uint64_t u;
@@ -53,119 +78,114 @@ __device__ __forceinline__ void to_pieces(double x, int e, int beta, int (&a)[kP
     u = s.m << sh;  // |x| < 2^e: the result stays below 2^beta
   else
     u = sh > -64 ? (s.m >> (-sh)) : 0ull;
+  if (s.neg) u = 0ull - u;
+  return BIG ? u : (u + 0x8080808080808080ull) ^ 0x8080808080808080ull;
+}
+
+// Four residues of modulus k plus 128 as the bytes of a word. Two 4-way INT8
+// dot products of digits and weights give |t| <= 8 * 128 * 127 < 2^17 (BIG: 0
+// <= t < 2^20) congruent to X, for which one FP32 quotient is exact (see
+// bal_mod); t carries + 128, so the remainder is an unsigned byte that one
+// conversion packs. m_0 = 256: the residue is the lowest digit.
+template <bool BIG>
+__device__ __forceinline__ uint32_t residue_word(const ResConst &rc, bool first, const uint64_t *z) {
+  uint32_t out = 0;
+  if (first) {
 #pragma unroll
-  for (int t = 0; t < kPieces; ++t) {
-    const int v = (int)((u >> (13 * t)) & 0x1fffu);
-    a[t] = s.neg ? -v : v;
+    for (int b = 0; b < 4; ++b) out |= (uint32_t)(z[b] & 0xff) << (8 * b);
+    return out ^ 0x80808080u;
   }
-}
-
-// Balanced residue of x' modulo m_K from its signed pieces:
-// x' = sum a_t 2^(13 t) = sum a_t pw_t (mod m) with |pw_t| <= 127, so the sum
-// stays below 8191 * (1 + 4 * 127) < 2^22 and bal_mod is exact. For m = 256
-// the residue is the low byte of x' in two's complement, which is the low
-// byte of a_0 (2^13 = 0 mod 256).
-template <int K>
-__device__ __forceinline__ int residue(const int (&a)[kPieces]) {
-  if constexpr (kT.m[K] == 256) {
-    return a[0];  // only its low byte is stored
-  } else {
-    int t = a[0];
 #pragma unroll
-    for (int p = 1; p < kPieces; ++p) t += __mul24(a[p], kT.pw[K][p]);
-    return bal_mod<K>(t);
+  for (int b = 0; b < 4; ++b) {
+    const int lo = (int)z[b], hi = (int)(z[b] >> 32);
+    int t;
+    if constexpr (BIG)
+      t = (int)__builtin_amdgcn_udot4(
+          (unsigned)hi, rc.u1,
+          __builtin_amdgcn_udot4((unsigned)lo, rc.u0, 128u + (unsigned)((hi >> 31) & rc.c64), false), false);
+    else
+      t = __builtin_amdgcn_sdot4(hi, rc.w1, __builtin_amdgcn_sdot4(lo, rc.w0, 128, false), false);
+    const float tf = (float)t;
+    const float q = __builtin_rintf(__builtin_fmaf(tf, rc.rm, -128.0f * rc.rm));
+    out = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(-q, rc.fm, tf), b, out);
   }
+  return out;
 }
 
-__device__ __forceinline__ uint32_t pack4(int r0, int r1, int r2, int r3) {
-  return (uint32_t)(r0 & 0xff) | ((uint32_t)(r1 & 0xff) << 8) | ((uint32_t)(r2 & 0xff) << 16) |
-         ((uint32_t)(r3 & 0xff) << 24);
+// The bytes 256 - b of the odd bytes (the residues negated; 256: modulo 256).
+__device__ __forceinline__ uint32_t neg_odd(uint32_t w) {
+  const uint32_t odd = (0x01000100u - ((w >> 8) & 0x00ff00ffu)) & 0x00ff00ffu;
+  return (w & 0x00ff00ffu) | (odd << 8);
 }
 
-// Residues of 16 consecutive contraction entries of one X' row, one 16-byte
-// store per modulus.
-template <int N, int K>
-__device__ __forceinline__ void store_residues(const int (&a)[8][kPieces], int8_t *dst, int64_t plane) {
-  if constexpr (K < N) {
-    int r[8];
-#pragma unroll
-    for (int x = 0; x < 8; ++x) r[x] = residue<K>(a[x]);
-    *reinterpret_cast<uint2 *>(dst + (int64_t)K * plane) =
-        make_uint2(pack4(r[0], r[1], r[2], r[3]), pack4(r[4], r[5], r[6], r[7]));
-    store_residues<N, K + 1>(a, dst, plane);
-  }
-}
-
-// Complex B: the residues of 4 elements (Re, Im) give both X' rows: row 2j
-// holds (Re, -Im) and row 2j+1 holds (Im, Re) along the contraction. The
-// residue of -x is the negated residue (odd moduli: the balanced range is
-// symmetric; 256: bytes negate modulo 256).
-template <int N, int K>
-__device__ __forceinline__ void store_residues_b(const int (&a)[8][kPieces], int8_t *dst0,
-                                                 int8_t *dst1, int64_t plane) {
-  if constexpr (K < N) {
-    int r[8];
-#pragma unroll
-    for (int x = 0; x < 8; ++x) r[x] = residue<K>(a[x]);  // r[2e] = Re, r[2e+1] = Im
-    *reinterpret_cast<uint2 *>(dst0 + (int64_t)K * plane) =
-        make_uint2(pack4(r[0], -r[1], r[2], -r[3]), pack4(r[4], -r[5], r[6], -r[7]));
-    *reinterpret_cast<uint2 *>(dst1 + (int64_t)K * plane) =
-        make_uint2(pack4(r[1], r[0], r[3], r[2]), pack4(r[5], r[4], r[7], r[6]));
-    store_residues_b<N, K + 1>(a, dst0, dst1, plane);
-  }
-}
-
-// One block: view rows [16 bx, 16 bx + 16) x contraction entries [128 by,
-// 128 by + 128) of X'. The tile is first copied into LDS with consecutive
-// threads on the unit-stride direction of the view; thread t then converts
-// the 8 entries [8 (t % 16), +8) of view row 16 bx + t / 16 and writes their
-// N residues into plane k of the packed fragment layout (nrb 32-row blocks x
-// nkb 32-entry contraction blocks per plane, `plane` bytes apart), where 8
-// consecutive entries of a row are 8 consecutive bytes. View rows beyond
-// v.R (up to the padded row count the grid covers) get zero residues.
-template <bool CPLX, bool SIDEB, int N>
-__global__ void __launch_bounds__(256) k_residues(View v, const int *code, int beta, int8_t *out,
-                                                  int64_t nrb, int64_t nkb, int64_t plane) {
-  constexpr int TL = CPLX ? kResEntries / 2 : kResEntries;  // view elements per tile row
-  __shared__ double tile[kResTileDoubles];
+// One thread per view row and 16 consecutive packed contraction entries (8
+// complex elements), as in the split: it reads its values once, keeps their
+// digits in registers and writes one 16-byte run per modulus (complex B: one
+// per X' row, 2j = (Re, -Im) and 2j + 1 = (Im, Re), from the same residues).
+// What bounds it is the arithmetic, about 8 operations per entry and modulus
+// (two dot products, conversion, quotient, remainder, packing; 13-bit pieces
+// with 24-bit products took 15), and the writes: 2048^3 complex, 14 moduli, A
+// 40 us and B 74 us (2.9 and 3.2 TB/s written), before 57 and 77. Rows and
+// entries beyond the operand give zero residues.
+template <bool CPLX, bool SIDEB, bool STAGED, bool BIG>
+__global__ void __launch_bounds__(256) k_residues(View v, const int *code, int n, int beta,
+                                                  int8_t *out, int64_t nrb, int64_t nkb,
+                                                  int64_t plane) {
+  using T = SplitTile<CPLX, false>;
+  using E = typename std::conditional<CPLX, double2, double>::type;
+  __shared__ __attribute__((aligned(16))) double tile[STAGED ? T::TR * T::PITCH : 2];
   const int64_t bx = blockIdx.x, by = blockIdx.y;
-  const int64_t r0 = bx * kResRows, l0 = by * TL;
-  const bool rows_fast = v.sr == 1 && v.sl != 1;
-  for (int c = threadIdx.x; c < kResRows * TL; c += 256) {
-    const int rr = rows_fast ? c % kResRows : c / TL;
-    const int ll = rows_fast ? c / kResRows : c % TL;
-    const int64_t r = r0 + rr, l = l0 + ll;
-    const bool in = r < v.R && l < v.L;
-    if constexpr (CPLX) {
-      double2 z = make_double2(0.0, 0.0);
-      if (in) z = reinterpret_cast<const double2 *>(v.base)[r * v.sr + l * v.sl];
-      tile[rr * kResPitch + res_slot(2 * ll)] = z.x;
-      tile[rr * kResPitch + res_slot(2 * ll + 1)] = v.conj ? -z.y : z.y;
-    } else {
-      tile[rr * kResPitch + res_slot(ll)] =
-          in ? reinterpret_cast<const double *>(v.base)[r * v.sr + l * v.sl] : 0.0;
-    }
-  }
-  __syncthreads();
-
+  if constexpr (STAGED) load_split_tile<CPLX, false>(v, bx, by, tile);
   const int tid = threadIdx.x;
-  const int trow = tid >> 4;                    // view row within the tile
-  const int kq0 = (tid & 15) * 8;               // first contraction entry within the tile
-  const int64_t vr = bx * kResRows + trow;
+  const int64_t vr = bx * 64 + (tid & 63);
+  const int64_t kk = (by * 4 + (tid >> 6)) * 16;
   const int c = vr < v.R ? code[vr] : 0;
   const bool live = vr < v.R && !code_bad(c);
   const int e = code_exp(c);
 
-  int a[8][kPieces];
+  uint64_t z[16];
+  constexpr int NE = CPLX ? 8 : 16;  // elements per thread
+  const int64_t l0 = CPLX ? kk >> 1 : kk;
+  E val[NE];
 #pragma unroll
-  for (int x = 0; x < 8; ++x)
-    to_pieces(live ? tile[trow * kResPitch + res_slot(kq0 + x)] : 0.0, e, beta, a[x]);
-  const int64_t kk = by * kResEntries + kq0;
-  if constexpr (CPLX && SIDEB) {
-    store_residues_b<N, 0>(a, out + frag_offset(0, 2 * vr, kk, nrb, nkb),
-                           out + frag_offset(0, 2 * vr + 1, kk, nrb, nkb), plane);
-  } else {
-    store_residues<N, 0>(a, out + frag_offset(0, vr, kk, nrb, nkb), plane);
+  for (int x = 0; x < NE; ++x) {
+    const int64_t l = l0 + x;
+    if constexpr (STAGED)
+      val[x] = *reinterpret_cast<const E *>(tile + (tid & 63) * T::PITCH + (l - by * T::TL) * T::EW);
+    else
+      val[x] = reinterpret_cast<const E *>(v.base)[(live && l < v.L) ? vr * v.sr + l * v.sl : 0];
+  }
+#pragma unroll
+  for (int x = 0; x < NE; ++x) {
+    const bool ok = live && l0 + x < v.L;
+    if constexpr (CPLX) {
+      z[2 * x] = digit_bytes<BIG>(ok ? val[x].x : 0.0, e, beta);
+      z[2 * x + 1] = digit_bytes<BIG>(ok ? (v.conj ? -val[x].y : val[x].y) : 0.0, e, beta);
+    } else {
+      z[x] = digit_bytes<BIG>(ok ? val[x] : 0.0, e, beta);
+    }
+  }
+
+  int8_t *dst = out + frag_offset(0, (CPLX && SIDEB) ? 2 * vr : vr, kk, nrb, nkb);
+  for (int k = 0; k < n; ++k) {
+    const ResConst rc = kRes.c[k];
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = residue_word<BIG>(rc, k == 0, z + 4 * q);
+    int8_t *d = dst + k * plane;
+    if constexpr (CPLX && SIDEB) {
+      uint32_t a[4], b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[q] = neg_odd(w[q]) ^ 0x80808080u;
+        b[q] = __builtin_amdgcn_perm(0u, w[q], 0x02030001u) ^ 0x80808080u;  // bytes 1, 0, 3, 2
+      }
+      *reinterpret_cast<uint4 *>(d) = make_uint4(a[0], a[1], a[2], a[3]);
+      *reinterpret_cast<uint4 *>(d + 16) = make_uint4(b[0], b[1], b[2], b[3]);
+    } else {
+      *reinterpret_cast<uint4 *>(d) = make_uint4(w[0] ^ 0x80808080u, w[1] ^ 0x80808080u,
+                                                 w[2] ^ 0x80808080u, w[3] ^ 0x80808080u);
+    }
   }
 }
 
@@ -200,41 +220,36 @@ int crt_beta(int n, int64_t kprime) {
   return b > 63 ? 63 : b;
 }
 
-namespace {
-template <bool CPLX, bool SIDEB>
-hipError_t residues_n(const View &v, const int *code, int n, int beta, int8_t *out, int64_t nrb,
-                      int64_t nkb, int64_t plane, dim3 grid, hipStream_t st) {
-  switch (n) {
-#define OZ_RES(N)                                                                                  \
-  case N:                                                                                          \
-    hipLaunchKernelGGL((crt::k_residues<CPLX, SIDEB, N>), grid, dim3(256), 0, st, v, code, beta,  \
-                       out, nrb, nkb, plane);                                                      \
-    break;
-    OZ_RES(2) OZ_RES(3) OZ_RES(4) OZ_RES(5) OZ_RES(6) OZ_RES(7) OZ_RES(8) OZ_RES(9) OZ_RES(10)
-    OZ_RES(11) OZ_RES(12) OZ_RES(13) OZ_RES(14) OZ_RES(15) OZ_RES(16) OZ_RES(17) OZ_RES(18)
-    OZ_RES(19) OZ_RES(20)
-#undef OZ_RES
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-}  // namespace
-
 hipError_t launch_residues(const View &v, bool cplx, bool side_b, const int *code, int n, int beta,
                            int8_t *out, int64_t nrb, int64_t nkb, hipStream_t st) {
-  // 128 contraction entries (four blocks) per workgroup; view rows up to the
+  // 64 contraction entries (two blocks) per workgroup; view rows up to the
   // padded X' rows (complex B: two X' rows per view row)
-  if (v.R <= 0 || nrb <= 0 || nkb <= 0 || nkb % 4 != 0) return hipErrorInvalidValue;
+  if (v.R <= 0 || nrb <= 0 || nrb % 4 != 0 || nkb <= 0 || nkb % 4 != 0) return hipErrorInvalidValue;
   const int64_t view_rows = (cplx && side_b) ? nrb * 16 : nrb * 32;
   if (view_rows < v.R) return hipErrorInvalidValue;
   const int64_t plane = nrb * nkb * kFragBytes;
-  const dim3 grid((unsigned)(view_rows / crt::kResRows), (unsigned)(nkb / 4));
-  if (cplx)
-    return side_b ? residues_n<true, true>(v, code, n, beta, out, nrb, nkb, plane, grid, st)
-                  : residues_n<true, false>(v, code, n, beta, out, nrb, nkb, plane, grid, st);
-  return residues_n<false, false>(v, code, n, beta, out, nrb, nkb, plane, grid, st);
+  const dim3 grid((unsigned)(view_rows / 64), (unsigned)(nkb / 2));
+  const bool staged = split_staged(v);
+#define OZ_RES2(C, B, T, G)                                                                          \
+  hipLaunchKernelGGL((crt::k_residues<C, B, T, G>), grid, dim3(256), 0, st, v, code, n, beta, out, \
+                     nrb, nkb, plane)
+#define OZ_RES(C, B, T) \
+  do {                  \
+    if (beta > 62)      \
+      OZ_RES2(C, B, T, true);  \
+    else                       \
+      OZ_RES2(C, B, T, false); \
+  } while (0)
+  if (cplx && side_b) {
+    if (staged) OZ_RES(true, true, true); else OZ_RES(true, true, false);
+  } else if (cplx) {
+    if (staged) OZ_RES(true, false, true); else OZ_RES(true, false, false);
+  } else {
+    if (staged) OZ_RES(false, false, true); else OZ_RES(false, false, false);
+  }
+#undef OZ_RES2
+#undef OZ_RES
+  return hipGetLastError();
 }
-
 
 }  // namespace oz

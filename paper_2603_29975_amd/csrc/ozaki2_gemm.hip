@@ -1,6 +1,10 @@
 // Fused Ozaki-II product of libozaki (gfx950): the N modular INT8 products of
 // an output tile and the Chinese-remainder rebuild in one kernel.
 //
+// The form that needs no scratch beyond the residue planes: taken where the
+// workspace ends with them (ozaki2_mod.hip is about twice as fast and is taken
+// everywhere else).
+//
 // Section 2.2 of the paper: the integer operands are multiplied modulo
 // several pairwise-coprime moduli on the integer matrix cores, and the Chinese
 // remainder theorem gives back the exact integer product. Here every modular

@@ -6,7 +6,7 @@
 //   split both operands into packed INT8 slices -> fused slice GEMM with FP64
 //   recombination and alpha/beta.
 // An Ozaki-II call shares the fill and scan, then writes INT8 residue planes,
-// runs one batched INT8 GEMM over the moduli and rebuilds C by the CRT.
+// runs the INT8 products of all moduli and rebuilds C by the CRT.
 // The interface mirrors a BLAS GEMM because the paper's solver reaches the
 // emulation through intercepted standard BLAS calls (Section 3.1).
 #include <algorithm>
@@ -160,6 +160,33 @@ int get_workspace(size_t bytes, void **out) {
   }
   *out = g.own_ws[dev];
   return OZAKI_OK;
+}
+
+// Workspace of at least `bytes` and, where it can be had, `want`: *got is what
+// there is. The caller's buffer is taken as it is; the library's own buffer
+// grows to `want`, except that nothing is allocated while the stream captures
+// or where only `bytes` can be allocated.
+int get_workspace_up_to(size_t bytes, size_t want, void **out, size_t *got) {
+  int rc;
+  if (g.user_ws != nullptr) {
+    if ((rc = get_workspace(bytes, out))) return rc;
+    *got = g.user_ws_bytes;
+    return OZAKI_OK;
+  }
+  int dev = 0;
+  if ((rc = current_device(&dev))) return rc;
+  if (g.own_ws_bytes[dev] >= bytes && g.own_ws_bytes[dev] < want) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(g.stream, &cs) != hipSuccess) {
+      (void)hipGetLastError();
+      cs = hipStreamCaptureStatusActive;
+    }
+    if (cs != hipStreamCaptureStatusNone) want = bytes;
+  }
+  rc = get_workspace(want, out);
+  if (rc == OZAKI_ERR_ALLOC && want > bytes) rc = get_workspace(bytes, out);
+  *got = g.own_ws_bytes[dev];
+  return rc;
 }
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -496,6 +523,28 @@ int make_plan2(bool cplx, int64_t m, int64_t n, int64_t k, int N, Plan2 *p) {
   return 0;
 }
 
+// Residue bytes of the modular products (ozaki2_mod.hip), kept behind the
+// plan's own workspace: N bytes per output entry, rows padded to whole 128-byte
+// lines, in strips of columns of at most kOz2StripBytes.
+constexpr int64_t kOz2RowPad = 32;
+constexpr int64_t kOz2StripJ = 256;  // j' per strip: a multiple of this (the tile) unless all fit
+constexpr size_t kOz2StripBytes = (size_t)1 << 30;
+
+size_t oz2_strip_bytes(const Plan2 &p, int64_t j) {
+  return (size_t)p.N * (size_t)round_up(p.m, kOz2RowPad) * (size_t)round_up(j, 4);
+}
+
+// j' per strip that `bytes` hold: all of them, a multiple of the tile, or 0.
+int64_t oz2_strip(const Plan2 &p, size_t bytes) {
+  if (oz2_strip_bytes(p, p.nprime) <= bytes) return p.nprime;
+  return (int64_t)(bytes / oz2_strip_bytes(p, kOz2StripJ)) * kOz2StripJ;
+}
+
+size_t oz2_plane_bytes(const Plan2 &p) {
+  const size_t all = oz2_strip_bytes(p, p.nprime);
+  return std::min(all, std::max(oz2_strip_bytes(p, kOz2StripJ), kOz2StripBytes));
+}
+
 int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, int64_t k,
                      double ar, double ai, const void *A, int64_t lda, const void *B, int64_t ldb,
                      double br, double bi, void *C, int64_t ldc, int moduli) {
@@ -518,7 +567,8 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   int dev = 0;
   if ((rc = current_device(&dev))) return rc;
   void *wsv = nullptr;
-  if ((rc = get_workspace(p.total, &wsv))) return rc;
+  size_t ws_bytes = 0;
+  if ((rc = get_workspace_up_to(p.total, p.total + oz2_plane_bytes(p), &wsv, &ws_bytes))) return rc;
   char *ws = static_cast<char *>(wsv);
   int *codeA = reinterpret_cast<int *>(ws + p.off_codeA);
   int *codeB = reinterpret_cast<int *>(ws + p.off_codeB);
@@ -543,7 +593,7 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
     return rc;
   phase_end(mk, st);
 
-  // the modular products and the rebuild: one fused kernel
+  // the modular products and the rebuild
   mk = phase_begin(OZAKI_PHASE_GEMM, st);
   Oz2Args ga{};
   ga.RA = RA;
@@ -564,7 +614,38 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   ga.cplx = cplx ? 1 : 0;
   ga.C = C;
   ga.ldc = ldc;
-  rc = hip_rc(launch_oz2gemm(moduli, ga, g.dev[dev].num_cu, st));
+  const int64_t strip = oz2_strip(p, ws_bytes - p.total);
+  if (strip == 0) {
+    rc = hip_rc(launch_oz2gemm(moduli, ga, g.dev[dev].num_cu, st));
+  } else {
+    Oz2ModArgs sa{};
+    sa.RA = RA;
+    sa.RB = RB;
+    sa.nrbQ = p.nrbQ;
+    sa.nrbP = p.nrbP;
+    sa.nkb = p.nkb;
+    sa.m = m;
+    sa.n = moduli;
+    sa.beta = p.beta;
+    sa.planes = reinterpret_cast<int8_t *>(ws + p.total);
+    sa.ldq = round_up(m, kOz2RowPad);
+    sa.codeA = codeA;
+    sa.codeB = codeB;
+    sa.ar = ar;
+    sa.ai = ai;
+    sa.br = br;
+    sa.bi = bi;
+    sa.beta_zero = ga.beta_zero;
+    sa.cplx = ga.cplx;
+    sa.C = C;
+    sa.ldc = ldc;
+    for (int64_t j0 = 0; rc == OZAKI_OK && j0 < p.nprime; j0 += strip) {
+      sa.jrb = j0 / 32;
+      sa.jn = std::min(strip, p.nprime - j0);
+      sa.plane_words = (sa.jn + 3) / 4 * sa.ldq;
+      rc = hip_rc(launch_oz2mod(sa, g.dev[dev].num_cu, st));
+    }
+  }
   phase_end(mk, st);
   if (g_tm.on) ++g_tm.calls;
   return rc;

@@ -245,6 +245,27 @@ struct Oz2Args {
   int64_t ldc;
 };
 hipError_t launch_oz2gemm(int n, const Oz2Args &a, int num_cu, hipStream_t st);
+// The same product by one residue byte per output entry and modulus (see
+// ozaki2_mod.hip), over the j' of one strip of columns: the 32-row blocks of B'
+// from jrb on, jn of their j'. planes: n planes of plane_words words, word
+// [j' / 4][i] (leading dimension ldq >= m) holding the bytes of four j'.
+struct Oz2ModArgs {
+  const int8_t *RA, *RB;
+  int64_t nrbQ, nrbP, nkb;
+  int64_t m;
+  int64_t jrb, jn;
+  int n;
+  int beta;
+  int8_t *planes;
+  int64_t plane_words, ldq;
+  const int *codeA, *codeB;
+  double ar, ai, br, bi;
+  int beta_zero;
+  int cplx;
+  void *C;
+  int64_t ldc;
+};
+hipError_t launch_oz2mod(const Oz2ModArgs &a, int num_cu, hipStream_t st);
 
 // Blocked LU and inverse (see ozaki_lu.hip): one pivot column (pivot search,
 // swap over the panel columns [p0, p1) and panel update), the panel's

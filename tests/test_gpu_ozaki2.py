@@ -159,3 +159,58 @@ def test_ozaki2_kkr_2048_sampled_bit_exact_and_accuracy():
     err = metrics.err_comp(sub.ravel(), hi, lo, den)
     _say("kkr 2048 ozaki2 N=14 err_comp (sampled)", err)
     assert err <= 1e-12
+
+
+def _planes(kind, m, n, k, nmod, ws_extra):
+    """C of the same product with the library's workspace and with a caller's workspace of
+    ozaki2_workspace_bytes + ws_extra."""
+    A, B = _operands(kind, m, n, k, seed=970 + m + n, nasty=True)
+    got = _run(kind, "N", "N", A, B, nmod)
+    ws = torch.empty(oz.ozaki2_workspace_bytes(kind, m, n, k, nmod) + ws_extra, dtype=torch.uint8,
+                     device="cuda")
+    assert oz.ozaki_set_workspace(ws, ws.numel()) == 0
+    try:
+        other = _run(kind, "N", "N", A, B, nmod)
+    finally:
+        oz.ozaki_set_workspace(None, 0)
+    return A, B, got, other
+
+
+# (kind, m, n, k, moduli): tiles of 64 (one work item; ragged), of 128 (from 256 items) and of 256
+# (from 192 items), row and column remainders on both sides of a tile, short and long contractions
+@pytest.mark.parametrize("kind,m,n,k,nmod", [
+    ("d", 1, 1, 1, 2), ("z", 63, 33, 70, 7), ("d", 65, 129, 300, 3), ("z", 257, 257, 33, 20),
+    ("d", 511, 513, 129, 18), ("z", 513, 385, 64, 16), ("d", 1025, 1023, 260, 12)])
+def test_ozaki2_residue_planes_and_fused_kernel_agree(kind, m, n, k, nmod):
+    # a caller's workspace that ends with the residue planes takes the fused kernel, one with room
+    # for a strip of 256 columns (the rest of C in further strips) and the library's own the planes
+    A, B, got, fused = _planes(kind, m, n, k, nmod, 0)
+    assert bits_equal(got, fused), mismatch_report(got, fused)
+    strip = _planes(kind, m, n, k, nmod, nmod * 256 * ((m + 31) // 32 * 32))[3]
+    assert bits_equal(got, strip), mismatch_report(got, strip)
+    r, c = slice(max(0, m - 9), m), slice(max(0, n - 9), n)
+    ref = ozaki2.ozaki2_gemm("N", "N", A[r], B[:, c], nmod)
+    assert bits_equal(got[r, c], ref), mismatch_report(got[r, c], ref)
+
+
+@pytest.mark.parametrize("nmod", [14, 16, 17, 18, 20])
+def test_ozaki2_rounding_at_ties(nmod):
+    # sums 2^p (1 + 2^-53) and neighbours, alone and moved off the tie by a term 2^-q below: the
+    # single rounding of the exact integer (limbs that cancel, ties to even, sticky tails)
+    beta = oz.ozaki2_beta_bits(nmod, 4)
+    rng = np.random.default_rng(nmod)
+    m, n = 64, 48
+    A = np.zeros((m, 4))
+    B = np.zeros((4, n))
+    half = beta // 2
+    A[:, 0] = 1.0
+    B[0] = 1.0 - 2.0 ** -rng.integers(1, half + 1, n)
+    A[:, 1] = 2.0 ** -rng.integers(20, half + 1, m) * rng.choice([-1.0, 1.0], m)
+    B[1] = 2.0 ** -rng.integers(20, 28, n)
+    A[:, 2] = rng.choice([0.0, 1.0, -1.0], m) * 2.0 ** -beta
+    B[2] = 2.0 ** -rng.integers(0, beta, n)
+    A[:, 3] = rng.choice([0.0, -1.0], m)
+    B[3] = B[0]
+    got = _run("d", "N", "N", A, B, nmod)
+    ref = ozaki2.ozaki2_gemm("N", "N", A, B, nmod)
+    assert bits_equal(got, ref), mismatch_report(got, ref)
