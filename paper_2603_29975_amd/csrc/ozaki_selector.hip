@@ -150,121 +150,271 @@ constexpr size_t kStateBytes = sW3h + (size_t)kH * 2 + 64;
 
 __device__ __forceinline__ float bf_round(float x) { return (float)(__bf16)x; }
 
-// C (M x N, FP32, row-major) = A (M x K, BF16, row-major) * Bt (N x K, BF16,
-// row-major)^T. One wave per 32 x 32 output tile; M, N multiples of 32, K a
-// multiple of 16. The MFMA's lane l reads 8 consecutive BF16 of row l % 32
-// from contraction offset 8 * (l / 32), and leaves D[8(r/4) + 4(l/32) + r%4][l%32]
-// in register r. Epilogue per `mode`:
-//   0: C = acc
-//   1: H = relu(acc + bias[col]): Cf (FP32), Ch (BF16 row-major), Cht (BF16
-//      transposed, ldt = M)
-//   2: G = acc * [mask[row][col] > 0]: Ch (BF16 row-major) and Cht (BF16 transposed)
-struct MmArgs {
-  const __bf16 *A;
-  const __bf16 *Bt;
-  int64_t M, N, K;
-  int mode;
-  float *Cf;
-  const float *bias;
-  const float *mask;
-  __bf16 *Ch;
-  __bf16 *Cht;
+// The network runs as three kernels: forward and the row part of the backward
+// pass on 32 batch rows per workgroup (the layers of a row block follow each
+// other through LDS), and the sums over the batch (weight and bias gradients,
+// loss) with one workgroup per 32 x 32 weight tile or few columns. At batch 256
+// they are bound by launch and memory latency: forward, loss and gradients
+// 20 us, where one launch per step (12), the head's atomics (296 us) and two
+// column sums by one workgroup (41 us each) took 430.
+//
+// One wave forms one 32 x 32 tile C = A * Bt^T with A, Bt rows of K BF16: lane l
+// reads 8 consecutive entries of row l % 32 from contraction offset 8 (l / 32),
+// and v_mfma_f32_32x32x16_bf16 leaves C[8 (r/4) + 4 (l/32) + r%4][l % 32] in
+// register r.
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+constexpr int kRows = 32;          // batch rows per workgroup
+constexpr int kPitch = kH + 8;     // BF16 per LDS row (16-byte aligned, rows 4 banks apart)
+
+__device__ __forceinline__ int mm_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+template <int K>
+__device__ __forceinline__ v16f mm_tile(const __bf16 *pa, const __bf16 *pb) {
+  v8bf x[K / 16], y[K / 16];
+#pragma unroll
+  for (int q = 0; q < K / 16; ++q) {
+    x[q] = *reinterpret_cast<const v8bf *>(pa + 16 * q);
+    y[q] = *reinterpret_cast<const v8bf *>(pb + 16 * q);
+  }
+  v16f acc = {0};
+#pragma unroll
+  for (int q = 0; q < K / 16; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[q], y[q], acc, 0, 0, 0);
+  return acc;
+}
+
+// Stores a wave's tile of BF16 values row-major (cols columns) and transposed
+// (bp columns), rows r0.., column col, and into the LDS tile if there is one.
+__device__ __forceinline__ void store_tile(const __bf16 (&h)[16], int lane, int64_t r0, int col,
+                                           int64_t bp, __bf16 *rm, __bf16 *tr, __bf16 *lds) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int rr = mm_row(4 * g, lane);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      rm[(r0 + rr + b) * kH + col] = h[4 * g + b];
+      if (lds) lds[(rr + b) * kPitch + col] = h[4 * g + b];
+    }
+    const v4bf v = {h[4 * g], h[4 * g + 1], h[4 * g + 2], h[4 * g + 3]};
+    *reinterpret_cast<v4bf *>(tr + col * bp + r0 + rr) = v;
+  }
+}
+
+struct MlpPtrs {
+  const float *theta;
+  const __bf16 *W1h, *W2h, *W2th, *w3h;
+  __bf16 *xh, *xht;
+  float *h1, *h2;
+  __bf16 *h1h, *h1ht, *h2h, *h2ht, *dh2h, *dh2ht, *dh1h, *dh1ht;
+  float *grad;
 };
 
-__global__ void __launch_bounds__(256) k_mm_bf16(MmArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t ntn = a.N / 32;
-  if (tile >= (a.M / 32) * ntn) return;
-  const int64_t r0 = (tile / ntn) * 32, c0 = (tile % ntn) * 32;
-  v16f acc = {0};
-  const __bf16 *pa = a.A + (r0 + (lane & 31)) * a.K + 8 * (lane >> 5);
-  const __bf16 *pb = a.Bt + (c0 + (lane & 31)) * a.K + 8 * (lane >> 5);
-  for (int64_t k0 = 0; k0 < a.K; k0 += 16) {
-    const v8bf x = *reinterpret_cast<const v8bf *>(pa + k0);
-    const v8bf y = *reinterpret_cast<const v8bf *>(pb + k0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+// Rows 32 blockIdx.x .. +31: Xh = bf16(X) (zero rows from b on), H1 = relu(Xh
+// W1^T + b1), H2 = relu(bf16(H1) W2^T + b2), y = w3 . H2 + b3. Wave w forms the
+// columns 32 w .. +31 of each layer.
+__global__ void __launch_bounds__(256) k_mlp_fwd(MlpPtrs p, const float *X, int64_t b, int64_t bp,
+                                                 float *y) {
+  __shared__ __attribute__((aligned(16))) __bf16 xt[kRows * (kIn + 8)];
+  __shared__ __attribute__((aligned(16))) __bf16 ht[kRows * kPitch];
+  __shared__ float yp[4][kRows];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t r0 = (int64_t)blockIdx.x * kRows;
+  for (int c = tid; c < kRows * kIn; c += 256) {
+    const int64_t r = r0 + c / kIn;
+    const __bf16 v = (__bf16)(r < b ? X[r * kIn + c % kIn] : 0.0f);
+    xt[(c / kIn) * (kIn + 8) + c % kIn] = v;
+    p.xh[r * kIn + c % kIn] = v;
   }
-  const int64_t col = c0 + (lane & 31);
+  __syncthreads();
+  for (int c = tid; c < kRows * kIn; c += 256)
+    p.xht[(c / kRows) * bp + r0 + c % kRows] = xt[(c % kRows) * (kIn + 8) + c / kRows];
+
+  const int col = 32 * wave + (lane & 31);
+  v16f acc = mm_tile<kIn>(xt + (lane & 31) * (kIn + 8) + 8 * (lane >> 5),
+                          p.W1h + col * kIn + 8 * (lane >> 5));
+  __bf16 h[16];
+  const float b1 = p.theta[oB1 + col];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int64_t row = r0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    float v = acc[r];
-    if (a.mode == 0) {
-      a.Cf[row * a.N + col] = v;
-    } else if (a.mode == 1) {
-      v = fmaxf(v + a.bias[col], 0.0f);
-      a.Cf[row * a.N + col] = v;
-      a.Ch[row * a.N + col] = (__bf16)v;
-      a.Cht[col * a.M + row] = (__bf16)v;
-    } else {
-      if (!(a.mask[row * a.N + col] > 0.0f)) v = 0.0f;
-      a.Ch[row * a.N + col] = (__bf16)v;
-      a.Cht[col * a.M + row] = (__bf16)v;
-    }
+    const float v = fmaxf(acc[r] + b1, 0.0f);
+    p.h1[(r0 + mm_row(r, lane)) * kH + col] = v;
+    h[r] = (__bf16)v;
   }
+  store_tile(h, lane, r0, col, bp, p.h1h, p.h1ht, ht);
+  __syncthreads();
+  acc = mm_tile<kH>(ht + (lane & 31) * kPitch + 8 * (lane >> 5), p.W2h + col * kH + 8 * (lane >> 5));
+  const float b2 = p.theta[oB2 + col], w3 = (float)p.w3h[col];
+  float part[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float v = fmaxf(acc[r] + b2, 0.0f);
+    p.h2[(r0 + mm_row(r, lane)) * kH + col] = v;
+    h[r] = (__bf16)v;
+    part[r] = w3 * v;
+  }
+  store_tile(h, lane, r0, col, bp, p.h2h, p.h2ht, nullptr);
+  // the head: each row's 128 terms over the 32 lanes of the half wave, then the waves
+#pragma unroll
+  for (int off = 16; off > 0; off >>= 1)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[r] += __shfl_xor(part[r], off);
+  if ((lane & 31) == 0)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) yp[wave][mm_row(r, lane)] = part[r];
+  __syncthreads();
+  if (tid < kRows && r0 + tid < b)
+    y[r0 + tid] = ((yp[0][tid] + yp[1][tid]) + (yp[2][tid] + yp[3][tid])) + p.theta[oB3];
 }
 
-// X (b x 64 FP32) -> Xh (bp x 64 BF16) and Xht (64 x bp), zero rows b..bp-1.
-__global__ void __launch_bounds__(256) k_pack_x(const float *X, int64_t b, int64_t bp, __bf16 *Xh,
-                                                __bf16 *Xht) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= bp * kIn) return;
-  const int64_t r = idx / kIn, c = idx % kIn;
-  const __bf16 v = (__bf16)(r < b ? X[r * kIn + c] : 0.0f);
-  Xh[r * kIn + c] = v;
-  Xht[c * bp + r] = v;
+// dL/dy of row r for L = (1/b) sum_r w_r (y_r - t_r)^2, w_r = under (y_r < t_r) or 1.
+__device__ __forceinline__ float loss_dy(float y, float t, float under, int64_t b) {
+  const float e = y - t;
+  const float w = y < t ? under : 1.0f;
+  return 2.0f * w * e / (float)b;
 }
 
-// y[r] = b3 + sum_k bf16(w3[k]) * H2[r][k]   (FP32, sequential in k)
-__global__ void __launch_bounds__(256) k_head_fwd(const float *H2, const float *theta,
-                                                  const __bf16 *w3h, int64_t b, float *y) {
-  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (r >= b) return;
-  float s = 0.0f;
-  for (int k = 0; k < kH; ++k) s = fmaf((float)w3h[k], H2[r * kH + k], s);
-  y[r] = s + theta[oB3];
+// Rows 32 blockIdx.x .. +31: dH2 = dy w3 [H2 > 0] (BF16, zero rows from b on),
+// dH1 = (dH2 W2) [H1 > 0] (BF16).
+__global__ void __launch_bounds__(256) k_mlp_bwd_rows(MlpPtrs p, const float *y, const float *t,
+                                                      float under, int64_t b, int64_t bp) {
+  __shared__ __attribute__((aligned(16))) __bf16 dt[kRows * kPitch];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t r0 = (int64_t)blockIdx.x * kRows;
+  const int col = 32 * wave + (lane & 31);
+  const float w3 = (float)p.w3h[col];
+  __bf16 g[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int64_t row = r0 + mm_row(r, lane);
+    const float dy = row < b ? loss_dy(y[row], t[row], under, b) : 0.0f;
+    g[r] = (__bf16)(row < b && p.h2[row * kH + col] > 0.0f ? dy * w3 : 0.0f);
+  }
+  store_tile(g, lane, r0, col, bp, p.dh2h, p.dh2ht, dt);
+  __syncthreads();
+  const v16f acc = mm_tile<kH>(dt + (lane & 31) * kPitch + 8 * (lane >> 5),
+                               p.W2th + col * kH + 8 * (lane >> 5));
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    g[r] = (__bf16)(p.h1[(r0 + mm_row(r, lane)) * kH + col] > 0.0f ? acc[r] : 0.0f);
+  store_tile(g, lane, r0, col, bp, p.dh1h, p.dh1ht, nullptr);
 }
 
-// Loss L = (1/b) sum_r w_r (y_r - t_r)^2 with w_r = under (y_r < t_r) or 1;
-// dy_r = (2/b) w_r (y_r - t_r). dH2[r][k] = dy_r * bf16(w3[k]) * [H2 > 0]
-// (BF16, row-major and transposed, zero for padded rows); dw3 and db3 are
-// atomically accumulated into the gradient.
-__global__ void __launch_bounds__(256) k_head_bwd(const float *H2, const float *y, const float *t,
-                                                  const __bf16 *w3h, int64_t b, int64_t bp,
-                                                  float under, float *grad, float *loss,
-                                                  __bf16 *dH2h, __bf16 *dH2ht) {
-  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (r >= bp) return;
-  float dy = 0.0f;
-  if (r < b) {
+// The sums over the batch, 512 threads: blocks 0..15 one 32 x 32 tile of dW2 =
+// dH2^T H1, 16..23 of dW1 = dH1^T X (the 8 waves take every eighth 16-row step
+// and add up through LDS), 24..55 the bias gradients (one wave per column of
+// dH1, dH2), 56..71 dw3 = H2^T dy (8 columns each), 72 db3 and the loss. Every
+// sum has a fixed order.
+constexpr int kSumTiles2 = (kH / 32) * (kH / 32), kSumTiles1 = (kH / 32) * (kIn / 32);
+constexpr int kSumBias = 2 * kH / 8, kSumHead = kH / 8;
+constexpr int kSumBlocks = kSumTiles2 + kSumTiles1 + kSumBias + kSumHead + 1;
+
+__global__ void __launch_bounds__(512) k_mlp_bwd_sums(MlpPtrs p, const float *y, const float *t,
+                                                      float under, float *loss, int64_t b, int64_t bp) {
+  __shared__ float red[8 * 1024];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int blk = blockIdx.x;
+  if (blk < kSumTiles2 + kSumTiles1) {
+    const bool first = blk >= kSumTiles2;  // dW1
+    if (first) blk -= kSumTiles2;
+    const int nc = (first ? kIn : kH) / 32;
+    const int r0 = (blk / nc) * 32, c0 = (blk % nc) * 32;
+    const __bf16 *pa = (first ? p.dh1ht : p.dh2ht) + (r0 + (lane & 31)) * bp + 8 * (lane >> 5);
+    const __bf16 *pb = (first ? p.xht : p.h1ht) + (c0 + (lane & 31)) * bp + 8 * (lane >> 5);
+    v16f acc = {0};
+    const int64_t steps = bp / 16;
+    int64_t q = wave;
+    for (; q + 24 < steps; q += 32) {  // four steps' loads in flight
+      v8bf x[4], z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        x[u] = *reinterpret_cast<const v8bf *>(pa + 16 * (q + 8 * u));
+        z[u] = *reinterpret_cast<const v8bf *>(pb + 16 * (q + 8 * u));
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[u], z[u], acc, 0, 0, 0);
+    }
+    for (; q < steps; q += 8)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const v8bf *>(pa + 16 * q),
+                                                    *reinterpret_cast<const v8bf *>(pb + 16 * q), acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave * 1024 + mm_row(r, lane) * 32 + (lane & 31)] = acc[r];
+    __syncthreads();
+    float *out = p.grad + (first ? oW1 : oW2);
+    for (int c = tid; c < 1024; c += 512) {
+      float s = red[c];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) s += red[w * 1024 + c];
+      out[(r0 + c / 32) * (first ? kIn : kH) + c0 + c % 32] = s;
+    }
+    return;
+  }
+  blk -= kSumTiles2 + kSumTiles1;
+  if (blk < kSumBias) {
+    const int c = blk * 8 + wave;  // columns of dH1, then of dH2
+    const __bf16 *g = (c < kH ? p.dh1ht + c * bp : p.dh2ht + (c - kH) * bp);
+    float s = 0.0f;
+    for (int64_t r = 8 * lane; r < bp; r += 512) {
+      const v8bf x = *reinterpret_cast<const v8bf *>(g + r);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += (float)x[u];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) p.grad[c < kH ? oB1 + c : oB2 + c - kH] = s;
+    return;
+  }
+  blk -= kSumBias;
+  if (blk < kSumHead) {
+    const int c = blk * 8 + (tid & 7);
+    float s = 0.0f;
+    int64_t r = tid >> 3;
+    for (; r + 192 < b; r += 256) {
+      float h[4], d[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        h[u] = p.h2[(r + 64 * u) * kH + c];
+        d[u] = loss_dy(y[r + 64 * u], t[r + 64 * u], under, b);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (d[u] != 0.0f) s = fmaf(d[u], h[u], s);  // an infinite H2 of a row without error adds nothing
+    }
+    for (; r < b; r += 64) {
+      const float d = loss_dy(y[r], t[r], under, b);
+      if (d != 0.0f) s = fmaf(d, p.h2[r * kH + c], s);
+    }
+    red[tid] = s;
+    __syncthreads();
+    if (tid < 8) {
+      for (int u = 1; u < 64; ++u) s += red[tid + 8 * u];
+      p.grad[oW3 + blk * 8 + tid] = s;
+    }
+    return;
+  }
+  float sd = 0.0f, sl = 0.0f;
+  for (int64_t r = tid; r < b; r += 512) {
     const float e = y[r] - t[r];
     const float w = y[r] < t[r] ? under : 1.0f;
-    dy = 2.0f * w * e / (float)b;
-    if (loss) atomicAdd(loss, w * e * e / (float)b);
-    atomicAdd(grad + oB3, dy);
+    sd += loss_dy(y[r], t[r], under, b);
+    sl += w * e * e / (float)b;
   }
-  for (int k = 0; k < kH; ++k) {
-    const float h = r < b ? H2[r * kH + k] : 0.0f;
-    const float g = h > 0.0f ? dy * (float)w3h[k] : 0.0f;
-    dH2h[r * kH + k] = (__bf16)g;
-    dH2ht[k * bp + r] = (__bf16)g;
-    if (r < b && dy != 0.0f) atomicAdd(grad + oW3 + k, dy * h);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sd += __shfl_xor(sd, off);
+    sl += __shfl_xor(sl, off);
   }
-}
-
-// bias gradient: grad[off + c] += sum_r G[r][c] (G BF16 row-major, rows < bp)
-__global__ void __launch_bounds__(128) k_colsum(const __bf16 *G, int64_t bp, int cols, float *out) {
-  const int c = threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.0f;
-  for (int64_t r = 0; r < bp; ++r) s += (float)G[r * cols + c];
-  out[c] += s;
-}
-
-__global__ void __launch_bounds__(256) k_zero_f32(float *p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.0f;
+  if (lane == 0) {
+    red[wave] = sd;
+    red[8 + wave] = sl;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 8; ++w) {
+      sd += red[w];
+      sl += red[8 + w];
+    }
+    p.grad[oB3] = sd;
+    if (loss) *loss = sl;
+  }
 }
 
 // BF16 copies of W1, W2, W2^T and w3 from theta.
@@ -398,93 +548,54 @@ hipError_t mlp_refresh(void *state, hipStream_t st) {
   return hipGetLastError();
 }
 
+namespace {
+MlpPtrs mlp_ptrs(const void *state, void *scratch, int64_t bp) {
+  // the state is written through `grad` only (backward pass, whose state is not const)
+  char *s = static_cast<char *>(const_cast<void *>(state));
+  char *w = static_cast<char *>(scratch);
+  const Scratch L = scratch_layout(bp);
+  auto bf = [](char *q) { return reinterpret_cast<__bf16 *>(q); };
+  MlpPtrs p{};
+  p.theta = reinterpret_cast<const float *>(s + sTheta);
+  p.W1h = bf(s + sW1h);
+  p.W2h = bf(s + sW2h);
+  p.W2th = bf(s + sW2th);
+  p.w3h = bf(s + sW3h);
+  p.grad = reinterpret_cast<float *>(s + sG);
+  p.xh = bf(w + L.xh);
+  p.xht = bf(w + L.xht);
+  p.h1 = reinterpret_cast<float *>(w + L.h1);
+  p.h2 = reinterpret_cast<float *>(w + L.h2);
+  p.h1h = bf(w + L.h1h);
+  p.h1ht = bf(w + L.h1ht);
+  p.h2h = bf(w + L.h2h);
+  p.h2ht = bf(w + L.h2ht);
+  p.dh2h = bf(w + L.dh2h);
+  p.dh2ht = bf(w + L.dh2ht);
+  p.dh1h = bf(w + L.dh1h);
+  p.dh1ht = bf(w + L.dh1ht);
+  return p;
+}
+}  // namespace
+
 hipError_t mlp_forward(const void *state, int64_t b, const float *X, float *y, void *scratch,
                        hipStream_t st) {
   if (b <= 0) return hipSuccess;
-  const char *s = static_cast<const char *>(state);
-  char *w = static_cast<char *>(scratch);
   const int64_t bp = (b + 31) / 32 * 32;
-  const Scratch L = scratch_layout(bp);
-  const float *th = reinterpret_cast<const float *>(s + sTheta);
-  hipLaunchKernelGGL(k_pack_x, dim3(blocks(bp * kIn, 256)), dim3(256), 0, st, X, b, bp,
-                     reinterpret_cast<__bf16 *>(w + L.xh), reinterpret_cast<__bf16 *>(w + L.xht));
-  MmArgs m1{};
-  m1.A = reinterpret_cast<const __bf16 *>(w + L.xh);
-  m1.Bt = reinterpret_cast<const __bf16 *>(s + sW1h);
-  m1.M = bp;
-  m1.N = kH;
-  m1.K = kIn;
-  m1.mode = 1;
-  m1.Cf = reinterpret_cast<float *>(w + L.h1);
-  m1.bias = th + oB1;
-  m1.Ch = reinterpret_cast<__bf16 *>(w + L.h1h);
-  m1.Cht = reinterpret_cast<__bf16 *>(w + L.h1ht);
-  hipLaunchKernelGGL(k_mm_bf16, dim3(blocks((bp / 32) * (kH / 32), 4)), dim3(256), 0, st, m1);
-  MmArgs m2 = m1;
-  m2.A = reinterpret_cast<const __bf16 *>(w + L.h1h);
-  m2.Bt = reinterpret_cast<const __bf16 *>(s + sW2h);
-  m2.K = kH;
-  m2.Cf = reinterpret_cast<float *>(w + L.h2);
-  m2.bias = th + oB2;
-  m2.Ch = reinterpret_cast<__bf16 *>(w + L.h2h);
-  m2.Cht = reinterpret_cast<__bf16 *>(w + L.h2ht);
-  hipLaunchKernelGGL(k_mm_bf16, dim3(blocks((bp / 32) * (kH / 32), 4)), dim3(256), 0, st, m2);
-  hipLaunchKernelGGL(k_head_fwd, dim3(blocks(b, 256)), dim3(256), 0, st,
-                     reinterpret_cast<const float *>(w + L.h2), th,
-                     reinterpret_cast<const __bf16 *>(s + sW3h), b, y);
+  hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)(bp / kRows)), dim3(256), 0, st,
+                     mlp_ptrs(state, scratch, bp), X, b, bp, y);
   return hipGetLastError();
 }
 
 hipError_t mlp_backward(void *state, int64_t b, const float *y, const float *target, float under,
                         float *loss, void *scratch, hipStream_t st) {
   if (b <= 0) return hipSuccess;
-  char *s = static_cast<char *>(state);
-  char *w = static_cast<char *>(scratch);
   const int64_t bp = (b + 31) / 32 * 32;
-  const Scratch L = scratch_layout(bp);
-  float *g = reinterpret_cast<float *>(s + sG);
-  hipLaunchKernelGGL(k_zero_f32, dim3(blocks(kP, 256)), dim3(256), 0, st, g, kP);
-  if (loss) hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(256), 0, st, loss, (int64_t)1);
-  hipLaunchKernelGGL(k_head_bwd, dim3(blocks(bp, 256)), dim3(256), 0, st,
-                     reinterpret_cast<const float *>(w + L.h2), y, target,
-                     reinterpret_cast<const __bf16 *>(s + sW3h), b, bp, under, g, loss,
-                     reinterpret_cast<__bf16 *>(w + L.dh2h), reinterpret_cast<__bf16 *>(w + L.dh2ht));
-  // dW2 = dH2^T H1  (128 x 128, contraction over the batch)
-  MmArgs a{};
-  a.A = reinterpret_cast<const __bf16 *>(w + L.dh2ht);
-  a.Bt = reinterpret_cast<const __bf16 *>(w + L.h1ht);
-  a.M = kH;
-  a.N = kH;
-  a.K = bp;
-  a.mode = 0;
-  a.Cf = g + oW2;
-  hipLaunchKernelGGL(k_mm_bf16, dim3(blocks((kH / 32) * (kH / 32), 4)), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(128), 0, st,
-                     reinterpret_cast<const __bf16 *>(w + L.dh2h), bp, kH, g + oB2);
-  // dH1 = (dH2 W2) * [H1 > 0]   (bp x 128)
-  MmArgs d{};
-  d.A = reinterpret_cast<const __bf16 *>(w + L.dh2h);
-  d.Bt = reinterpret_cast<const __bf16 *>(s + sW2th);
-  d.M = bp;
-  d.N = kH;
-  d.K = kH;
-  d.mode = 2;
-  d.mask = reinterpret_cast<const float *>(w + L.h1);
-  d.Ch = reinterpret_cast<__bf16 *>(w + L.dh1h);
-  d.Cht = reinterpret_cast<__bf16 *>(w + L.dh1ht);
-  hipLaunchKernelGGL(k_mm_bf16, dim3(blocks((bp / 32) * (kH / 32), 4)), dim3(256), 0, st, d);
-  // dW1 = dH1^T X  (128 x 64)
-  MmArgs e{};
-  e.A = reinterpret_cast<const __bf16 *>(w + L.dh1ht);
-  e.Bt = reinterpret_cast<const __bf16 *>(w + L.xht);
-  e.M = kH;
-  e.N = kIn;
-  e.K = bp;
-  e.mode = 0;
-  e.Cf = g + oW1;
-  hipLaunchKernelGGL(k_mm_bf16, dim3(blocks((kH / 32) * (kIn / 32), 4)), dim3(256), 0, st, e);
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(128), 0, st,
-                     reinterpret_cast<const __bf16 *>(w + L.dh1h), bp, kH, g + oB1);
+  const MlpPtrs p = mlp_ptrs(state, scratch, bp);
+  hipLaunchKernelGGL(k_mlp_bwd_rows, dim3((unsigned)(bp / kRows)), dim3(256), 0, st, p, y, target,
+                     under, b, bp);
+  hipLaunchKernelGGL(k_mlp_bwd_sums, dim3(kSumBlocks), dim3(512), 0, st, p, y, target, under, loss, b,
+                     bp);
   return hipGetLastError();
 }
 

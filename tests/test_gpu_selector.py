@@ -104,6 +104,14 @@ def test_mlp_forward_backward_match_oracle(batch):
     assert stage_violations(theta, X, t, 4.0, y_gpu, g, inter) == []
 
 
+# the batch sums take four 16-row steps of a wave together from 32 steps (512 rows) on and 256 rows
+# of the head at a time: whole and ragged remainders of both, and a batch of whole 32-row blocks
+@pytest.mark.parametrize("batch", [32, 33, 511, 513, 1061])
+def test_mlp_batch_sums_at_the_edges_of_their_steps(batch):
+    test_mlp_forward_backward_match_oracle(batch)
+
+
+
 def test_adam_step_matches_oracle():
     theta = _theta(3)
     st = _state_with(theta)
