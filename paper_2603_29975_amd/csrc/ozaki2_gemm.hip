@@ -26,7 +26,8 @@
 // instruction) in the packed layout of the slices, so every access is one
 // contiguous 16-byte run per lane. A plain product gives each fragment only
 // IB MFMAs, so a stage holds KS blocks and the ring runs (NBUF - 1) KS blocks
-// ahead to cover the memory latency.
+// ahead to cover the memory latency. (The packed layout is made for 16x16x64
+// MFMAs; the copies gather each 32 x 32 fragment from it in runs of 256 bytes.)
 //
 // INT32 range: odd moduli have residues |r| <= 127 and K' <= 2^17 keeps every
 // sum exact; for m = 256 the accumulator wraps modulo 2^32, which keeps the
@@ -118,14 +119,16 @@ __global__ void __launch_bounds__(64 * kNW, 1) k_oz2gemm(Oz2Args G) {
       src = G.RA + (ti * NQB + (wave - kWJ)) * nkb * kFragBytes;
       plane = planeA;
     }
-    src += lane * 16;
+    // lane 32 h + r takes row r, entries 16 h .. +15 of its 32-entry block, half
+    // a 64-entry fragment of its 16-row block
+    src += ((lane >> 4) & 1) * (nkb >> 1) * kFragBytes + (lane >> 5) * 256 + (lane & 15) * 16;
     // issue pointer: the next step to copy, as (modulus, first block)
     int64_t ik = 0, ikb = 0;
     auto issue = [&](int buf) {
       if (wave < NF) {
 #pragma unroll
         for (int x = 0; x < KS; ++x)
-          tile::copy_frag(src + ik * plane + (ikb + x) * kFragBytes,
+          tile::copy_frag(src + ik * plane + ((ikb + x) >> 1) * kFragBytes + ((ikb + x) & 1) * 512,
                           lds + buf * STAGE + (wave * KS + x) * kFragBytes);
       }
       ikb += KS;

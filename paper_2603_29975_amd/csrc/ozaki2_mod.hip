@@ -76,156 +76,152 @@ __device__ __forceinline__ uint32_t residue4(const ModConst &mc, bool first, int
 }
 
 // One work item is one output tile of one modulus. WJ x WI waves, JB x IB
-// blocks of 32 x 32 per wave (MFMA rows: j', columns: i). The contraction runs
-// in stages of KS 32-entry blocks through an LDS ring of NBUF stages filled by
-// direct-to-LDS copies. The fragments of block b + 1 are read into a second
-// register set, one read after each MFMA of block b, so a wave never waits out
-// an LDS latency; the stage's copies are issued the same way. Two workgroups
-// share a CU: one's reduction to bytes runs under the other's MFMAs.
-template <int WJ, int WI, int JB, int IB, int NBUF, int KS, int WPS>
+// blocks of 16 x 16 per wave (MFMA rows: j', columns: i), v_mfma_i32_16x16x64_i8.
+// The contraction runs in 64-entry blocks through an LDS ring of four stages
+// filled by direct-to-LDS copies. A wave holds the A' fragments of a block in
+// registers and streams the B' ones past them, LA ahead; the next block's A'
+// fragments, its first B' ones and the copies of the block after the next but
+// one follow a barrier in the middle of a block, so no LDS latency is waited
+// out.
+template <int WJ, int WI, int JB, int IB, int WPS>
 __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_oz2mod(Oz2ModArgs G) {
   constexpr int NW = WJ * WI;
-  constexpr int NFP = WJ * JB, NFQ = WI * IB, NF = NFP + NFQ;
-  constexpr int NC = NF * KS;   // copies per stage
-  constexpr int CPW = NC / NW;  // per wave
-  constexpr int STAGE = NC * kFragBytes;
-  constexpr int D = NBUF - 1;
-  constexpr int NM = JB * IB, NR = JB + IB;
-  static_assert(NC % NW == 0 && KS % 2 == 0 && D >= 2, "ring");
-  constexpr int RPM = (NR + NM - 1) / NM, CPM = (CPW + NM - 1) / NM;
-  static_assert((D - 2) * CPW < 64, "vmcnt immediate (6 bits)");
+  constexpr int NBUF = 4, D = NBUF - 1;
+  constexpr int FJ = WJ * JB, FI = WI * IB, NF = FJ + FI;  // 16-row blocks per tile
+  constexpr int CPW = NF / NW;                             // copies per wave and block
+  constexpr int STAGE = NF * kFragBytes;
+  constexpr int LA = JB > 2 ? 2 : 1, R = 2 * LA;           // B' look-ahead and slots
+  constexpr int MID = JB / 2;
+  static_assert(NF % NW == 0 && JB % R == 0 && JB - LA >= MID, "schedule");
+  static_assert(CPW < 64, "vmcnt immediate (6 bits)");
+  static_assert(NBUF * STAGE * (4 * WPS / NW) <= 160 * 1024, "LDS");
   __shared__ __attribute__((aligned(16))) int8_t lds[NBUF * STAGE];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int wj = wave % WJ, wi = wave / WJ;
-  const int64_t nkb = G.nkb;  // a multiple of KS
-  const int nst = (int)(nkb / KS);
-  const int64_t ntj = (G.jn + 32 * NFP - 1) / (32 * NFP), nti = (G.m + 32 * NFQ - 1) / (32 * NFQ);
+  const uint32_t lane16 = lane * 16;
+  const int nkb = (int)(G.nkb >> 1);  // even: the contraction is padded to 128
+  const int64_t rowst = (int64_t)nkb * kFragBytes;
+  const int64_t ntj = (G.jn + 16 * FJ - 1) / (16 * FJ), nti = (G.m + 16 * FI - 1) / (16 * FI);
   const int64_t ntiles = ntj * nti, nitems = ntiles * G.n;
 
   for (int64_t item0 = blockIdx.x; item0 < nitems; item0 += gridDim.x) {
     const int64_t item = tile::xcd_major(item0, nitems);
     const int k = (int)(item / ntiles);
     int64_t tj, ti;
-    tile::tile_coords(item - k * ntiles, 3, G.m, G.jn, 32 * NFP, 32 * NFQ, tj, ti);
+    tile::tile_coords(item - k * ntiles, 3, G.m, G.jn, 16 * FJ, 16 * FI, tj, ti);
 
-    // sources of this wave's copies: copy c = wave * CPW + y moves block c % KS
-    // of fragment row c / KS. Row blocks past the padded operand repeat its
-    // last one (their products are not stored).
+    // sources of this wave's copies: fragment rows wave * CPW + y. Row blocks
+    // past the padded operand repeat its last one (their products are not
+    // stored).
     const int8_t *src[CPW];
 #pragma unroll
     for (int y = 0; y < CPW; ++y) {
-      const int c = wave * CPW + y, f = c / KS;
+      const int f = wave * CPW + y;
       int64_t rb;
       const int8_t *base;
-      if (f < NFP) {
-        rb = G.jrb + tj * NFP + f;
-        rb = rb < G.nrbP ? rb : G.nrbP - 1;
-        base = G.RB + (k * G.nrbP + rb) * nkb * kFragBytes;
+      if (f < FJ) {
+        rb = G.jrb * 2 + tj * FJ + f;
+        rb = rb < G.nrbP * 2 ? rb : G.nrbP * 2 - 1;
+        base = G.RB + (k * G.nrbP * 2 + rb) * rowst;
       } else {
-        rb = ti * NFQ + (f - NFP);
-        rb = rb < G.nrbQ ? rb : G.nrbQ - 1;
-        base = G.RA + (k * G.nrbQ + rb) * nkb * kFragBytes;
+        rb = ti * FI + (f - FJ);
+        rb = rb < G.nrbQ * 2 ? rb : G.nrbQ * 2 - 1;
+        base = G.RA + (k * G.nrbQ * 2 + rb) * rowst;
       }
-      src[y] = base + (c % KS) * kFragBytes;
+      src[y] = base;
     }
-    auto copy = [&](int y, int st, int buf) {
-      tile::copy_frag(src[y] + (int64_t)st * (KS * kFragBytes) + lane * 16,
-                      lds + buf * STAGE + (wave * CPW + y) * kFragBytes);
+    auto copy = [&](int y, uint32_t voff, int buf) {
+      tile::copy_frag_s(src[y], voff, lds + buf * STAGE + (wave * CPW + y) * kFragBytes);
     };
 
-    v16i acc[JB][IB];
+    v4i acc[JB][IB];
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-      for (int ib = 0; ib < IB; ++ib) acc[jb][ib] = v16i{0};
+      for (int ib = 0; ib < IB; ++ib) acc[jb][ib] = v4i{0};
 
 #pragma unroll
     for (int d = 0; d < D; ++d)
-      if (d < nst) {
+      if (d < nkb) {
 #pragma unroll
-        for (int y = 0; y < CPW; ++y) copy(y, d, d);
+        for (int y = 0; y < CPW; ++y) copy(y, lane16 + d * kFragBytes, d);
       }
-    // stage 0 has landed once at most the younger stages' copies are in flight
-    if (nst >= D)
+    // block 0 has landed once at most the younger blocks' copies are in flight
+    if (nkb >= D)
       tile::wait_vmcnt<(D - 1) * CPW>();
     else
       tile::wait_vmcnt<0>();
     tile::barrier_only();
 
-    v4i pf[2][JB], qf[2][IB];
-    // fragment read r of block x of the stage at L into register set s
-    auto read = [&](int r, int s, const int8_t *L, int x) {
-      if (r < IB)
-        qf[s][r] = *reinterpret_cast<const v4i *>(L + ((NFP + wi * IB + r) * KS + x) * kFragBytes);
-      else
-        pf[s][r - IB] = *reinterpret_cast<const v4i *>(L + ((wj * JB + r - IB) * KS + x) * kFragBytes);
-    };
-    const int8_t *L = lds + lane * 16;
+    v4i pf[R], qf[2][IB];
+    uint32_t lb = tile::lds_addr(lds) + lane16 + wj * JB * kFragBytes;
+    uint32_t lq = tile::lds_addr(lds) + lane16 + (FJ + wi * IB) * kFragBytes;
+    asm volatile("" : "+v"(lb), "+v"(lq));
 #pragma unroll
-    for (int r = 0; r < NR; ++r) read(r, 0, L, 0);
+    for (int ib = 0; ib < IB; ++ib) qf[0][ib] = tile::lds_read(lq + ib * kFragBytes);
+#pragma unroll
+    for (int jb = 0; jb < LA; ++jb) pf[jb] = tile::lds_read(lb + jb * kFragBytes);
 
     int buf = 0;
-    for (int st = 0; st < nst; ++st) {
-      const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
+    for (int kb0 = 0; kb0 < nkb; kb0 += 2) {
 #pragma unroll
-      for (int x = 0; x < KS; ++x) {
-        const int s = x & 1;
-        const bool last = x == KS - 1;
-        const bool more = !last || st + 1 < nst;
-        bool refill = false;
-        int rbuf = 0;
-        if (last && st + 1 < nst) {
-          // The next stage's copies of this wave have landed, then every
-          // wave's; all reads of the stage before this one have been used, so
-          // its buffer can be refilled.
-          if (D > 2 && st + D < nst)
-            tile::wait_vmcnt<(D - 2) * CPW>();
-          else
-            tile::wait_vmcnt<0>();
-          tile::barrier_only();
-          refill = st + D < nst;
-          rbuf = buf + D >= NBUF ? buf + D - NBUF : buf + D;
-        }
-        const int8_t *Ln = lds + (last ? nbuf : buf) * STAGE + lane * 16;
-        const int xn = last ? 0 : x + 1;
+      for (int s = 0; s < 2; ++s) {
+        const int kb = kb0 + s;
+        const int nbuf = (buf + 1) & (NBUF - 1), fbuf = (buf + D) & (NBUF - 1);
+        const uint32_t co = buf * STAGE, no = nbuf * STAGE;
+        const bool fill = kb + D < nkb;
+        const uint32_t voff = lane16 + (uint32_t)(kb + D) * kFragBytes;
 #pragma unroll
-        for (int i = 0; i < NM; ++i) {
-          const int jb = i / IB, ib = i % IB;
-          if (more)
+        for (int jb = 0; jb < JB; ++jb) {
+          if (jb == MID) {
+            // the next block has landed: this wave's copies, then every wave's;
+            // all reads of the block before this one have been used
+            if (kb + D <= nkb)
+              tile::wait_vmcnt<(D - 2) * CPW>();
+            else
+              tile::wait_vmcnt<0>();
+            tile::barrier_only();
+          }
+          const int n = jb + LA;
+          pf[n % R] = tile::lds_read(lb + (n < JB ? co : no) + (n % JB) * kFragBytes);
+          if (jb >= MID) {
 #pragma unroll
-            for (int r = i * RPM; r < (i + 1) * RPM && r < NR; ++r) read(r, s ^ 1, Ln, xn);
-          acc[jb][ib] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf[s][jb], qf[s][ib], acc[jb][ib], 0, 0, 0);
-          if (last && refill) {
+            for (int ib = 0; ib < IB; ++ib)
+              if (ib * (JB - MID) / IB == jb - MID) qf[s ^ 1][ib] = tile::lds_read(lq + no + ib * kFragBytes);
+            if (fill) {
 #pragma unroll
-            for (int y = i * CPM; y < (i + 1) * CPM && y < CPW; ++y) copy(y, st + D, rbuf);
+              for (int y = 0; y < CPW; ++y)
+                if (y * (JB - MID) / CPW == jb - MID) copy(y, voff, fbuf);
+            }
           }
           __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int ib = 0; ib < IB; ++ib)
+            acc[jb][ib] = __builtin_amdgcn_mfma_i32_16x16x64_i8(pf[jb % R], qf[s][ib], acc[jb][ib], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
         }
+        buf = nbuf;
       }
-      buf = nbuf;
     }
     // every wave is done reading the ring before the next item refills it
     tile::barrier_only();
 
     // ---------------------------------------------------------- residue bytes
-    // Lane register 4 g + b of a block holds j' = 32 block + 8 g + 4 (lane / 32)
-    // + b, row i = lane % 32: four consecutive j' of one row are one word.
+    // Lane register r of a block holds j' = 16 block + 4 (lane / 16) + r, row i =
+    // lane % 16: four consecutive j' of one row are one word.
     const ModConst mc = kMod.c[k];
     uint32_t *out = reinterpret_cast<uint32_t *>(G.planes) + k * G.plane_words;
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
-      const int64_t i = ti * (32 * NFQ) + (wi * IB + ib) * 32 + (lane & 31);
+      const int64_t i = (ti * FI + wi * IB + ib) * 16 + (lane & 15);
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int64_t jq = tj * (8 * NFP) + (wj * JB + jb) * 8 + 2 * g + (lane >> 5);
-          const uint32_t w = residue4(mc, k == 0, acc[jb][ib][4 * g], acc[jb][ib][4 * g + 1],
-                                      acc[jb][ib][4 * g + 2], acc[jb][ib][4 * g + 3]);
-          if (i < G.m && 4 * jq < G.jn) out[jq * G.ldq + i] = w;
-        }
+        const int64_t jq = (tj * FJ + wj * JB + jb) * 4 + (lane >> 4);
+        const v4i &c = acc[jb][ib];
+        const uint32_t w = residue4(mc, k == 0, c[0], c[1], c[2], c[3]);
+        if (i < G.m && 4 * jq < G.jn) out[jq * G.ldq + i] = w;
       }
     }
   }
@@ -465,15 +461,12 @@ __global__ void __launch_bounds__(256) k_oz2rebuild(Oz2ModArgs G) {
   }
 }
 
-template <int WJ, int WI, int JB, int IB, int NBUF, int KS, int WPS>
+template <int WJ, int WI, int JB, int IB, int WPS>
 hipError_t launch_mod(const Oz2ModArgs &a, int num_cu, hipStream_t st) {
-  const int64_t ntj = (a.jn + 32 * WJ * JB - 1) / (32 * WJ * JB);
-  const int64_t nti = (a.m + 32 * WI * IB - 1) / (32 * WI * IB);
-  const int64_t per_cu = 4 * WPS / (WJ * WI);
-  const int64_t grid = std::min<int64_t>(ntj * nti * a.n, per_cu * num_cu);
-  if (a.nkb % KS != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_oz2mod<WJ, WI, JB, IB, NBUF, KS, WPS>), dim3((unsigned)grid),
-                     dim3(64 * WJ * WI), 0, st, a);
+  const int64_t ntj = (a.jn + 16 * WJ * JB - 1) / (16 * WJ * JB);
+  const int64_t nti = (a.m + 16 * WI * IB - 1) / (16 * WI * IB);
+  const int64_t grid = std::min<int64_t>(ntj * nti * a.n, (int64_t)(4 * WPS / (WJ * WI)) * num_cu);
+  hipLaunchKernelGGL((k_oz2mod<WJ, WI, JB, IB, WPS>), dim3((unsigned)grid), dim3(64 * WJ * WI), 0, st, a);
   return hipGetLastError();
 }
 
@@ -492,11 +485,11 @@ hipError_t launch_oz2mod(const Oz2ModArgs &a, int num_cu, hipStream_t st) {
   auto items = [&](int64_t t) { return ((a.m + t - 1) / t) * ((a.jn + t - 1) / t) * a.n; };
   hipError_t e;
   if (items(256) * 4 >= 3 * (int64_t)num_cu)
-    e = launch_mod<2, 4, 4, 2, 4, 2, 2>(a, num_cu, st);
+    e = launch_mod<2, 4, 8, 4, 2>(a, num_cu, st);
   else if (items(128) >= num_cu)
-    e = launch_mod<2, 2, 2, 2, 4, 2, 2>(a, num_cu, st);
+    e = launch_mod<2, 2, 4, 4, 2>(a, num_cu, st);
   else
-    e = launch_mod<2, 2, 1, 1, 4, 2, 2>(a, num_cu, st);
+    e = launch_mod<2, 2, 2, 2, 2>(a, num_cu, st);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)((a.m + 255) / 256), (unsigned)((a.jn + 3) / 4));
   switch (a.n) {

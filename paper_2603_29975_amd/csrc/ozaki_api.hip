@@ -229,7 +229,7 @@ Plan make_plan(bool cplx, int64_t m, int64_t n, int64_t k, int S, int num_cu, bo
   p.off_SB = off;
   off += align256((size_t)S * p.nrbP * 32 * p.kpad);
   p.off_flush = off;
-  if (p.nkb > p.kb_chunk) off += align256(gemm_flush_bytes(S, 0, num_cu));
+  if (p.nkb > p.kb_chunk) off += align256(gemm_flush_bytes(S, num_cu));
   p.total = off;
   return p;
 }
@@ -387,7 +387,6 @@ GemmArgs gemm_args(const Plan &p, char *ws, double ar, double ai, double br, dou
   a.flush_ws = reinterpret_cast<int64_t *>(ws + p.off_flush);
   a.kb_chunk = p.kb_chunk;
   a.chunked = p.nkb > p.kb_chunk ? 1 : 0;
-  a.split = (a.chunked && p.nkb <= kb_split_for(p.S, p.b8)) ? 1 : 0;
   a.max_groups = g.grid_limit;
   return a;
 }
@@ -854,8 +853,9 @@ int enqueue_plan(const BatchedPlan &pl, hipStream_t st, bool capturing) {
 
 // Builds (or finds) the plan of a validated batched call.
 // Tile configuration of the grouped GEMM of batched calls: OZAKI_BATCHED_CONFIG
-// (a tuning id) or the default 8, the four-wave 64 x 64 tiles (two workgroups
-// per CU), which waste less padding on the small problems of a batch.
+// (a tuning id) or the default 13: 128 x 128 tiles up to 6 slices, then 128 x 64,
+// along the columns. 512 problems of sides 32..1024, GEMM at s = 5, 6, 7, 8, 9:
+// 631, 779, 965, 1125, 1362 us, with 64 x 64 tiles 667, 798, 1116, 1270, 1424.
 int batched_tune_id() {
   static int id = -2;
   if (id == -2) {
@@ -863,7 +863,7 @@ int batched_tune_id() {
     id = (e != nullptr && *e) ? atoi(e) : -1;
     if (id >= gemm_num_configs()) id = -1;
   }
-  return id >= 0 ? id : 8;
+  return id >= 0 ? id : 13;
 }
 
 // Lays out one batched plan: problem descriptors, scan and split task tables,
@@ -915,7 +915,7 @@ int build_plan(const char *transa, const char *transb, const int64_t *m, const i
     prob_ws.push_back(ws_total);
     ws_total += align256(p.off_flush);  // codes and packed operands (carry space is shared)
     prob_S.push_back(slices[b]);
-    if (p.nkb > p.kb_chunk) flush_bytes = std::max(flush_bytes, gemm_flush_bytes(p.S, 0, num_cu));
+    if (p.nkb > p.kb_chunk) flush_bytes = std::max(flush_bytes, gemm_flush_bytes(p.S, num_cu));
     GemmProblem gp = gemm_problem(p, nullptr, alpha[b].re, alpha[b].im, beta[b].re, beta[b].im,
                                   beta_zero, C[b], ldc[b], nullptr);
     gp.unscaled = unscaled ? 1 : 0;

@@ -17,7 +17,7 @@ constexpr int kCodeBias = 2048;        // exponent code = e + bias (zero -> 0)
 constexpr int kCodeBad = 0x7fff0000;   // row/column holds Inf or NaN
 constexpr int64_t kRowPad = 128;       // packed operand rows are padded to this
 constexpr int64_t kKPad = 64;          // packed contraction length padded to this
-constexpr int kFragBytes = 1024;       // one packed 32 x 32 int8 fragment
+constexpr int kFragBytes = 1024;       // one packed 16 x 64 int8 fragment
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -84,16 +84,17 @@ __device__ __forceinline__ int digit(const Sig &x, int p) {
 
 // ---------------------------------------------------------------- packed layout
 // A packed operand X' (R' rows, K' contraction entries, both zero padded) is a
-// sequence of 1 KiB fragments indexed [p][rb][kb] (slice, 32-row block,
-// 32-entry contraction block). Inside a fragment byte (h*32 + r)*16 + b holds
-// row 32*rb + r, contraction index 32*kb + 16*h + b: exactly the 16 bytes that
-// lane (h*32 + r) of a 64-lane wave feeds to a 32x32x32 INT8 MFMA. A wave
-// therefore moves a fragment with one contiguous 16-byte access per lane.
+// sequence of 1 KiB fragments indexed [p][rb][kb] (slice, 16-row block, 64-entry
+// contraction block). Inside a fragment byte (h*16 + r)*16 + b holds row 16*rb +
+// r, contraction index 64*kb + 16*h + b: exactly the 16 bytes that lane (h*16 +
+// r) of a 64-lane wave feeds to a 16x16x64 INT8 MFMA. A wave therefore moves a
+// fragment with one contiguous 16-byte access per lane. The sizes of a packed
+// operand are counted in 32-row blocks (nrb) and 32-entry blocks (nkb, even).
 __host__ __device__ __forceinline__ int64_t frag_offset(int p, int64_t row, int64_t kk,
                                                         int64_t nrb, int64_t nkb) {
-  const int64_t rb = row >> 5, kb = kk >> 5;
-  const int64_t ri = row & 31, ki = kk & 31;
-  return (((int64_t)p * nrb + rb) * nkb + kb) * kFragBytes + (((ki >> 4) * 32 + ri) * 16) +
+  const int64_t rb = row >> 4, kb = kk >> 6;
+  const int64_t ri = row & 15, ki = kk & 63;
+  return (((int64_t)p * 2 * nrb + rb) * (nkb >> 1) + kb) * kFragBytes + (((ki >> 4) * 16 + ri) * 16) +
          (ki & 15);
 }
 

@@ -9,11 +9,11 @@
 // it again.
 //
 // Work: a tile table of 64 x 64 output tiles (j' x i) over the problems; each
-// of the 4 waves owns one 32 x 32 block, loads its B' and A' fragments of
-// every slice pair of the diagonal straight from the packed operands (one
-// contiguous 16-byte run per lane) and accumulates with
-// v_mfma_i32_32x32x32_i8; INT32 partial sums are carried into int64 before
-// (d - 1) * 32 * kb * 127^2 could reach 2^31. Only problems flagged for a
+// of the 4 waves owns one 32 x 32 block (2 x 2 MFMA blocks), loads its B' and A'
+// fragments of every slice pair of the diagonal straight from the packed
+// operands (one contiguous 16-byte run per lane) and accumulates with
+// v_mfma_i32_16x16x64_i8; INT32 partial sums are carried into int64 before
+// (d - 1) * 64 * kb * 127^2 could reach 2^31. Only problems flagged for a
 // raise do any work (flag[id] == 1); the others' tiles return at once.
 #include "ozaki_gemm_tile.hpp"
 
@@ -35,54 +35,72 @@ __global__ void __launch_bounds__(256) k_add_diagonal(const DiagTask *tasks, con
   const int64_t ntj = (tk.nprime + kDiagTile - 1) / kDiagTile;
   const int64_t local = tile_local[blockIdx.x];
   const int64_t tj = local % ntj, ti = local / ntj;
-  const int64_t rbP = tj * 2 + wj, rbQ = ti * 2 + wi;
-  const int64_t nkb = tk.nkb;
-  const int64_t planeP = tk.nrbP * nkb * kFragBytes, planeQ = tk.nrbQ * nkb * kFragBytes;
-  const int8_t *bp = tk.SP + rbP * nkb * kFragBytes + lane * 16;
-  const int8_t *aq = tk.SQ + rbQ * nkb * kFragBytes + lane * 16;
-  const int64_t chunk = tile::chunk_blocks(d - 1);
+  const int64_t nkb = tk.nkb >> 1;  // blocks of 64 contraction entries
+  const int64_t rowst = nkb * kFragBytes;
+  const int64_t planeP = tk.nrbP * 2 * rowst, planeQ = tk.nrbQ * 2 * rowst;
+  const int8_t *bp = tk.SP + (tj * 4 + wj * 2) * rowst + lane * 16;
+  const int8_t *aq = tk.SQ + (ti * 4 + wi * 2) * rowst + lane * 16;
+  const int64_t chunk = tile::chunk_blocks(d - 1) >> 1;
 
-  int64_t tot[16];
+  int64_t tot[2][2][4];
+  v4i acc[2][2];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) tot[r] = 0;
-  v16i acc = v16i{0};
+  for (int x = 0; x < 4; ++x) {
+    acc[x >> 1][x & 1] = v4i{0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tot[x >> 1][x & 1][r] = 0;
+  }
   int64_t next = chunk;
   for (int64_t kb = 0; kb < nkb; ++kb) {
-    // four slice pairs per pass, their eight fragment loads issued together
+    // two slice pairs per pass, their eight fragment loads issued together
     // (past the last pair: the last pair's fragments again, not used)
-    for (int p0 = 1; p0 < d; p0 += 4) {
-      v4i bf[4], af[4];
+    for (int p0 = 1; p0 < d; p0 += 2) {
+      v4i bf[2][2], af[2][2];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
+      for (int x = 0; x < 2; ++x) {
         const int p = p0 + x < d ? p0 + x : d - 1;
-        bf[x] = *reinterpret_cast<const v4i *>(bp + (d - p - 1) * planeP + kb * kFragBytes);
-        af[x] = *reinterpret_cast<const v4i *>(aq + (p - 1) * planeQ + kb * kFragBytes);
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          bf[x][y] = *reinterpret_cast<const v4i *>(bp + (d - p - 1) * planeP + y * rowst + kb * kFragBytes);
+          af[x][y] = *reinterpret_cast<const v4i *>(aq + (p - 1) * planeQ + y * rowst + kb * kFragBytes);
+        }
       }
 #pragma unroll
-      for (int x = 0; x < 4; ++x)
-        if (p0 + x < d) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[x], af[x], acc, 0, 0, 0);
+      for (int x = 0; x < 2; ++x)
+        if (p0 + x < d)
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            acc[y >> 1][y & 1] =
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[x][y >> 1], af[x][y & 1], acc[y >> 1][y & 1], 0, 0, 0);
     }
     if (kb + 1 == next || kb + 1 == nkb) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) tot[r] += (int64_t)acc[r];
-      acc = v16i{0};
+      for (int y = 0; y < 4; ++y) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tot[y >> 1][y & 1][r] += (int64_t)acc[y >> 1][y & 1][r];
+        acc[y >> 1][y & 1] = v4i{0};
+      }
       next += chunk;
     }
   }
 
-  // lane register r: output row i, column side j' = jbase + 8 (r / 4) + r % 4
-  const int64_t i = ti * kDiagTile + wi * 32 + (lane & 31);
-  if (i >= tk.m) return;
-  const int64_t jbase = tj * kDiagTile + wj * 32 + 4 * (lane >> 5);
+  // block (y, x), lane register r: row i, column side j' = jbase + r
   const int w = tk.woff - tk.wbits * d;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int64_t jp = jbase + 8 * (r >> 2) + (r & 3);
-    if (jp >= tk.nprime) continue;
-    // complex: j' = 2 j + c is part c of column j
-    double *pp = tk.cplx ? reinterpret_cast<double *>(tk.P) + 2 * (i + (jp >> 1) * tk.m) + (jp & 1)
-                         : reinterpret_cast<double *>(tk.P) + i + jp * tk.m;
-    *pp = add_rn(*pp, ldexp((double)tot[r], w));
+  for (int x = 0; x < 2; ++x) {
+    const int64_t i = ti * kDiagTile + wi * 32 + x * 16 + (lane & 15);
+    if (i >= tk.m) continue;
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t jp = tj * kDiagTile + wj * 32 + y * 16 + 4 * (lane >> 4) + r;
+        if (jp >= tk.nprime) continue;
+        // complex: j' = 2 j + c is part c of column j
+        double *pp = tk.cplx ? reinterpret_cast<double *>(tk.P) + 2 * (i + (jp >> 1) * tk.m) + (jp & 1)
+                             : reinterpret_cast<double *>(tk.P) + i + jp * tk.m;
+        *pp = add_rn(*pp, ldexp((double)tot[y][x][r], w));
+      }
   }
 }
 

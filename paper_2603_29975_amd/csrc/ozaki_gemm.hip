@@ -4,425 +4,483 @@
 // in higher precision" of the Ozaki-I scheme (Section 2.2 of the paper).
 //
 // Output orientation: the MFMA row index is the output column side j' and the
-// MFMA column index (lane % 32) is the output row i, so the 32 lanes of a
-// half-wave hold 32 consecutive rows of one column of C and every store of the
-// epilogue is a contiguous run in column-major C. For complex data j' = 2j + c
-// (c = 0 real, 1 imaginary part of column j), so a lane holds Re and Im of one
-// C entry in neighbouring accumulator registers and writes 16 bytes.
+// MFMA column index (lane % 16) is the output row i, so 16 lanes hold 16
+// consecutive rows of one column of C and every store of the epilogue is a
+// contiguous run in column-major C. For complex data j' = 2j + c (c = 0 real, 1
+// imaginary part of column j), so a lane holds Re and Im of one C entry in
+// neighbouring accumulator registers and writes 16 bytes.
 //
-// Work per workgroup tile (BJ = 32*WJ columns j', BI = 32*WI rows i), per wave
-// one 32 x 32 block with one INT32 accumulator set per diagonal t = 2..S+1:
-//   for each 32-wide contraction block:
-//     for p = 1..S, q = 1..S+1-p:  acc[p+q-2] += SB'_q(32x32) * SA'_p(32x32)^T
-// using v_mfma_i32_32x32x32_i8 (exact INT8 x INT8 -> INT32). Slice fragments
-// move from global memory straight into an NBUF-stage LDS ring with
+// Work per workgroup tile (BJ = 16 WJ columns j', BI = 16 WI IB rows i), per wave
+// IB blocks of 16 x 16 side by side along i with one INT32 accumulator set per
+// diagonal t = 2..S+1:
+//   for each 64-wide contraction block:
+//     for p = 1..S, q = 1..S+1-p:  acc[p+q-2] += SB'_q(16x64) * SA'_p(16x64)^T
+// using v_mfma_i32_16x16x64_i8 (exact INT8 x INT8 -> INT32).
+//
+// What bounds it is the chip's power: with random digits the clock falls to
+// 1.7-1.8 GHz while the matrix pipe is busy 70-80% of the time, and removing
+// stalls lowers the clock further, so the energy per product decides.
+//  - The 16x16x64 form keeps half as many accumulators per product as 32x32x32:
+//    bare MFMA loops on random operands run at 4.02 against 3.43 POP/s.
+//  - The copies into LDS are the largest other share (13%), so the tile is as
+//    large as the accumulators allow (128 x 128 up to S = 6, else 128 x 64),
+//    then the LDS reads (6%): each wave holds the B' fragments of all S slices
+//    of its 16 columns in registers and streams the A' fragments past them.
+// Measured per launch, here / 32x32x32 blocks with every LDS latency of a block
+// exposed behind its barrier: 2048^3 complex, 8-bit S = 6 441 / 542 us (0.65 of
+// the nominal INT8 rate), 4096^3 3.55 / 4.29 ms; 4096^3 real, 7-bit S = 7 1.22 /
+// 1.53 ms, 2048^3 complex S = 7 611 / 720 us.
+//
+// Slice fragments move from global memory straight into LDS with
 // global_load_lds_dwordx4 (one 1 KiB fragment per wave instruction, no staging
-// registers), issued NBUF-1 contraction blocks ahead of their use. Waits are
-// explicit (vmcnt for this wave's own copies, then s_barrier), because the
-// generic workgroup barrier would drain every copy in flight. The packed
-// fragment layout makes every global and LDS access one contiguous 16-byte
-// run per lane and the LDS reads conflict free. The triangle of pairs gives
-// natural operand reuse: each fragment feeds (S+1)/2 MFMAs on average.
+// registers). The packed fragment layout makes every global and LDS access one
+// contiguous 16-byte run per lane and the LDS reads conflict free. No LDS
+// latency is waited out: A' fragments are read LA ahead, also across the block
+// boundary, and B' slice q of the next block is read as soon as the slice is done
+// with, which needs the next block in LDS before this one ends. Two LDS plans
+// give that, both with explicit waits (vmcnt for this wave's own copies, then
+// s_barrier), because the generic workgroup barrier would drain every copy in
+// flight:
+//  RING  three stages of one contraction block; one barrier per block, after the
+//        first A' fragment: the next block has landed, the one after it is copied.
+//  else  (three stages do not fit) one buffer for B', two for A': a barrier X,
+//        when every wave has read its B' fragments, starts the copies of the
+//        next block, a barrier Y before the first read of the next B' ends them.
 //
-// INT32 range: a diagonal of S pairs over 32*kb contraction entries is bounded
-// by S * 32 * kb * 127^2. Past that bound a single product with one A' block
-// per wave splits each diagonal's pairs over two INT32 sets (p below or from
-// ceil(S/2)), which doubles the reach; beyond that, or with two A' blocks per
-// wave, the contraction is cut into chunks that keep each sum below 2^31 and
-// each chunk is carried exactly into int64 workgroup-private memory. The FP64 epilogue converts every S_t exactly (|S_t| < 2^53) and adds
-// them largest weight first, one rounding per addition, then scales by
-// 2^(e_i + f_j) and applies alpha/beta without fused multiply-adds.
+// INT32 range: a diagonal of S pairs over 64 * kb contraction entries is bounded
+// by S * 64 * kb * 127^2. Past that bound the contraction is cut into chunks
+// whose INT32 sums go to workgroup-private memory (as they are, for up to three
+// chunks, else added up in int64); the epilogue adds them in int64. At 16384^3
+// complex, S = 6, that is 25.8 GB of traffic, 2% of the time, where splitting
+// each diagonal over two INT32 sets needed the smaller tile. The FP64 epilogue
+// converts every S_t exactly (|S_t| < 2^53) and adds them largest weight first,
+// one rounding per addition, then scales by 2^(e_i + f_j) and applies alpha/beta
+// without fused multiply-adds.
+#include <type_traits>
+#include <utility>
+
 #include "ozaki_gemm_tile.hpp"
 
 namespace oz {
 
 namespace {
 
-template <int S, int WJ, int WI, int IB, int NBUF>
-struct Cfg {
-  static constexpr int NW = WJ * WI;
-  static constexpr int NT = 64 * NW;
-  static constexpr int BJ = 32 * WJ;
-  static constexpr int BI = 32 * WI * IB;
-  static constexpr int NQB = WI * IB;  // 32-row blocks of A' per tile
-  static constexpr int NFP = S * WJ;   // B' fragments per contraction block
-  static constexpr int NFQ = S * NQB;  // A' fragments per contraction block
-  static constexpr int NF = NFP + NFQ;
-  static constexpr int NFW = (NF + NW - 1) / NW;  // copies issued per wave (at most)
-  static constexpr int MINW = NF / NW;            // copies issued per wave (at least)
-  static constexpr int STAGE = NF * kFragBytes;
-  static constexpr int LDS = NBUF * STAGE;
-  static_assert(LDS <= 160 * 1024, "LDS ring too large");
-  static_assert(MINW < 64, "vmcnt immediate (6 bits)");
-};
-
 using tile::barrier_only;
 using tile::chunk_blocks;
 using tile::wait_vmcnt;
 
-template <int S, int WJ, int WI, int IB, int NBUF, bool RAW, bool CHUNKED, bool GROUPED,
-          bool EARLY, bool SPLIT = false>
-__global__ void __launch_bounds__(64 * WJ * WI, 512 / (64 * WJ * WI)) k_ozgemm(GemmArgs G) {
-  using C_ = Cfg<S, WJ, WI, IB, NBUF>;
-  static_assert(!(SPLIT && (CHUNKED || RAW)), "split accumulation replaces the carry");
-  constexpr int PM = tile::split_pm(S);
-  constexpr int XN = SPLIT ? tile::split_extra(S) : 0;
-  __shared__ __attribute__((aligned(16))) int8_t lds[C_::LDS];
+// The kernel's arguments and problem table in constant address space, so that
+// fields are fetched by scalar loads where they are used.
+typedef const __attribute__((address_space(4))) GemmArgs *ArgsPtr;
+typedef const __attribute__((address_space(4))) GemmProblem *ProblemPtr;
+typedef const __attribute__((address_space(4))) int *IntPtr;
+
+constexpr int kInt32Chunks = 3;  // up to so many chunks each keeps its own INT32 sums
+
+// f(0), ..., f(N - 1) with constant arguments.
+template <typename F, int... N>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, N...>, F f) {
+  (f(std::integral_constant<int, N>{}), ...);
+}
+
+template <int S, int WJ, int WI, int IB>
+struct Cfg {
+  static constexpr int NW = WJ * WI;
+  static constexpr int FJ = WJ, FI = WI * IB;  // 16-row blocks of B' and A' per tile
+  static constexpr int BJ = 16 * FJ, BI = 16 * FI;
+  static constexpr int RingBytes = 3 * S * (FJ + FI) * kFragBytes;
+  static constexpr int XyBytes = S * (FJ + 2 * FI) * kFragBytes;
+};
+
+// Word w of this wave's chunk sums, lane-interleaved: a wave-uniform base and a
+// 32-bit lane offset, so that the addresses cost no vector registers. The
+// accesses are device-scope, which keeps the traffic in L2, away from stale
+// lines of the non-coherent vector L1.
+template <typename T>
+__device__ __forceinline__ T *carry_word(char *base, int w, uint32_t lane) {
+  return reinterpret_cast<T *>(base + (int64_t)w * (64 * sizeof(T)) + lane * (uint32_t)sizeof(T));
+}
+
+template <int S, int WJ, int WI, int IB, int WPS, bool RING, int LA, bool RAW, bool CHUNKED>
+__global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
+  using C_ = Cfg<S, WJ, WI, IB>;
+  constexpr int NW = C_::NW, FJ = C_::FJ, FI = C_::FI;
+  constexpr int NCB = S * FJ, NCA = S * FI;  // copies per block
+  constexpr int XB = (NCB + NW - 1) / NW, XA = (NCA + NW - 1) / NW;
+  constexpr int XC = XB + XA;                // copies per wave and block (at most)
+  constexpr int MINC = NCB / NW + NCA / NW;  // at least
+  constexpr int STAGE = (NCB + NCA) * kFragBytes;
+  constexpr int LDS = RING ? C_::RingBytes : C_::XyBytes;
+  constexpr int NA = S * IB;  // A' fragments per block
+  constexpr int R = LA + 1;   // their register slots
+  // X (RING: the one barrier) comes when the first A' fragment is done with,
+  // which has used every B' slice of the block; Y before step S - 2 (0-based),
+  // which leaves its three slice pairs' MFMAs to cover the first reads of the
+  // next B'. The copies go out with the IB fragments after X. Spreading them
+  // further, or X and Y a step later or earlier, was at most 1% faster in one
+  // case and up to 12% slower in others.
+  constexpr int NX = 1, NY = (S - 2) * IB, PY = RING ? 1 : S - 2;
+  constexpr int WORDS = IB * S * 4;  // accumulator words per lane
+  static_assert(LDS * (4 * WPS / NW) <= 160 * 1024, "LDS");
+  static_assert(RING || S >= 4, "X before Y");
+  static_assert(NA - LA >= (RING ? NX : NY), "the look-ahead crosses into a block that has landed");
+  static_assert(MINC < 64, "vmcnt immediate (6 bits)");
+  __shared__ __attribute__((aligned(16))) int8_t lds[LDS];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // wave-uniform
   const int wj = wave % WJ;
   const int wi = wave / WJ;
-
-  constexpr bool chunked = CHUNKED;
-  const int64_t ntiles =
-      GROUPED ? G.ntiles
-              : ((G.one.nprime + C_::BJ - 1) / C_::BJ) * ((G.one.m + C_::BI - 1) / C_::BI);
+  const uint32_t lane16 = lane * 16;
+  const ArgsPtr ga = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const bool grouped = ga->probs != nullptr;
+  const int64_t ntiles = grouped ? ga->ntiles
+                                 : ((ga->one.nprime + C_::BJ - 1) / C_::BJ) *
+                                       ((ga->one.m + C_::BI - 1) / C_::BI);
 
   for (int64_t tn = blockIdx.x; tn < ntiles; tn += gridDim.x) {
-    // The problem this tile belongs to (uniform across the workgroup, so the
-    // descriptor is fetched with scalar loads).
-    const GemmProblem a = GROUPED ? G.probs[G.tile_prob[tn]] : G.one;
-    int64_t local = GROUPED ? (int64_t)G.tile_local[tn] : tn;
-    if (!GROUPED && G.order == 3) local = tile::xcd_major(tn, ntiles);
+    // The problem this tile belongs to (uniform across the workgroup).
+    ProblemPtr pr = grouped ? (ProblemPtr)(uint64_t)(ga->probs + ((IntPtr)(uint64_t)ga->tile_prob)[tn])
+                            : &ga->one;
     int64_t tj, ti;
-    tile::tile_coords(local, G.order, a.m, a.nprime, C_::BJ, C_::BI, tj, ti);
-    const int64_t nkb = a.nkb;
-
-    // Copy of contraction block kb into LDS stage `buf`: fragment f lands at
-    // stage offset f KiB (B' fragments first, then A' fragments).
-    auto issue = [&](int64_t kb, int buf) {
-#pragma unroll
-      for (int x = 0; x < C_::NFW; ++x) {
-        const int f = wave + x * C_::NW;
-        if (f >= C_::NF) break;
-        const int8_t *src;
-        if (f < C_::NFP) {
-          const int p = f / WJ, rb = f % WJ;
-          src = a.SP + (((int64_t)p * a.nrbP + tj * WJ + rb) * nkb + kb) * kFragBytes;
-        } else {
-          const int g = f - C_::NFP;
-          const int p = g / C_::NQB, rb = g % C_::NQB;
-          src = a.SQ + (((int64_t)p * a.nrbQ + ti * C_::NQB + rb) * nkb + kb) * kFragBytes;
-        }
-        tile::copy_frag(src + lane * 16, lds + buf * C_::STAGE + f * kFragBytes);
-      }
-    };
-
-    v16i acc[IB][S];
-    v16i accx[IB][XN > 0 ? XN : 1];
-#pragma unroll
-    for (int ib = 0; ib < IB; ++ib) {
-#pragma unroll
-      for (int t = 0; t < S; ++t) acc[ib][t] = v16i{0};
-#pragma unroll
-      for (int t = 0; t < XN; ++t) accx[ib][t] = v16i{0};
+    {
+      const int order = ga->order;
+      int64_t local = grouped ? (int64_t)((IntPtr)(uint64_t)ga->tile_local)[tn] : tn;
+      if (!grouped && order == 3) local = tile::xcd_major(tn, ntiles);
+      tile::tile_coords(local, order, pr->m, pr->nprime, C_::BJ, C_::BI, tj, ti);
     }
+    const int64_t nkb_all = pr->nkb >> 1;  // pr->nkb counts 32 entries
+    const int64_t rowst = nkb_all * kFragBytes;
+    const int64_t chunk = CHUNKED ? ga->kb_chunk >> 1 : nkb_all;
 
-    // Exact int64 carry of the INT32 accumulators (chunked contraction only).
-    int64_t *ws = G.flush_ws + ((int64_t)blockIdx.x * C_::NW + wave) * (int64_t)IB * S * 1024;
-    auto carry = [&](bool first) {
-#pragma unroll
-      for (int ib = 0; ib < IB; ++ib) tile::carry_block<S>(acc[ib], ws + ib * S * 1024, lane, first);
+    v4i acc[IB][S];
+    auto acc_word = [&](int w) { return acc[w / (4 * S)][w / 4 % S][w % 4]; };
+    // chunk sums of this wave: one INT32 slot per chunk carried, or (wide) int64
+    constexpr int64_t kSlot = (int64_t)NW * WORDS * 64 * sizeof(int32_t);
+    const bool wide = nkb_all > kInt32Chunks * chunk;
+    int slots = 0;
+    auto carry_base = [&]() {
+      return reinterpret_cast<char *>(ga->flush_ws) + blockIdx.x * (2 * kSlot) +
+             (int64_t)wave * (WORDS * 64) * (wide ? sizeof(int64_t) : sizeof(int32_t));
     };
 
-    constexpr int D = NBUF - 1;  // prefetch distance in contraction blocks
+    int64_t k0 = 0;
+    do {
+      const int nkb = CHUNKED ? (int)(nkb_all - k0 < chunk ? nkb_all - k0 : chunk) : (int)nkb_all;
+      // sources of this wave's copies at block k0: copy x moves fragment wave +
+      // x NW of the block's B' (then A') fragments, slice-major
+      const int8_t *src[XC];
+      {
+        const int64_t planeB = pr->nrbP * 2 * rowst, planeA = pr->nrbQ * 2 * rowst;
+        const int8_t *sp = pr->SP + (tj * FJ) * rowst + k0 * kFragBytes;
+        const int8_t *sq = pr->SQ + k0 * kFragBytes;
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-      if (d < nkb) issue(d, d);
+        for (int x = 0; x < XB; ++x) {
+          const int c = wave + x * NW;
+          src[x] = sp + (int64_t)(c / FJ) * planeB + (int64_t)(c % FJ) * rowst;
+        }
+#pragma unroll
+        for (int x = 0; x < XA; ++x) {
+          const int c = wave + x * NW;
+          src[XB + x] = sq + (int64_t)(c / FI) * planeA + (ti * FI + c % FI) * rowst;
+        }
+      }
+      // Copy x of block kb. b_buf, a_buf: LDS offsets of the block's B' and A'.
+      auto copy = [&](int x, uint32_t voff, int b_buf, int a_buf) {
+        const bool isb = x < XB;
+        const int c = wave + (isb ? x : x - XB) * NW;
+        if (isb ? (NCB % NW == 0 || c < NCB) : (NCA % NW == 0 || c < NCA))
+          tile::copy_frag_s(src[x], voff, lds + (isb ? b_buf : a_buf) + c * kFragBytes);
+      };
+      auto b_off = [&](int st) { return RING ? st * STAGE : 0; };
+      auto a_off = [&](int st) {
+        return RING ? st * STAGE + NCB * kFragBytes : (NCB + st * NCA) * kFragBytes;
+      };
 
-    int64_t next_flush = G.kb_chunk;
-    bool carried = false;
-    int buf = 0;
-    for (int64_t kb = 0; kb < nkb; ++kb) {
-      // This wave's copies of block kb are complete when at most the copies
-      // of the (up to D-1) younger blocks are in flight; the barrier then
-      // makes every wave's copies visible and retires the reads of the stage
-      // about to be refilled.
-      if constexpr (D >= 2) {
-        if (kb + 1 < nkb)
-          wait_vmcnt<C_::MINW>();
-        else
-          wait_vmcnt<0>();
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+        for (int t = 0; t < S; ++t) acc[ib][t] = v4i{0};
+
+      v4i pf[S], qf[R];
+      // LDS addresses of this wave's fragments in the first B' and A' buffer. (The
+      // asm keeps their constant parts out of the reads' offsets, which then fit
+      // the 16 bits of the instruction.)
+      uint32_t lb = tile::lds_addr(lds) + lane16 + wj * kFragBytes;
+      uint32_t lq = tile::lds_addr(lds) + lane16 + a_off(0) + wi * IB * kFragBytes;
+      asm volatile("" : "+v"(lb), "+v"(lq));
+      auto rdB = [&](int q, uint32_t base) { pf[q] = tile::lds_read(base + q * FJ * kFragBytes); };
+      auto rdA = [&](int n, int slot, uint32_t base) {  // fragment n = p IB + ib
+        qf[slot] = tile::lds_read(base + ((n / IB) * FI + n % IB) * kFragBytes);
+      };
+      constexpr int NST = RING ? 3 : 2;
+      constexpr uint32_t kStepB = RING ? STAGE : 0, kStepA = RING ? STAGE : NCA * kFragBytes;
+
+#pragma unroll
+      for (int x = 0; x < XC; ++x) copy(x, lane16, b_off(0), a_off(0));
+      if (RING && nkb > 1) {
+#pragma unroll
+        for (int x = 0; x < XC; ++x) copy(x, lane16 + kFragBytes, b_off(1), a_off(1));
+        wait_vmcnt<MINC>();
       } else {
         wait_vmcnt<0>();
       }
       barrier_only();
-      if (kb + D < nkb) {
-        int nb = buf + D;
-        if (nb >= NBUF) nb -= NBUF;
-        issue(kb + D, nb);
-      }
-      const int8_t *L = lds + buf * C_::STAGE;
-      // One MFMA of slice pair (p, q) into the set of diagonal p + q.
-      auto mfma = [&](int p, int q, int ib, const v4i &pq, const v4i &qp) {
-        if (XN > 0 && p >= PM)  // the second set of diagonal p + q
-          accx[ib][p + q - PM] =
-              __builtin_amdgcn_mfma_i32_32x32x32_i8(pq, qp, accx[ib][p + q - PM], 0, 0, 0);
-        else
-          acc[ib][p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pq, qp, acc[ib][p + q], 0, 0, 0);
-      };
-      auto read_q = [&](int p, int ib) {
-        return *reinterpret_cast<const v4i *>(L + (C_::NFP + p * C_::NQB + wi * IB + ib) * kFragBytes +
-                                              lane * 16);
-      };
-      if constexpr (!EARLY) {
-        // Left to itself the compiler reads each A' fragment just before its
-        // MFMAs (with two A' blocks per wave, into one register set: the
-        // fragments of every slice do not fit next to the 2 S accumulator
-        // sets) and waits out every LDS latency. Here the A' reads of slice
-        // p + 1 go out before the MFMAs of slice p (two register sets), the
-        // order pinned by scheduling barriers.
-        v4i pf[S], qa[IB], qb[IB];
 #pragma unroll
-        for (int ib = 0; ib < IB; ++ib) qa[ib] = read_q(0, ib);
-        pf[S - 1] = *reinterpret_cast<const v4i *>(L + ((S - 1) * WJ + wj) * kFragBytes + lane * 16);
+      for (int n = 0; n < LA; ++n) rdA(n, n, lq);
 #pragma unroll
-        for (int q = 0; q < S - 1; ++q)
-          pf[q] = *reinterpret_cast<const v4i *>(L + (q * WJ + wj) * kFragBytes + lane * 16);
+      for (int q = S - 1; q > 0; --q) rdB(q, lb);
+
+      int st = 0;
+      for (int kb = 0; kb < nkb; ++kb) {
+        const int st1 = st + 1 == NST ? 0 : st + 1;
+        const uint32_t bo = lb + st * kStepB, ao = lq + st * kStepA;
+        const uint32_t bn = lb + st1 * kStepB, an = lq + st1 * kStepA;
+        // blocks whose copies start in this one: the second next (RING) or the next
+        const int ahead = RING ? 2 : 1;
+        const int stc = RING ? (st1 + 1 == 3 ? 0 : st1 + 1) : st1;
+        const int bc = b_off(stc), ac = a_off(stc);
+        const uint32_t voff = lane16 + (uint32_t)(kb + ahead) * kFragBytes;
+        const bool fill = kb + ahead < nkb;
+        // The reads of the next block are unconditional: after the last one they
+        // fetch what LDS happens to hold, which nothing uses.
+        unrolled(std::make_integer_sequence<int, NA>{}, [&](auto nc) {
+          constexpr int n = decltype(nc)::value;
+          constexpr int p = n / IB, ib = n % IB;
+          if constexpr (n == NX) {
+            // RING: the next block's copies have landed, here and (after the
+            // barrier) in every wave. Otherwise X. Either way every wave has
+            // used its reads of the block before this one and of this B'.
+            if (RING) wait_vmcnt<0>();
+            barrier_only();
+          }
+          if constexpr (!RING && n == NY) {
+            wait_vmcnt<0>();
+            barrier_only();
+          }
+          rdA((n + LA) % NA, (n + LA) % R, n + LA < NA ? ao : an);
+          // B' slice 1 of this block (used last in the first step), then the
+          // next block's slices over those done with
+          if constexpr (n == 0) rdB(0, bo);
+          if constexpr (p >= 1 && p == PY) {
 #pragma unroll
-        for (int p = 0; p < S; ++p) {
-          if (p + 1 < S) {
+            for (int x = 0; x < PY; ++x)
+              if (x * IB / PY == ib) rdB(S - 1 - x, bn);
+          } else if constexpr (p > PY && ib == 0) {
+            rdB(S - p, bn);
+          }
+          if (n >= NX && n < NX + IB && fill) {
 #pragma unroll
-            for (int ib = 0; ib < IB; ++ib) qb[ib] = read_q(p + 1, ib);
+            for (int x = 0; x < XC; ++x)
+              if (x * IB / XC == n - NX) copy(x, voff, bc, ac);
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-#pragma unroll
-            for (int q = 0; q < S - p; ++q) mfma(p, q, ib, pf[q], qa[ib]);
+          for (int qq = 0; qq < S - p; ++qq) {
+            constexpr bool desc = p == 0;
+            const int q = desc ? S - 1 - qq : qq;
+            acc[ib][p + q] =
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(pf[q], qf[n % R], acc[ib][p + q], 0, 0, 0);
+          }
           __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (NA % R != 0) {
+          // the look-ahead fragments to the slots the next block expects
+          v4i tmp[LA];
 #pragma unroll
-          for (int ib = 0; ib < IB; ++ib) qa[ib] = qb[ib];
+          for (int n = 0; n < LA; ++n) tmp[n] = qf[(NA + n) % R];
+#pragma unroll
+          for (int n = 0; n < LA; ++n) qf[n] = tmp[n];
         }
-      } else {
-        // All fragment reads of the block are issued up front, A' of slice 1
-        // first; a wave's LDS reads return in order, so each MFMA waits only
-        // for the reads it needs and the later ones arrive under the earlier
-        // MFMAs.
-        v4i qf[S][IB];
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib) qf[0][ib] = read_q(0, ib);
-        // The compiler starts each block with the MFMA of the longest
-        // accumulation chain (slice pair 1, S), so B' slice S is read second.
-        v4i pf[S];
-        pf[S - 1] = *reinterpret_cast<const v4i *>(L + ((S - 1) * WJ + wj) * kFragBytes + lane * 16);
-#pragma unroll
-        for (int q = 0; q < S - 1; ++q)
-          pf[q] = *reinterpret_cast<const v4i *>(L + (q * WJ + wj) * kFragBytes + lane * 16);
-#pragma unroll
-        for (int p = 1; p < S; ++p)
-#pragma unroll
-          for (int ib = 0; ib < IB; ++ib) qf[p][ib] = read_q(p, ib);
-        // EARLY keeps the reads above the MFMAs (the scheduler would otherwise
-        // sink each A' read to just before its first use and expose its
-        // latency); for large S the registers of all fragments would not fit
-        if constexpr (EARLY && S * (1 + IB) <= 18) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int p = 0; p < S; ++p)
-#pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-#pragma unroll
-            for (int q = 0; q < S - p; ++q) mfma(p, q, ib, pf[q], qf[p][ib]);
+        st = st1;
       }
-      if constexpr (chunked) {
-        if (kb + 1 == next_flush && kb + 1 < nkb) {
-          carry(!carried);
-          carried = true;
-          next_flush += G.kb_chunk;
-          wait_vmcnt<0>();  // keep the in-order vmcnt accounting to LDS copies only
-        }
-      }
-      buf = buf + 1 == NBUF ? 0 : buf + 1;
-    }
-    // every wave is done reading the ring before the next tile refills it
-    barrier_only();
+      // every wave is done reading LDS before the next chunk or tile refills it
+      barrier_only();
 
-    if constexpr (chunked) carry(!carried);
+      if (CHUNKED && k0 + chunk < nkb_all) {
+        char *cb = carry_base();
+        if (!wide) {
+          cb += slots * kSlot;
+#pragma unroll
+          for (int w = 0; w < WORDS; ++w) {
+            __hip_atomic_store(carry_word<int32_t>(cb, w, lane), acc_word(w), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            if (w % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+#pragma unroll
+          for (int w = 0; w < WORDS; ++w) {
+            int64_t *p = carry_word<int64_t>(cb, w, lane);
+            const int64_t v = acc_word(w);
+            if (slots == 0)
+              __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+              __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (w % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        ++slots;
+        wait_vmcnt<0>();  // the copies' vmcnt counts stay to themselves
+      }
+      k0 += chunk;
+    } while (CHUNKED && k0 < nkb_all);
 
     // ------------------------------------------------------------ epilogue
+    // (the problem's fields are fetched again here, not kept through the loop)
+    asm volatile("" : "+s"(pr));
+    const int64_t i0 = ti * C_::BI + wi * IB * 16 + (lane & 15);
+    const int64_t j0 = tj * C_::BJ + wj * 16 + 4 * (lane >> 4);
+    unrolled(std::make_integer_sequence<int, IB>{}, [&](auto ibc) {
+      constexpr int ib = decltype(ibc)::value;
+      // The block with its chunk sums: none, one or two INT32 ones, or int64.
+      auto finish = [&](auto kind) {
+        constexpr int K = decltype(kind)::value;
+        auto total = [&](int t, int r) -> int64_t {
+          const int w = (ib * S + t) * 4 + r;
+          int64_t v = acc[ib][t][r];
+          if constexpr (K == 3)
+            v += __hip_atomic_load(carry_word<int64_t>(carry_base(), w, lane), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+          if constexpr (K == 1 || K == 2)
 #pragma unroll
-    for (int ib = 0; ib < IB; ++ib)
-      tile::store_block<S, CHUNKED, RAW, XN>(a, acc[ib], ws + ib * S * 1024, lane,
-                                             ti * C_::BI + (wi * IB + ib) * 32 + (lane & 31),
-                                             tj * C_::BJ + wj * 32 + 4 * (lane >> 5), accx[ib]);
+            for (int c = 0; c < K; ++c)
+              v += __hip_atomic_load(carry_word<int32_t>(carry_base() + c * kSlot, w, lane),
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          return v;
+        };
+        if constexpr (RAW) {
+          tile::store_raw<S>(pr, total, i0 + ib * 16, j0);
+        } else {
+          double val[4];
+          const int wbits = pr->wbits, woff = pr->woff;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            val[r] = 0.0;
+#pragma unroll
+            for (int t = 0; t < S; ++t)
+              val[r] = add_rn(val[r], ldexp(K == 0 ? (double)acc[ib][t][r] : (double)total(t, r),
+                                            woff - wbits * (t + 2)));
+            // one entry's loads at a time (all at once need too many registers)
+            if constexpr (K != 0) __builtin_amdgcn_sched_barrier(0);
+          }
+          tile::store_block(pr, val, i0 + ib * 16, j0);
+        }
+      };
+      if (!CHUNKED || slots == 0)
+        finish(std::integral_constant<int, 0>{});
+      else if (wide)
+        finish(std::integral_constant<int, 3>{});
+      else if (slots == 1)
+        finish(std::integral_constant<int, 1>{});
+      else
+        finish(std::integral_constant<int, 2>{});
+      // one block at a time
+      __builtin_amdgcn_sched_barrier(0);
+    });
   }
 }
 
-template <int S, int WJ, int WI, int IB, int NBUF, bool WITH_RAW, bool EARLY = false>
+template <int S, int WJ, int WI, int IB, int WPS, bool RING, int LA, bool RAW, bool CHUNKED>
 hipError_t launch_cfg(const GemmArgs &a, int num_cu, hipStream_t st) {
-  using C_ = Cfg<S, WJ, WI, IB, NBUF>;
-  const bool grouped = a.probs != nullptr;
-  const int64_t ntiles =
-      grouped ? a.ntiles
-              : ((a.one.nprime + C_::BJ - 1) / C_::BJ) * ((a.one.m + C_::BI - 1) / C_::BI);
-  // persistent grid: 8 waves per CU, i.e. one workgroup of 8 waves or two of 4
-  // (whose barriers are independent, so one's MFMAs fill the other's waits)
-  const int64_t per_cu = C_::NW >= 8 ? 1 : 8 / C_::NW;
-  int64_t grid = std::min<int64_t>(ntiles, per_cu * num_cu);
+  using C_ = Cfg<S, WJ, WI, IB>;
+  const int64_t ntiles = a.probs != nullptr
+                             ? a.ntiles
+                             : ((a.one.nprime + C_::BJ - 1) / C_::BJ) * ((a.one.m + C_::BI - 1) / C_::BI);
+  // persistent grid: WPS waves per SIMD, i.e. one workgroup of 8 waves per CU or
+  // two of 4 (whose barriers are independent, so one's MFMAs fill the other's waits)
+  int64_t grid = std::min<int64_t>(ntiles, (int64_t)(4 * WPS / C_::NW) * num_cu);
   if (a.max_groups > 0) grid = std::min<int64_t>(grid, a.max_groups);
   if (grid <= 0) return hipSuccess;
-  const dim3 g((unsigned)grid), b(C_::NT);
-  if (grouped) {
-    if (a.chunked)
-      hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, false, true, true, EARLY>), g, b, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, false, false, true, EARLY>), g, b, 0, st, a);
-  } else if (a.one.raw != nullptr) {
-    if constexpr (WITH_RAW) {
-      if (a.chunked)
-        hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, true, true, false, EARLY>), g, b, 0, st, a);
-      else
-        hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, true, false, false, EARLY>), g, b, 0, st, a);
-    } else {
-      return hipErrorInvalidValue;
-    }
-  } else {
-    // a contraction each of whose diagonals fits two INT32 sets takes the
-    // split accumulation where its extra sets fit the registers (one A' block
-    // per wave, S <= 7; two blocks' extra sets, or S >= 8, spill)
-    bool split = false;
-    if constexpr (IB == 1 && S >= 2 && S <= 7) {
-      if (a.chunked && a.split) {
-        hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, false, false, false, EARLY, true>), g, b,
-                           0, st, a);
-        split = true;
-      }
-    }
-    if (split)
-      ;
-    else if (a.chunked)
-      hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, false, true, false, EARLY>), g, b, 0, st, a);
-    else
-      hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, NBUF, false, false, false, EARLY>), g, b, 0, st, a);
-  }
+  hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, WPS, RING, LA, RAW, CHUNKED>), dim3((unsigned)grid),
+                     dim3(64 * C_::NW), 0, st, a);
   return hipGetLastError();
 }
 
-// Tile configurations (the autotuner's candidates). All use 32 x 32 x 32 INT8
-// MFMA blocks, one INT32 accumulator set per diagonal and 8 waves (two per
-// SIMD), one 32 x 32 output block per wave:
-//   0: 4 waves along j' x 2 along i (workgroup tile 128 j' x 64 i), LDS ring of
-//      three contraction blocks where it fits in 160 KiB (S <= 8), else two
-//   1: 2 along j' x 4 along i (64 j' x 128 i), same ring
-//   2: as 0 with a ring of two blocks (prefetch distance one)
-//   3: as 2 with every fragment read of a block issued before its MFMAs
-//   4: 4 waves (2 x 2), tile 64 j' x 64 i, ring of two, two workgroups per CU
-//   5: as 4 with the reads of 3 (4 and 5 fall back to 2 for S >= 11)
-//   6: as 2 with two 32-row blocks of A' per wave (tile 128 j' x 128 i): each
-//      B' fragment feeds two MFMAs; S <= 6 only (else configuration 2)
-// A tuning id below 14 is 2 * configuration + tile order (0: consecutive
-// tiles walk down the rows i, 1: along the columns j'); ids 14 .. 20 are
-// configurations 0 .. 6 with the grouped tile order 2, ids 21 .. 27 with the
-// XCD-aware order 3 (see tile_coords and xcd_major).
+// Tile shapes. All use 16 x 16 x 64 INT8 MFMA blocks and one INT32 accumulator
+// set per diagonal; a wave has one 16-row block of B' and IB of A'.
+//   128 x 128 (j' x i): 8 waves of 16 x 128; S <= 6, whose 8 S sets, S B' and 4
+//     A' fragments fit the 256 registers
+//   128 x 64: 8 waves of 16 x 64; S <= 10 (LDS)
+//   64 x 128: 8 waves, 4 x 2, each 16 x 64; S <= 8 (LDS)
+//   64 x 64: 4 waves of 16 x 64, two workgroups per CU, while two fit the LDS (S
+//     <= 6); else 8 waves, 4 x 2, each 16 x 32
+// With 32 x 64 (B' halves in turn, S = 6) or 32 x 32 per wave the LDS reads were
+// fewer, but one needed a few registers too many and the other larger copies:
+// 4096^3 complex S = 6 5264 and 4207 us against 3627, 4096^3 real S = 7 1260
+// against 1230; 128 x 96 tiles 3776 and 1279.
+enum Shape { kBig, kTall, kWide, kSmall };
+
+// Tile configurations 0 .. 6 (the autotuner's candidates): 6 is 128 x 128, 1 is
+// 64 x 128, 4 and 5 are 64 x 64, the others 128 x 64; the shapes a slice count
+// is too large for fall back to the next smaller one. A tuning id below 14 is 2
+// * configuration + tile order (0: consecutive tiles walk down the rows i, 1:
+// along the columns j'); ids 14 .. 20 are configurations 0 .. 6 with the grouped
+// tile order 2, ids 21 .. 27 with the XCD-aware order 3 (see tile_coords and
+// xcd_major).
 constexpr int kNumCfg = 7;
 constexpr int id_cfg(int id) { return id < 2 * kNumCfg ? id >> 1 : (id - 2 * kNumCfg) % kNumCfg; }
 constexpr int id_order(int id) { return id < 2 * kNumCfg ? (id & 1) : 2 + (id - 2 * kNumCfg) / kNumCfg; }
 
-template <int CFG>
-struct Pick;
-template <>
-struct Pick<0> {
-  static constexpr int WJ = 4, WI = 2, IB = 1, RING = 3;
-};
-template <>
-struct Pick<1> {
-  static constexpr int WJ = 2, WI = 4, IB = 1, RING = 3;
-};
-template <>
-struct Pick<2> {
-  static constexpr int WJ = 4, WI = 2, IB = 1, RING = 2;
-};
-template <>
-struct Pick<3> {  // two 32-row blocks of A' per wave (S <= 6: the accumulators fit)
-  static constexpr int WJ = 4, WI = 2, IB = 2, RING = 2;
-};
-
-template <int S, int CFG>
-constexpr int nbuf_for() {
-  using P = Pick<CFG>;
-  return (P::RING == 3 && S * (P::WJ + P::WI * P::IB) * kFragBytes * 3 <= 160 * 1024) ? 3 : 2;
+constexpr Shape shape_of(int S, int cfg) {
+  if (S >= 11 || cfg == 4 || cfg == 5) return kSmall;
+  if (cfg == 6 && S <= 6) return kBig;
+  return cfg == 1 && S <= 8 ? kWide : kTall;
 }
+constexpr int shape_bj(Shape s) { return s == kBig || s == kTall ? 128 : 64; }
+constexpr int shape_bi(Shape s) { return s == kBig || s == kWide ? 128 : 64; }
 
-template <int S, int CFG>
-hipError_t launch_pick(const GemmArgs &a, int num_cu, hipStream_t st) {
-  using P = Pick<CFG>;
-  return launch_cfg<S, P::WJ, P::WI, P::IB, nbuf_for<S, CFG>(), CFG == 0>(a, num_cu, st);
+constexpr bool ring_fits(int bytes, int groups) { return bytes * groups <= 160 * 1024; }
+
+template <int S, bool RAW, bool CHUNKED>
+hipError_t launch_shape(Shape shape, const GemmArgs &a, int num_cu, hipStream_t st) {
+  constexpr int LA = S == 1 ? 1 : 3;
+  constexpr bool all = !RAW;  // raw sums take 128 x 64 or 64 x 64 tiles
+  if (shape == kBig) {
+    if constexpr (S <= 6 && all)
+      return launch_cfg<S, 8, 1, 8, 2, ring_fits(Cfg<S, 8, 1, 8>::RingBytes, 1), LA, RAW, CHUNKED>(a, num_cu, st);
+  } else if (shape == kTall) {
+    if constexpr (S <= 10)
+      return launch_cfg<S, 8, 1, 4, 2, ring_fits(Cfg<S, 8, 1, 4>::RingBytes, 1), LA, RAW, CHUNKED>(a, num_cu, st);
+  } else if (shape == kWide) {
+    if constexpr (S <= 8 && all)
+      return launch_cfg<S, 4, 2, 4, 2, ring_fits(Cfg<S, 4, 2, 4>::RingBytes, 1), LA, RAW, CHUNKED>(a, num_cu, st);
+  } else {
+    if constexpr (S <= 6)
+      return launch_cfg<S, 4, 1, 4, 2, ring_fits(Cfg<S, 4, 1, 4>::RingBytes, 2), LA, RAW, CHUNKED>(a, num_cu, st);
+    else
+      return launch_cfg<S, 4, 2, 2, 2, false, LA, RAW, CHUNKED>(a, num_cu, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int S>
 hipError_t launch_s(int cfg, const GemmArgs &a, int num_cu, hipStream_t st) {
-  switch (cfg) {
-    case 1: return launch_pick<S, 1>(a, num_cu, st);
-    case 2: return launch_pick<S, 2>(a, num_cu, st);
-    case 3: return launch_cfg<S, 4, 2, 1, 2, false, true>(a, num_cu, st);
-    case 4:
-    case 5:
-      // two four-wave workgroups per CU need <= 256 registers per wave, which
-      // the accumulators of S >= 11 exceed: configuration 2 there
-      if constexpr (S <= 10) {
-        if (cfg == 4) return launch_cfg<S, 2, 2, 1, 2, false, false>(a, num_cu, st);
-        return launch_cfg<S, 2, 2, 1, 2, false, true>(a, num_cu, st);
-      } else {
-        return launch_pick<S, 2>(a, num_cu, st);
-      }
-    case 6:
-      if constexpr (S <= 6)
-        return launch_pick<S, 3>(a, num_cu, st);
-      else
-        return launch_pick<S, 2>(a, num_cu, st);
-    default: return launch_pick<S, 0>(a, num_cu, st);
-  }
-}
-
-template <int CFG>
-constexpr int waves_of() {
-  return Pick<CFG>::WJ * Pick<CFG>::WI * Pick<CFG>::IB;
+  const bool raw = a.one.raw != nullptr;
+  const Shape shape = shape_of(S, raw ? 0 : cfg);
+  if (raw)
+    return a.chunked ? launch_shape<S, true, true>(shape, a, num_cu, st)
+                     : launch_shape<S, true, false>(shape, a, num_cu, st);
+  return a.chunked ? launch_shape<S, false, true>(shape, a, num_cu, st)
+                   : launch_shape<S, false, false>(shape, a, num_cu, st);
 }
 
 }  // namespace
 
 int64_t kb_chunk_for(int S, bool b8) { return chunk_blocks(S, b8 ? 128 : 127); }
-int64_t kb_split_for(int S, bool b8) { return chunk_blocks(tile::split_pm(S), b8 ? 128 : 127); }
 
 int gemm_num_configs() { return 4 * kNumCfg; }
 
-size_t gemm_flush_bytes(int S, int cfg, int num_cu) {
-  // the largest per-workgroup carry space over the configurations, so that a
-  // plan is valid whichever configuration runs
-  (void)cfg;
-  const int waves =
-      std::max(std::max(waves_of<0>(), waves_of<1>()), std::max(waves_of<2>(), waves_of<3>()));
-  return (size_t)num_cu * waves * (size_t)S * 1024 * sizeof(int64_t);
+size_t gemm_flush_bytes(int S, int num_cu) {
+  // one int64 per accumulator word of one 128 x 128 tile per CU (the other
+  // shapes need no more, so that a plan is valid whichever configuration runs);
+  // two INT32 sums per word take the same space
+  static_assert(kInt32Chunks - 1 <= 2, "INT32 chunk sums fit the int64 space");
+  return (size_t)num_cu * 128 * 128 * (size_t)S * sizeof(int64_t);
 }
 
-int64_t gemm_tiles(int S, int cfg, int64_t m, int64_t nprime) {
-  int64_t BJ, BI;
-  switch (id_cfg(cfg)) {
-    case 1: BJ = 32 * Pick<1>::WJ; BI = 32 * Pick<1>::WI * Pick<1>::IB; break;
-    case 2: BJ = 32 * Pick<2>::WJ; BI = 32 * Pick<2>::WI * Pick<2>::IB; break;
-    case 3: BJ = 32 * Pick<2>::WJ; BI = 32 * Pick<2>::WI * Pick<2>::IB; break;
-    case 4:
-    case 5:
-      if (S <= 10) {
-        BJ = 64;
-        BI = 64;
-      } else {  // launched as configuration 2
-        BJ = 32 * Pick<2>::WJ;
-        BI = 32 * Pick<2>::WI * Pick<2>::IB;
-      }
-      break;
-    case 6:
-      if (S <= 6) {
-        BJ = 32 * Pick<3>::WJ;
-        BI = 32 * Pick<3>::WI * Pick<3>::IB;
-      } else {  // launched as configuration 2
-        BJ = 32 * Pick<2>::WJ;
-        BI = 32 * Pick<2>::WI * Pick<2>::IB;
-      }
-      break;
-    default: BJ = 32 * Pick<0>::WJ; BI = 32 * Pick<0>::WI * Pick<0>::IB; break;
-  }
+int64_t gemm_tiles(int S, int id, int64_t m, int64_t nprime) {
+  const Shape s = shape_of(S, id_cfg(id));
+  const int64_t BJ = shape_bj(s), BI = shape_bi(s);
   return ((nprime + BJ - 1) / BJ) * ((m + BI - 1) / BI);
 }
 

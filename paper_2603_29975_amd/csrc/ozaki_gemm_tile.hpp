@@ -1,11 +1,10 @@
-// Pieces shared by the fused slice GEMM kernels of libozaki (gfx950): explicit
-// wait/barrier primitives, the INT32 chunk bound, the int64 carry of a 32 x 32
-// accumulator block and the FP64 recombination epilogue of one block.
+// Pieces shared by the INT8 GEMM kernels of libozaki (gfx950): explicit
+// wait/barrier primitives, direct-to-LDS copies, the INT32 chunk bound, the
+// FP64 epilogue of one block and the tile orders.
 //
-// Accumulator layout of v_mfma_i32_32x32x32_i8 as used here: the MFMA row
-// index is the output column side j', the MFMA column index (lane % 32) is the
-// output row i. Register r of a lane holds j' = jbase + 8 (r / 4) + r % 4 with
-// jbase = 32 * block + 4 * (lane / 32).
+// Accumulator layout of v_mfma_i32_16x16x64_i8 as used here: the MFMA row index
+// is the output column side j', the MFMA column index (lane % 16) is the output
+// row i. Register r of a lane holds j' = 16 * block + 4 * (lane / 16) + r.
 #pragma once
 
 #include "ozaki_internal.hpp"
@@ -24,20 +23,32 @@ __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" ::: "memory"); }
 
-// One 1 KiB slice fragment from global memory straight into LDS: lane l
-// copies the 16 bytes at src_lane (its own part of the fragment) to LDS
-// address lds_wave + 16 l. Inline assembly rather than the compiler's builtin
-// for the same instruction: with the builtin in a loop the compiler waits for
-// every outstanding LDS read (lgkmcnt(0)) before each fragment's first use,
-// which serialises the fragment reads with the MFMAs; with the copy hidden
-// from it, it waits for exactly the reads each MFMA needs. The copy counts in
-// vmcnt, which the kernels wait on explicitly (wait_vmcnt); the LDS base goes
-// through M0, set in the same statement.
+// One 1 KiB fragment from global memory straight into LDS: lane l copies 16
+// bytes to LDS address lds_wave + 16 l, from its own address (copy_frag) or from
+// base + off_lane (copy_frag_s: the wave-uniform base stays in scalar
+// registers). Inline assembly rather than the compiler's builtin for the same
+// instruction: with the builtin in a loop the compiler waits for every
+// outstanding LDS read (lgkmcnt(0)) before each fragment's first use, which
+// serialises the fragment reads with the MFMAs; with the copy hidden from it, it
+// waits for exactly the reads each MFMA needs. The copy counts in vmcnt, which
+// the kernels wait on explicitly (wait_vmcnt); the LDS base goes through M0, set
+// in the same statement.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ uint32_t lds_addr(const int8_t *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) int8_t *)p;
+}
+__device__ __forceinline__ v4i lds_read(uint32_t addr) {
+  return *(const __attribute__((address_space(3))) v4i *)(uintptr_t)addr;
+}
 __device__ __forceinline__ void copy_frag(const int8_t *src_lane, const int8_t *lds_wave) {
-  const uint32_t la = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) int8_t *)lds_wave;
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(la)
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane),
+               "s"(lds_addr(lds_wave))
+               : "memory", "m0");
+}
+__device__ __forceinline__ void copy_frag_s(const int8_t *base, uint32_t off_lane, const int8_t *lds_wave) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off_lane), "s"(base),
+               "s"(lds_addr(lds_wave))
                : "memory", "m0");
 }
 #pragma clang diagnostic pop
@@ -48,168 +59,93 @@ __host__ __device__ constexpr int64_t chunk_blocks(int S, int dmax = 127) {
   return (int64_t)(2147483647ll / ((int64_t)S * 32 * dmax * dmax));
 }
 
-// Exact int64 carry of one block's S INT32 accumulator sets into its carry
-// space `ws` (S * 16 * 64 int64, lane-interleaved); the accumulators restart
-// at zero. Device-scope atomics keep the traffic in L2, away from stale lines
-// of the non-coherent vector L1.
-// The lane's base address goes through an empty asm statement: the S x 16
-// addresses are then formed here, one at a time, instead of being hoisted out
-// of the contraction loop, where keeping them live costs 2 S x 16 registers
-// and the compiler spills.
-template <int S>
-__device__ __forceinline__ void carry_block(v16i (&acc)[S], int64_t *ws, int lane, bool first) {
-  int64_t *q = ws + lane;
-  asm volatile("" : "+v"(q));
+// Stores of one 16 x 16 block: lane register r is column side j' = j0 + r of row
+// i. a: the problem (any address space).
+
+// The exact diagonals, total(t, r) being diagonal t + 2 of register r.
+template <int S, typename Problem, typename Total>
+__device__ __forceinline__ void store_raw(Problem a, Total total, int64_t i, int64_t j0) {
+  if (i >= a->m) return;
 #pragma unroll
-  for (int t = 0; t < S; ++t) {
+  for (int r = 0; r < 4; ++r) {
+    const int64_t jp = j0 + r;
+    if (jp >= a->nprime) continue;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      int64_t *p = q + (t * 16 + r) * 64;
-      if (first)
-        __hip_atomic_store(p, (int64_t)acc[t][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else
-        __hip_atomic_fetch_add(p, (int64_t)acc[t][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int t = 0; t < S; ++t) {
+      const int64_t v = total(t, r);
+      if (a->cplx) {
+        const int64_t n = a->nprime >> 1;
+        a->raw[(((int64_t)t * n + (jp >> 1)) * a->m + i) * 2 + (jp & 1)] = v;
+      } else {
+        a->raw[((int64_t)t * a->nprime + jp) * a->m + i] = v;
+      }
     }
-    acc[t] = v16i{0};
   }
 }
 
-// Split accumulation: diagonal t (t + 1 slice pairs) keeps the pairs with
-// p < split_pm(S) in one INT32 set and the others (at most as many) in a
-// second, so a contraction of up to chunk_blocks(split_pm(S)) blocks needs no
-// int64 carry; the two sets add exactly in int64 in the epilogue.
-__host__ __device__ constexpr int split_pm(int S) { return (S + 1) / 2; }
-__host__ __device__ constexpr int split_extra(int S) { return S - split_pm(S); }
-
-// Recombination and store of one 32 x 32 block: row i of the output, lane
-// register r at column side j' = jbase + 8 (r / 4) + r % 4. Diagonal t + 2 of
-// the block is acc[t] (plus accx[t - split_pm(S)] for t >= split_pm(S) when XN
-// > 0; or, for a chunked contraction, the int64 total in the carry space
-// `ws`). acc = RN(acc + S_t 2^(woff - wbits t)) for t = 2..S+1 (2^-7t for
-// trunc-7 slices, 2^(4-8t) for 8-bit balanced ones), then ldexp(acc, e_i +
-// f_j) and alpha/beta without fused multiply-adds; rows or columns flagged
-// non-finite give NaN. RAW writes the exact diagonals instead.
-template <int S, bool CHUNKED, bool RAW, int XN = 0>
-__device__ __forceinline__ void store_block(const GemmProblem &a, const v16i (&acc)[S],
-                                            const int64_t *ws, int lane, int64_t i,
-                                            int64_t jbase, const v16i *accx = nullptr) {
-  const bool row_ok = i < a.m;
-  const int codeA = row_ok ? a.codeA[i] : 0;
-
-  const int64_t *q = ws + lane;
-  if constexpr (CHUNKED) asm volatile("" : "+v"(q));  // as in carry_block
-  auto total = [&](int t, int r) -> int64_t {
-    if constexpr (CHUNKED)
-      return __hip_atomic_load(q + (t * 16 + r) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if constexpr (XN > 0) {
-      if (t >= S - XN) return (int64_t)acc[t][r] + (int64_t)accx[t - (S - XN)][r];
-    }
-    return (int64_t)acc[t][r];
-  };
-
-  if constexpr (RAW) {
-    if (row_ok) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t jp = jbase + 8 * (r >> 2) + (r & 3);
-        if (jp >= a.nprime) continue;
-#pragma unroll
-        for (int t = 0; t < S; ++t) {
-          const int64_t v = total(t, r);
-          if (a.cplx) {
-            const int64_t n = a.nprime >> 1;
-            a.raw[(((int64_t)t * n + (jp >> 1)) * a.m + i) * 2 + (jp & 1)] = v;
-          } else {
-            a.raw[((int64_t)t * a.nprime + jp) * a.m + i] = v;
-          }
-        }
-      }
-    }
-    return;
-  }
-
-  double val[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    double acc64 = 0.0;
-#pragma unroll
-    for (int t = 0; t < S; ++t)
-      acc64 = add_rn(acc64, ldexp((double)total(t, r), a.woff - a.wbits * (t + 2)));
-    val[r] = acc64;
-    // chunked: the S int64 totals of one entry at a time (issuing all 16 S
-    // loads at once needs 32 S registers)
-    if constexpr (CHUNKED) __builtin_amdgcn_sched_barrier(0);
-  }
-  if (!row_ok) return;
+// The recombined sums val[r] times 2^(e_i + f_j) and alpha/beta without fused
+// multiply-adds; rows or columns flagged non-finite give NaN.
+template <typename Problem>
+__device__ __forceinline__ void store_block(Problem a, const double (&val)[4], int64_t i, int64_t j0) {
+  if (i >= a->m) return;
+  const int codeA = a->codeA[i];
   const int ea = code_exp(codeA);
   const bool bad_i = code_bad(codeA);
-
-  if (a.unscaled) {
-    // the recombined sums as they are (NaN for non-finite rows/columns): a
-    // later diagonal adds to them exactly as the loop above would have
-    if (a.cplx) {
-      double2 *C = reinterpret_cast<double2 *>(a.C);
-      const int64_t n = a.nprime >> 1;
+  const int *codeB = a->codeB;
+  const int64_t ldc = a->ldc;
+  const double ar = a->ar, ai = a->ai, br = a->br, bi = a->bi;
+  const int beta_zero = a->beta_zero;
+  // the recombined sums as they are (NaN for non-finite rows/columns): a later
+  // diagonal adds to them exactly as the recombination would have
+  const int unscaled = a->unscaled;
+  if (a->cplx) {
+    double2 *C = reinterpret_cast<double2 *>(a->C);
+    const int64_t n = a->nprime >> 1;
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const int64_t j = (jbase + 8 * (r >> 2) + (r & 3)) >> 1;
-        if (j >= n) continue;
-        const bool bad = bad_i || code_bad(a.codeB[j]);
-        C[i + j * a.ldc] = bad ? make_double2(qnan(), qnan()) : make_double2(val[r], val[r + 1]);
-      }
-    } else {
-      double *C = reinterpret_cast<double *>(a.C);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t j = jbase + 8 * (r >> 2) + (r & 3);
-        if (j >= a.nprime) continue;
-        C[i + j * a.ldc] = (bad_i || code_bad(a.codeB[j])) ? qnan() : val[r];
-      }
-    }
-    return;
-  }
-
-  if (a.cplx) {
-    double2 *C = reinterpret_cast<double2 *>(a.C);
-    const int64_t n = a.nprime >> 1;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int64_t jp = jbase + 8 * (r >> 2) + (r & 3);
-      const int64_t j = jp >> 1;
+    for (int r = 0; r < 4; r += 2) {
+      const int64_t j = (j0 + r) >> 1;
       if (j >= n) continue;
-      const int cb = a.codeB[j];
-      double2 *cp = C + i + j * a.ldc;
+      const int cb = codeB[j];
+      double2 *cp = C + i + j * ldc;
       if (bad_i || code_bad(cb)) {
         *cp = make_double2(qnan(), qnan());
+        continue;
+      }
+      if (unscaled) {
+        *cp = make_double2(val[r], val[r + 1]);
         continue;
       }
       const int sc = ea + code_exp(cb);
       const double pr = ldexp(val[r], sc);
       const double pi = ldexp(val[r + 1], sc);
-      double re = sub_rn(mul_rn(a.ar, pr), mul_rn(a.ai, pi));
-      double im = add_rn(mul_rn(a.ar, pi), mul_rn(a.ai, pr));
-      if (!a.beta_zero) {
+      double re = sub_rn(mul_rn(ar, pr), mul_rn(ai, pi));
+      double im = add_rn(mul_rn(ar, pi), mul_rn(ai, pr));
+      if (!beta_zero) {
         const double2 z = *cp;
-        re = add_rn(re, sub_rn(mul_rn(a.br, z.x), mul_rn(a.bi, z.y)));
-        im = add_rn(im, add_rn(mul_rn(a.br, z.y), mul_rn(a.bi, z.x)));
+        re = add_rn(re, sub_rn(mul_rn(br, z.x), mul_rn(bi, z.y)));
+        im = add_rn(im, add_rn(mul_rn(br, z.y), mul_rn(bi, z.x)));
       }
       *cp = make_double2(re, im);
     }
   } else {
-    double *C = reinterpret_cast<double *>(a.C);
+    double *C = reinterpret_cast<double *>(a->C);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t j = jbase + 8 * (r >> 2) + (r & 3);
-      if (j >= a.nprime) continue;
-      const int cb = a.codeB[j];
-      double *cp = C + i + j * a.ldc;
+    for (int r = 0; r < 4; ++r) {
+      const int64_t j = j0 + r;
+      if (j >= a->nprime) continue;
+      const int cb = codeB[j];
+      double *cp = C + i + j * ldc;
       if (bad_i || code_bad(cb)) {
         *cp = qnan();
         continue;
       }
+      if (unscaled) {
+        *cp = val[r];
+        continue;
+      }
       const double p = ldexp(val[r], ea + code_exp(cb));
-      double out = mul_rn(a.ar, p);
-      if (!a.beta_zero) out = add_rn(out, mul_rn(a.br, *cp));
+      double out = mul_rn(ar, p);
+      if (!beta_zero) out = add_rn(out, mul_rn(br, *cp));
       *cp = out;
     }
   }

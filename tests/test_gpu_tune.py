@@ -71,6 +71,30 @@ def test_every_tuning_id_chunked_contraction(kind, s, k):
         assert bits_equal(got, ref), f"id {tid}\n" + mismatch_report(got, ref)
 
 
+# Every slice count of both kinds in each tile shape (ids 0: 128 x 64, 2: 64 x
+# 128, 8: 64 x 64, 12: 128 x 128), at the edges of tiles and of 64-entry
+# contraction blocks: one entry, one tile, one row, column or block past it.
+@pytest.mark.parametrize("split", ["t7", "b8"])
+@pytest.mark.parametrize("kind,m,n,k", [("d", 1, 1, 1), ("d", 64, 128, 64), ("d", 65, 129, 65),
+                                        ("d", 129, 257, 193), ("z", 128, 64, 32), ("z", 127, 65, 97)])
+def test_every_slice_count_at_tile_edges(split, kind, m, n, k):
+    from oracle import ozaki_b8
+    model = ozaki_b8.ozaki_gemm_b8 if split == "b8" else ozaki.ozaki_gemm
+    A, B = uniform_binade(m, n, k, seed=710 + m, complex_=kind == "z")
+    assert oz.ozaki_set_split(split) == 0
+    try:
+        for s in range(1, (8 if split == "b8" else 12) + 1):
+            ref = model("N", "N", A, B, s)
+            for tid in (0, 2, 8, 12):
+                assert oz.ozaki_tune_set(kind, m, n, k, s, tid) == 0
+                _say("tile edges", split, kind, (m, n, k), s, "tuning id", tid)
+                got = _gemm(kind, A, B, s)
+                assert bits_equal(got, ref), f"s={s} id {tid}\n" + mismatch_report(got, ref)
+    finally:
+        torch.cuda.synchronize()
+        oz.ozaki_set_split("t7")
+
+
 def test_every_tuning_id_alpha_beta():
     m, n, k, s = 97, 130, 65, 6
     A, B = uniform_binade(m, n, k, seed=780, complex_=True)
