@@ -337,18 +337,24 @@ int prepare(const Plan &p, char *ws, const View &va, const View &vb, hipStream_t
   int8_t *SA = reinterpret_cast<int8_t *>(ws + p.off_SA);
   int8_t *SB = reinterpret_cast<int8_t *>(ws + p.off_SB);
   int rc;
+  const PrepTask ta{va, codeA, SA, p.nrbQ, p.nkb, p.S, p.cplx ? 1 : 0, 0};
+  const PrepTask tb{vb, codeB, SB, p.nrbP, p.nkb, p.S, p.cplx ? 1 : 0, 1};
+  if (prep_fits(ta, tb)) {
+    const int mk = timed ? phase_begin(OZAKI_PHASE_SPLIT, st) : -1;  // scan included
+    rc = hip_rc(launch_prep(ta, tb, st, p.b8));
+    phase_end(mk, st);
+    return rc;
+  }
   int mk = timed ? phase_begin(OZAKI_PHASE_SCAN, st) : -1;
   // codeA and codeB lie back to back (codeB at off_codeB): one fill zeroes both
   if ((rc = hip_rc(launch_fill_i32(codeA, (int64_t)((p.off_codeB - p.off_codeA) / sizeof(int)) + p.n,
                                    0, st))))
     return rc;
-  if ((rc = hip_rc(launch_scan(va, p.cplx, codeA, st)))) return rc;
-  if ((rc = hip_rc(launch_scan(vb, p.cplx, codeB, st)))) return rc;
+  if ((rc = hip_rc(launch_scan(va, codeA, vb, codeB, p.cplx, st)))) return rc;
   phase_end(mk, st);
   mk = timed ? phase_begin(OZAKI_PHASE_SPLIT, st) : -1;
-  if ((rc = hip_rc(launch_split(va, p.cplx, false, codeA, p.S, SA, p.nrbQ, p.nkb, st, p.b8))))
-    return rc;
-  if ((rc = hip_rc(launch_split(vb, p.cplx, true, codeB, p.S, SB, p.nrbP, p.nkb, st, p.b8))))
+  if ((rc = hip_rc(launch_split(va, codeA, SA, p.nrbQ, vb, codeB, SB, p.nrbP, p.nkb, p.cplx, p.S, st,
+                                p.b8))))
     return rc;
   phase_end(mk, st);
   return OZAKI_OK;
@@ -581,8 +587,7 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   if ((rc = hip_rc(launch_fill_i32(codeA, (int64_t)((p.off_codeB - p.off_codeA) / sizeof(int)) + n,
                                    0, st))))
     return rc;
-  if ((rc = hip_rc(launch_scan(va, cplx, codeA, st)))) return rc;
-  if ((rc = hip_rc(launch_scan(vb, cplx, codeB, st)))) return rc;
+  if ((rc = hip_rc(launch_scan(va, codeA, vb, codeB, cplx, st)))) return rc;
   phase_end(mk, st);
 
   mk = phase_begin(OZAKI_PHASE_SPLIT, st);
@@ -2048,8 +2053,7 @@ int ozaki_features(char kind, char transa, char transb, int64_t m, int64_t n, in
   if ((rc = hip_rc(launch_fill_i32(codeA, m, 0, st)))) return rc;
   if ((rc = hip_rc(launch_fill_i32(codeB, n, 0, st)))) return rc;
   if ((rc = hip_rc(launch_fill_i32(hist, 64, 0, st)))) return rc;
-  if ((rc = hip_rc(launch_scan(va, cplx, codeA, st)))) return rc;
-  if ((rc = hip_rc(launch_scan(vb, cplx, codeB, st)))) return rc;
+  if ((rc = hip_rc(launch_scan(va, codeA, vb, codeB, cplx, st)))) return rc;
   if ((rc = hip_rc(launch_feat_hist(reinterpret_cast<const FeatTask *>(ws + ot),
                                     reinterpret_cast<const int64_t *>(ws + os), 2, start[2], st))))
     return rc;
@@ -2238,7 +2242,7 @@ int ozaki_debug_exponents(char kind, char side, char trans, int64_t rows, int64_
   if ((rc = get_workspace(align256(sizeof(int) * rows), &wsv))) return rc;
   int *code = static_cast<int *>(wsv);
   if ((rc = hip_rc(launch_fill_i32(code, rows, 0, g.stream)))) return rc;
-  if ((rc = hip_rc(launch_scan(v, cplx, code, g.stream)))) return rc;
+  if ((rc = hip_rc(launch_scan(v, code, View{}, nullptr, cplx, g.stream)))) return rc;
   return hip_rc(launch_codes_to_exps(code, rows, exps, flags, g.stream));
 }
 
@@ -2263,7 +2267,7 @@ int ozaki_debug_split(char kind, char side, char trans, int64_t rows, int64_t L,
   int *code = static_cast<int *>(wsv);
   int8_t *packed = static_cast<int8_t *>(wsv) + code_bytes;
   if ((rc = hip_rc(launch_fill_i32(code, rows, 0, g.stream)))) return rc;
-  if ((rc = hip_rc(launch_scan(v, cplx, code, g.stream)))) return rc;
+  if ((rc = hip_rc(launch_scan(v, code, View{}, nullptr, cplx, g.stream)))) return rc;
   if ((rc = hip_rc(launch_split(v, cplx, side_b, code, slices, packed, nrb, kpad / 32, g.stream,
                                 b8))))
     return rc;

@@ -11,7 +11,8 @@ namespace oz {
 hipError_t launch_fill_i32(int *p, int64_t n, int value, hipStream_t st);
 // Pseudo-random digits in [-127, 127] (timing data of the autotuner).
 hipError_t launch_fill_digits(int8_t *p, int64_t n, uint64_t seed, hipStream_t st);
-hipError_t launch_scan(const View &v, bool cplx, int *code, hipStream_t st);
+// Both operands in one launch (a view without rows takes no part).
+hipError_t launch_scan(const View &va, int *ca, const View &vb, int *cb, bool cplx, hipStream_t st);
 
 // Slicing step: writes all nrb*32 x nkb*32 packed rows/entries of S slices.
 // side_b selects the B-operand construction for complex data (rows 2j and
@@ -20,6 +21,11 @@ hipError_t launch_scan(const View &v, bool cplx, int *code, hipStream_t st);
 constexpr int kS8Max = 8;
 hipError_t launch_split(const View &v, bool cplx, bool side_b, const int *code, int S,
                         int8_t *out, int64_t nrb, int64_t nkb, hipStream_t st, bool b8 = false);
+
+// Both operands of a product in one launch (the same S, nkb and slice kind).
+hipError_t launch_split(const View &va, const int *ca, int8_t *oa, int64_t nrba, const View &vb,
+                        const int *cb, int8_t *ob, int64_t nrbb, int64_t nkb, bool cplx, int S,
+                        hipStream_t st, bool b8);
 
 // Batched scan and split: task tables in device memory. A scan task covers
 // all rows of one operand view over its whole contraction (codes are stored,
@@ -46,6 +52,26 @@ hipError_t launch_scan_batched(const ScanTask *tasks, const int64_t *start, int 
                                int64_t nblocks, hipStream_t st);
 hipError_t launch_split_batched(const SplitTask *tasks, const int64_t *start, int ntasks,
                                 int64_t nblocks, hipStream_t st);
+
+// Scan and split of both operands of a product in one kernel, 16 rows per block
+// (codes stored, no zero fill needed), for short contractions.
+struct PrepTask {
+  View v;
+  int *code;
+  int8_t *out;
+  int64_t nrb, nkb;
+  int S;
+  int cplx;
+  int side_b;
+};
+// A short contraction is scanned and split in one kernel, 16 rows per block: one
+// launch instead of three. A block takes 256 packed entries per pass, so a longer
+// contraction would run its passes one after the other on too few blocks.
+// Measured, whole call: z 32^3 17.6 us (23.4 with three launches), d 256^3 (K' =
+// 256) 20.8 (25.3); beyond it z 256^3 (K' = 512) 30.8 (22.0).
+constexpr int64_t kPrepK = 256;  // packed contraction up to which that holds
+bool prep_fits(const PrepTask &a, const PrepTask &b);
+hipError_t launch_prep(const PrepTask &a, const PrepTask &b, hipStream_t st, bool b8);
 
 // Debug helpers.
 hipError_t launch_unpack(const int8_t *packed, bool cplx, bool side_b, int64_t R, int64_t L,

@@ -82,12 +82,6 @@ __device__ __forceinline__ void scan_rowsfast_block(const View &v, int64_t rb, i
   }
 }
 
-template <bool CPLX>
-__global__ void __launch_bounds__(256) k_scan_rowsfast(View v, int64_t lchunk, int *code) {
-  const int64_t l0 = (int64_t)blockIdx.y * lchunk;
-  scan_rowsfast_block<CPLX>(v, blockIdx.x, l0, min(v.L, l0 + lchunk), code, false);
-}
-
 // Each row is unit-stride (sl == 1): one wave per row and contraction chunk,
 // lanes read consecutive elements, a wave max-reduction gives the row code.
 template <bool CPLX>
@@ -114,12 +108,6 @@ __device__ __forceinline__ void scan_rowcontig_block(const View &v, int64_t rb, 
     else if (c > 0)
       atomicMax(code + r, c);
   }
-}
-
-template <bool CPLX>
-__global__ void __launch_bounds__(256) k_scan_rowcontig(View v, int64_t lchunk, int *code) {
-  const int64_t l0 = (int64_t)blockIdx.y * lchunk;
-  scan_rowcontig_block<CPLX>(v, blockIdx.x, l0, min(v.L, l0 + lchunk), code, false);
 }
 
 // One thread per (packed row, 16 consecutive packed contraction entries):
@@ -349,6 +337,45 @@ __global__ void __launch_bounds__(256) k_split(View v, const int *code, int S, i
   }
 }
 
+// Both operands of a product in one launch: blocks [0, na) take the first view.
+// Each block is one of nr row groups times a contraction chunk.
+struct ScanSide {
+  View v;
+  int *code;
+  int64_t nr, lchunk;
+  int rows_fast;
+};
+template <bool CPLX>
+__global__ void __launch_bounds__(256) k_scan(ScanSide a, ScanSide b, int64_t na) {
+  const bool first = blockIdx.x < na;
+  const ScanSide &s = first ? a : b;
+  const int64_t blk = first ? blockIdx.x : blockIdx.x - na;
+  const int64_t l0 = (blk / s.nr) * s.lchunk, l1 = min(s.v.L, l0 + s.lchunk);
+  if (s.rows_fast)
+    scan_rowsfast_block<CPLX>(s.v, blk % s.nr, l0, l1, s.code, false);
+  else
+    scan_rowcontig_block<CPLX>(s.v, blk % s.nr, l0, l1, s.code, false);
+}
+
+// Both operands in one launch: blocks [0, na) take the first.
+struct SplitSide {
+  View v;
+  const int *code;
+  int8_t *out;
+  int64_t nrb, nkb;
+};
+template <bool CPLX, bool B8>
+__global__ void __launch_bounds__(256) k_split_pair(SplitSide a, SplitSide b, int64_t na, int S) {
+  __shared__ __attribute__((aligned(16))) double tile[kSplitTileDoubles];
+  if (blockIdx.x < na) {
+    const int64_t nbx = a.nrb / 2, blk = blockIdx.x;
+    split_dispatch<CPLX, false, B8>(a.v, a.code, S, a.out, a.nrb, a.nkb, blk % nbx, blk / nbx, tile);
+  } else {
+    const int64_t nbx = b.nrb / 2, blk = blockIdx.x - na;
+    split_dispatch<CPLX, true, B8>(b.v, b.code, S, b.out, b.nrb, b.nkb, blk % nbx, blk / nbx, tile);
+  }
+}
+
 // ---------------------------------------------------------------- batched
 // Block b of a batched launch belongs to the task t with
 // start[t] <= b < start[t + 1] (binary search, uniform per block).
@@ -403,6 +430,135 @@ __global__ void __launch_bounds__(256) k_split_batched(const SplitTask *tasks, c
   } else {
     split_dispatch<false, false>(tk.v, tk.code, tk.S, tk.out, tk.nrb, tk.nkb, bx, by, tile);
   }
+}
+
+// ---------------------------------------------------------------- scan + split
+// Bound by the launches it replaces and by its one chain of loads (scan, then the
+// packed entries out of the caches). Whole call with this kernel and the GEMM / with
+// a fill, two scans and two splits before it: z 32^3 S = 7 16 / 27 us, d 256^3
+// 19 / 25 us.
+// The slices of 16 packed entries of view row vr (see pack_rows): one 16-byte
+// run per slice, or for complex B two, X' rows 2 vr = (Re, -Im) and 2 vr + 1 =
+// (Im, Re), from the same digits: with trunc-7 slices those of -Im are the
+// negated ones of Im, with 8-bit slices -Im is split as it stands.
+__device__ __forceinline__ uint32_t swap_pairs(uint32_t w) {
+  return __builtin_amdgcn_perm(0u, w, 0x02030001u);  // bytes 1, 0, 3, 2
+}
+
+template <bool CPLX, bool SIDEB, bool B8, int SC>
+__device__ __forceinline__ void emit_slices(const double (&x)[16], int e, int S, int8_t *dst, int64_t plane) {
+  constexpr bool PAIR = CPLX && SIDEB;
+  Sig sg[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) sg[q] = decompose(x[q], e);
+  auto put = [&](int p, const uint32_t (&a)[4], const uint32_t (&b)[4]) {
+    int8_t *d = dst + (int64_t)(p - 1) * plane;
+    *reinterpret_cast<uint4 *>(d) = make_uint4(a[0], a[1], a[2], a[3]);
+    if constexpr (PAIR) *reinterpret_cast<uint4 *>(d + 16) = make_uint4(b[0], b[1], b[2], b[3]);
+  };
+  if constexpr (B8) {
+    // the bytes of X + 0x80...80, as in split_block
+    constexpr uint64_t kBias = 0x8080808080808080ull >> (8 * (8 - SC));
+    uint64_t Y[16], M[8];  // M: -Im
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const uint64_t u = top_nbits<8 * SC - 2>(sg[q]);
+      Y[q] = (sg[q].neg ? 0ull - u : u) + kBias;
+      if (PAIR && (q & 1)) M[q >> 1] = (sg[q].neg ? u : 0ull - u) + kBias;
+    }
+#pragma unroll
+    for (int p = SC; p >= 1; --p) {
+      const int sh = 8 * (SC - p);
+      uint32_t a[4], b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w |= ((uint32_t)(Y[4 * q + k] >> sh) & 0xffu) << (8 * k);
+        w ^= 0x80808080u;
+        a[q] = w;
+        if constexpr (PAIR) {
+          uint32_t m = (((uint32_t)(M[2 * q] >> sh) & 0xffu) << 8) | (((uint32_t)(M[2 * q + 1] >> sh) & 0xffu) << 24);
+          b[q] = swap_pairs(w);
+          a[q] = (w & 0x00ff00ffu) | (m ^ 0x80008000u);
+        }
+      }
+      put(p, a, b);
+    }
+  } else {
+    uint64_t T[16];
+    uint32_t neg[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t mk = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (SC > 0) T[4 * q + k] = top_bits<SC>(sg[4 * q + k]);
+        mk |= (sg[4 * q + k].neg ? 0xffu : 0u) << (8 * k);
+      }
+      neg[q] = mk;
+    }
+    auto slice = [&](int p) {
+      uint32_t a[4], b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          uint32_t d;
+          if constexpr (SC > 0)
+            d = (uint32_t)(T[4 * q + k] >> (kDigitBits * (SC - p))) & 127u;
+          else
+            d = (uint32_t)digit(Sig{sg[4 * q + k].m, sg[4 * q + k].sh0, false}, p);
+          w |= d << (8 * k);
+        }
+        a[q] = neg_bytes(w, neg[q]);
+        if constexpr (PAIR) {
+          b[q] = swap_pairs(a[q]);
+          a[q] = neg_bytes(w, neg[q] ^ 0xff00ff00u);
+        }
+      }
+      put(p, a, b);
+    };
+    if constexpr (SC > 0) {
+#pragma unroll
+      for (int p = 1; p <= SC; ++p) slice(p);
+    } else {
+      for (int p = 1; p <= S; ++p) slice(p);
+    }
+  }
+}
+
+template <bool CPLX, bool SIDEB, bool B8>
+__device__ __forceinline__ void prep_task(const PrepTask &tk, int64_t block, RowsLds &lds) {
+  const int64_t plane = tk.nrb * tk.nkb * kFragBytes;
+  pack_rows<CPLX>(tk.v, block, tk.nkb * 2, tk.code, lds, [&](const double(&x)[16], int e, int64_t vr, int64_t ch) {
+    int8_t *dst = tk.out + frag_offset(0, (CPLX && SIDEB) ? 2 * vr : vr, ch * 16, tk.nrb, tk.nkb);
+    switch (tk.S) {
+#define OZ_EMIT(N) \
+  case N: emit_slices<CPLX, SIDEB, B8, N>(x, e, N, dst, plane); break;
+      OZ_EMIT(1) OZ_EMIT(2) OZ_EMIT(3) OZ_EMIT(4) OZ_EMIT(5) OZ_EMIT(6) OZ_EMIT(7) OZ_EMIT(8)
+      default:
+        if constexpr (!B8) {
+          if (tk.S == 9)
+            emit_slices<CPLX, SIDEB, B8, 9>(x, e, 9, dst, plane);
+          else
+            emit_slices<CPLX, SIDEB, B8, 0>(x, e, tk.S, dst, plane);
+        }
+        break;
+#undef OZ_EMIT
+    }
+  });
+}
+
+template <bool CPLX, bool B8>
+__global__ void __launch_bounds__(256) k_prep(PrepTask a, PrepTask b, int64_t blocks_a) {
+  __shared__ RowsLds lds;
+  const int64_t blk = blockIdx.x;
+  if (blk < blocks_a)
+    prep_task<CPLX, false, B8>(a, blk, lds);
+  else
+    prep_task<CPLX, true, B8>(b, blk - blocks_a, lds);
 }
 
 template <bool CPLX, bool SIDEB>
@@ -460,6 +616,9 @@ __global__ void __launch_bounds__(256) k_scale(int64_t m, int64_t n, double br, 
   }
 }
 
+// Blocks of 256 threads in one launch (fewer than 2^32 threads along x).
+constexpr int64_t kMaxBlocks = (1 << 24) - 1;
+
 inline unsigned grid1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
@@ -477,31 +636,42 @@ hipError_t launch_fill_digits(int8_t *p, int64_t n, uint64_t seed, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const View &v, bool cplx, int *code, hipStream_t st) {
-  if (v.R <= 0 || v.L <= 0) return hipSuccess;
+namespace {
+// Row groups and contraction chunks of one operand: about 2048 blocks.
+ScanSide scan_side(const View &v, int *code, int64_t *blocks) {
+  ScanSide s{v, code, 1, v.L, 0};
+  *blocks = 0;
+  if (v.R <= 0 || v.L <= 0) return s;
   const int64_t target = 2048;
-  if (v.sr == 1 && !(v.sl == 1 && v.R < 64)) {
-    const int64_t rb = (v.R + 63) / 64;
-    int64_t ncol = std::max<int64_t>(1, std::min<int64_t>((v.L + 15) / 16, target / rb));
-    const int64_t lchunk = (v.L + ncol - 1) / ncol;
-    ncol = (v.L + lchunk - 1) / lchunk;
-    dim3 g((unsigned)rb, (unsigned)ncol);
+  s.rows_fast = v.sr == 1 && !(v.sl == 1 && v.R < 64);
+  // otherwise sl == 1 (each row contiguous): one of the two strides of a BLAS
+  // operand is always 1
+  const int64_t rows = s.rows_fast ? 64 : 4, depth = s.rows_fast ? 16 : 256;
+  s.nr = (v.R + rows - 1) / rows;
+  const int64_t ncol = std::max<int64_t>(
+      1, std::min<int64_t>((v.L + depth - 1) / depth, std::max<int64_t>(1, target / s.nr)));
+  s.lchunk = (v.L + ncol - 1) / ncol;
+  *blocks = s.nr * ((v.L + s.lchunk - 1) / s.lchunk);
+  return s;
+}
+}  // namespace
+
+hipError_t launch_scan(const View &va, int *ca, const View &vb, int *cb, bool cplx, hipStream_t st) {
+  int64_t na = 0, nb = 0;
+  const ScanSide a = scan_side(va, ca, &na), b = scan_side(vb, cb, &nb);
+  auto go = [&](const ScanSide &x, const ScanSide &y, int64_t nx, int64_t ny) {
+    if (nx + ny == 0) return;
+    const dim3 g((unsigned)(nx + ny));
     if (cplx)
-      hipLaunchKernelGGL(k_scan_rowsfast<true>, g, dim3(256), 0, st, v, lchunk, code);
+      hipLaunchKernelGGL(k_scan<true>, g, dim3(256), 0, st, x, y, nx);
     else
-      hipLaunchKernelGGL(k_scan_rowsfast<false>, g, dim3(256), 0, st, v, lchunk, code);
+      hipLaunchKernelGGL(k_scan<false>, g, dim3(256), 0, st, x, y, nx);
+  };
+  if (na + nb <= kMaxBlocks) {
+    go(a, b, na, nb);
   } else {
-    // sl == 1 (each row contiguous). A general-stride operand never reaches
-    // here: one of the two strides of a BLAS operand is always 1.
-    const int64_t rb = (v.R + 3) / 4;
-    int64_t ncol = std::max<int64_t>(1, std::min<int64_t>((v.L + 255) / 256, std::max<int64_t>(1, target / rb)));
-    const int64_t lchunk = (v.L + ncol - 1) / ncol;
-    ncol = (v.L + lchunk - 1) / lchunk;
-    dim3 g((unsigned)rb, (unsigned)ncol);
-    if (cplx)
-      hipLaunchKernelGGL(k_scan_rowcontig<true>, g, dim3(256), 0, st, v, lchunk, code);
-    else
-      hipLaunchKernelGGL(k_scan_rowcontig<false>, g, dim3(256), 0, st, v, lchunk, code);
+    go(a, a, na, 0);
+    go(b, b, nb, 0);
   }
   return hipGetLastError();
 }
@@ -534,6 +704,27 @@ hipError_t launch_split(const View &v, bool cplx, bool side_b, const int *code, 
     split_launch<true>(v, cplx, side_b, code, S, out, nrb, nkb, g, st);
   else
     split_launch<false>(v, cplx, side_b, code, S, out, nrb, nkb, g, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_split(const View &va, const int *ca, int8_t *oa, int64_t nrba, const View &vb,
+                        const int *cb, int8_t *ob, int64_t nrbb, int64_t nkb, bool cplx, int S,
+                        hipStream_t st, bool b8) {
+  if (b8 && (S < 1 || S > kS8Max)) return hipErrorInvalidValue;
+  const int64_t na = (nrba / 2) * (nkb / 2), nb = (nrbb / 2) * (nkb / 2);
+  if (na + nb > kMaxBlocks) {
+    const hipError_t e = launch_split(va, cplx, false, ca, S, oa, nrba, nkb, st, b8);
+    return e != hipSuccess ? e : launch_split(vb, cplx, true, cb, S, ob, nrbb, nkb, st, b8);
+  }
+  const SplitSide a{va, ca, oa, nrba, nkb}, b{vb, cb, ob, nrbb, nkb};
+  const dim3 g((unsigned)(na + nb));
+#define OZ_SPLIT_PAIR(C, B) hipLaunchKernelGGL((k_split_pair<C, B>), g, dim3(256), 0, st, a, b, na, S)
+  if (cplx) {
+    if (b8) OZ_SPLIT_PAIR(true, true); else OZ_SPLIT_PAIR(true, false);
+  } else {
+    if (b8) OZ_SPLIT_PAIR(false, true); else OZ_SPLIT_PAIR(false, false);
+  }
+#undef OZ_SPLIT_PAIR
   return hipGetLastError();
 }
 
@@ -577,6 +768,34 @@ hipError_t launch_split_batched(const SplitTask *tasks, const int64_t *start, in
                                 int64_t nblocks, hipStream_t st) {
   if (ntasks <= 0 || nblocks <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_split_batched, dim3((unsigned)nblocks), dim3(256), 0, st, tasks, start, ntasks);
+  return hipGetLastError();
+}
+
+namespace {
+int64_t prep_task_blocks(const PrepTask &t) {
+  return t.nrb * ((t.cplx && t.side_b) ? 16 : 32) / kRowsBlock;
+}
+}  // namespace
+
+bool prep_fits(const PrepTask &a, const PrepTask &b) {
+  return a.nkb * 32 <= kPrepK && prep_task_blocks(a) + prep_task_blocks(b) <= kMaxBlocks;
+}
+
+hipError_t launch_prep(const PrepTask &a, const PrepTask &b, hipStream_t st, bool b8) {
+  if (b8 && (a.S < 1 || a.S > kS8Max)) return hipErrorInvalidValue;
+  const int64_t na = prep_task_blocks(a), nb = prep_task_blocks(b);
+  const dim3 g((unsigned)(na + nb));
+  if (a.cplx) {
+    if (b8)
+      hipLaunchKernelGGL((k_prep<true, true>), g, dim3(256), 0, st, a, b, na);
+    else
+      hipLaunchKernelGGL((k_prep<true, false>), g, dim3(256), 0, st, a, b, na);
+  } else {
+    if (b8)
+      hipLaunchKernelGGL((k_prep<false, true>), g, dim3(256), 0, st, a, b, na);
+    else
+      hipLaunchKernelGGL((k_prep<false, false>), g, dim3(256), 0, st, a, b, na);
+  }
   return hipGetLastError();
 }
 

@@ -178,6 +178,32 @@ def test_gemm_bit_exact(kind, ta, tb, s):
     assert bits_equal(got, ref), mismatch_report(got, ref)
 
 
+# Up to 256 packed entries one kernel scans and splits 16 rows per block, beyond
+# that three do: one entry, one pass and one past it, in every storage order,
+# with Inf and NaN, subnormal and zero rows, for both slice kinds and every way
+# the slices are emitted (up to 8 or 9 in one word, more by digits).
+@pytest.mark.parametrize("split,s", [("t7", 1), ("t7", 8), ("t7", 9), ("t7", 12), ("b8", 3), ("b8", 8)])
+@pytest.mark.parametrize("kind,m,n,k", [("d", 16, 17, 1), ("d", 33, 15, 256), ("d", 33, 15, 257),
+                                        ("z", 17, 33, 128), ("z", 17, 33, 129), ("z", 1, 1, 65)])
+def test_short_contractions_bit_exact(split, s, kind, m, n, k):
+    from oracle import ozaki_b8
+    model = ozaki_b8.ozaki_gemm_b8 if split == "b8" else ozaki.ozaki_gemm
+    assert oz.ozaki_set_split(split) == 0
+    try:
+        for ta, tb in (("N", "N"), ("T", "N"), ("N", "T"), ("C", "C")):
+            for bad in (False, True):
+                A, B = _operands(kind, m, n, k, seed=620 + s, nasty=m > 1)
+                if bad:
+                    A[m // 2, k - 1], B[0, n // 2] = np.nan, -np.inf
+                _say("short contraction", split, s, kind, (m, n, k), ta, tb, bad)
+                got = _run_gemm(kind, ta, tb, A, B, s)
+                ref = model("N", "N", A, B, s)
+                assert bits_equal(got, ref), mismatch_report(got, ref)
+    finally:
+        torch.cuda.synchronize()
+        oz.ozaki_set_split("t7")
+
+
 @pytest.mark.parametrize("kind", ["d", "z"])
 def test_gemm_alpha_beta_bit_exact(kind):
     m, n, k = 97, 130, 65
