@@ -307,10 +307,13 @@ int ozaki_batched_cache_clear(void);
  * output rows, 1: along the columns); ids 14 .. 20 are configurations 0 .. 6
  * walking the tiles in groups of 16 tile rows, ids 21 .. 27 in groups of 8
  * tile rows with each XCD's workgroups on consecutive tiles.
- * ozaki_tune_configs() gives their number. Every id computes bit-identical
- * results: only the
- * workgroup shape, the LDS ring depth and the order in which the persistent
- * workgroups walk the output tiles differ.
+ * Id 0 instead leaves the shape and order to the product's sizes; where they
+ * give few tiles, workgroups also share a tile's contraction in parts, if the
+ * workspace has room for their sums (it is sized for them when it grows, but
+ * never grows for them alone).
+ * ozaki_tune_configs() gives the number of ids. Every id computes bit-identical
+ * results: only the workgroup shape, the parts, the LDS plan and the order in
+ * which the persistent workgroups walk the output tiles differ.
  * The table maps (kind, slices, bucket of m, of n' = n or 2n, of the 32-deep
  * contraction blocks of k' = k or 2k; bucket = ceil(log2)) to an id; ozaki_dgemm,
  * ozaki_zgemm and ozaki_debug_diagonals look their shape up there (default 0).

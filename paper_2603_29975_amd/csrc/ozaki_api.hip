@@ -149,7 +149,7 @@ int get_workspace(size_t bytes, void **out) {
       g.own_ws[dev] = nullptr;
       g.own_ws_bytes[dev] = 0;
     }
-    const size_t grow = std::max(bytes, (size_t)64 << 20);
+    const size_t grow = std::max(bytes, (size_t)256 << 20);
     void *p = nullptr;
     if (hipMalloc(&p, grow) != hipSuccess) {
       (void)hipGetLastError();
@@ -295,7 +295,7 @@ int tune_load(const char *path);
 
 // Tuning id of one emulated product: OZAKI_GEMM_CONFIG (a tuning id) wins,
 // then the tuning table (seeded once from the file named by OZAKI_TUNE_CACHE),
-// then the default 0.
+// then the default 0 (chosen by the sizes, see gemm_route).
 int gemm_config(bool cplx, int S, int64_t m, int64_t nprime, int64_t nkb) {
   static int env = -2;
   if (env == -2) {
@@ -397,6 +397,23 @@ GemmArgs gemm_args(const Plan &p, char *ws, double ar, double ai, double br, dou
   return a;
 }
 
+// Tuning id 0 (no entry in the table) resolved for a product's sizes: the tile
+// shape and, with the scratch that is there behind the plan's, the number of
+// parts of the contraction. The workspace never grows for the parts alone.
+int gemm_route(const Plan &p, int id, char *ws, size_t cap, int num_cu, GemmArgs *ga) {
+  if (id != 0) return id;
+  const size_t off = align256(p.total);
+  size_t need = 0;
+  const GemmChoice c = gemm_choose(p.S, p.m, p.nprime, p.nkb, p.kb_chunk, num_cu,
+                                   cap > off ? cap - off : 0, &need);
+  if (c.ksplit > 1) {
+    ga->ksplit = c.ksplit;
+    ga->kpart = c.kpart;
+    ga->parts = reinterpret_cast<int32_t *>(ws + off);
+  }
+  return c.id;
+}
+
 // One emulated product. fixed_ws == nullptr: scratch from get_workspace and
 // phase timing as enabled; otherwise the scratch is the device memory that
 // fixed_ws provides (called once the arguments have passed their checks;
@@ -424,10 +441,18 @@ int emulated_gemm_ws(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   int dev = 0;
   if ((rc = current_device(&dev))) return rc;
   const Plan p = make_plan(cplx, m, n, k, slices, g.dev[dev].num_cu, b8);
+  const int id = gemm_config(cplx, slices, m, p.nprime, p.nkb);
   char *ws = nullptr;
+  size_t cap = fixed_cap;
   if (fixed_ws == nullptr) {
     void *wsv = nullptr;
-    if ((rc = get_workspace(p.total, &wsv))) return rc;
+    size_t want = p.total;
+    if (g.user_ws == nullptr && g.own_ws_bytes[dev] < p.total && id == 0) {
+      size_t parts = 0;
+      (void)gemm_choose(slices, m, p.nprime, p.nkb, p.kb_chunk, g.dev[dev].num_cu, SIZE_MAX, &parts);
+      want = align256(p.total) + parts;
+    }
+    if ((rc = get_workspace_up_to(p.total, want, &wsv, &cap))) return rc;
     ws = static_cast<char *>(wsv);
   } else {
     if (p.total > fixed_cap) return OZAKI_ERR_TOO_LARGE;
@@ -437,10 +462,10 @@ int emulated_gemm_ws(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   const View va = view_opA(A, transa, m, k, lda, cplx);
   const View vb = view_opB(B, transb, k, n, ldb, cplx);
   if ((rc = prepare(p, ws, va, vb, g.stream, timed))) return rc;
-  const GemmArgs ga = gemm_args(p, ws, ar, ai, br, bi, beta_zero, C, ldc, nullptr);
+  GemmArgs ga = gemm_args(p, ws, ar, ai, br, bi, beta_zero, C, ldc, nullptr);
+  const int route = gemm_route(p, id, ws, cap, g.dev[dev].num_cu, &ga);
   const int mk = timed ? phase_begin(OZAKI_PHASE_GEMM, g.stream) : -1;
-  rc = hip_rc(launch_ozgemm(slices, gemm_config(cplx, slices, m, p.nprime, p.nkb), ga,
-                            g.dev[dev].num_cu, g.stream));
+  rc = hip_rc(launch_ozgemm(slices, route, ga, g.dev[dev].num_cu, g.stream));
   phase_end(mk, g.stream);
   if (timed && g_tm.on) ++g_tm.calls;
   return rc;
@@ -1583,6 +1608,7 @@ int autotune(bool cplx, int64_t m, int64_t n, int64_t k, int S, int reps, int *b
   void *wsv = nullptr;
   if ((rc = get_workspace(p.total, &wsv))) return rc;
   char *ws = static_cast<char *>(wsv);
+  const size_t cap = g.user_ws != nullptr ? g.user_ws_bytes : g.own_ws_bytes[dev];
   const hipStream_t st = g.stream;
   if ((rc = hip_rc(launch_fill_i32(reinterpret_cast<int *>(ws + p.off_codeA), m, kCodeBias, st))))
     return rc;
@@ -1608,8 +1634,11 @@ int autotune(bool cplx, int64_t m, int64_t n, int64_t k, int S, int reps, int *b
   for (int round = 0; rc == OZAKI_OK && round <= kRounds; ++round) {
     for (int id = 0; rc == OZAKI_OK && id < nid; ++id) {
       if ((rc = hip_rc(hipEventRecord(e0, st)))) break;
-      for (int r = 0; rc == OZAKI_OK && r < reps; ++r)
-        rc = hip_rc(launch_ozgemm(S, id, ga, g.dev[dev].num_cu, st));
+      for (int r = 0; rc == OZAKI_OK && r < reps; ++r) {
+        GemmArgs gi = ga;
+        const int route = gemm_route(p, id, ws, cap, g.dev[dev].num_cu, &gi);
+        rc = hip_rc(launch_ozgemm(S, route, gi, g.dev[dev].num_cu, st));
+      }
       if (rc) break;
       if ((rc = hip_rc(hipEventRecord(e1, st)))) break;
       if ((rc = hip_rc(hipEventSynchronize(e1)))) break;

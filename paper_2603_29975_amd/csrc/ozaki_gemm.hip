@@ -92,6 +92,10 @@ struct Cfg {
   static constexpr int XyBytes = S * (FJ + 2 * FI) * kFragBytes;
 };
 
+// How a tile's contraction runs: in one piece, in chunks carried by the workgroup,
+// or (few tiles) in parts by different workgroups, whose sums k_ozparts adds.
+enum { kWhole, kChunked, kParts };
+
 // Word w of this wave's chunk sums, lane-interleaved: a wave-uniform base and a
 // 32-bit lane offset, so that the addresses cost no vector registers. The
 // accesses are device-scope, which keeps the traffic in L2, away from stale
@@ -101,7 +105,7 @@ __device__ __forceinline__ T *carry_word(char *base, int w, uint32_t lane) {
   return reinterpret_cast<T *>(base + (int64_t)w * (64 * sizeof(T)) + lane * (uint32_t)sizeof(T));
 }
 
-template <int S, int WJ, int WI, int IB, int WPS, bool RING, int LA, bool RAW, bool CHUNKED>
+template <int S, int WJ, int WI, int IB, int WPS, bool RING, int LA, bool RAW, int MODE>
 __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
   using C_ = Cfg<S, WJ, WI, IB>;
   constexpr int NW = C_::NW, FJ = C_::FJ, FI = C_::FI;
@@ -111,6 +115,7 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
   constexpr int MINC = NCB / NW + NCA / NW;  // at least
   constexpr int STAGE = (NCB + NCA) * kFragBytes;
   constexpr int LDS = RING ? C_::RingBytes : C_::XyBytes;
+  constexpr bool CHUNKED = MODE == kChunked, PARTS = MODE == kParts;
   constexpr int NA = S * IB;  // A' fragments per block
   constexpr int R = LA + 1;   // their register slots
   // X (RING: the one barrier) comes when the first A' fragment is done with,
@@ -137,14 +142,17 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
   const int64_t ntiles = grouped ? ga->ntiles
                                  : ((ga->one.nprime + C_::BJ - 1) / C_::BJ) *
                                        ((ga->one.m + C_::BI - 1) / C_::BI);
+  const int64_t nitems = PARTS ? ntiles * ga->ksplit : ntiles;
 
-  for (int64_t tn = blockIdx.x; tn < ntiles; tn += gridDim.x) {
+  for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+    // part first: the workgroups of one part share its A' and B' rows
+    const int64_t tn = PARTS ? item % ntiles : item;
     // The problem this tile belongs to (uniform across the workgroup).
     ProblemPtr pr = grouped ? (ProblemPtr)(uint64_t)(ga->probs + ((IntPtr)(uint64_t)ga->tile_prob)[tn])
                             : &ga->one;
     int64_t tj, ti;
     {
-      const int order = ga->order;
+      const int order = PARTS ? 0 : ga->order;
       int64_t local = grouped ? (int64_t)((IntPtr)(uint64_t)ga->tile_local)[tn] : tn;
       if (!grouped && order == 3) local = tile::xcd_major(tn, ntiles);
       tile::tile_coords(local, order, pr->m, pr->nprime, C_::BJ, C_::BI, tj, ti);
@@ -164,9 +172,9 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
              (int64_t)wave * (WORDS * 64) * (wide ? sizeof(int64_t) : sizeof(int32_t));
     };
 
-    int64_t k0 = 0;
+    int64_t k0 = PARTS ? (item / ntiles) * ga->kpart : 0;
     do {
-      const int nkb = CHUNKED ? (int)(nkb_all - k0 < chunk ? nkb_all - k0 : chunk) : (int)nkb_all;
+      const int nkb = PARTS ? (int)(nkb_all - k0 < ga->kpart ? nkb_all - k0 : ga->kpart) : CHUNKED ? (int)(nkb_all - k0 < chunk ? nkb_all - k0 : chunk) : (int)nkb_all;
       // sources of this wave's copies at block k0: copy x moves fragment wave +
       // x NW of the block's B' (then A') fragments, slice-major
       const int8_t *src[XC];
@@ -325,6 +333,18 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
       k0 += chunk;
     } while (CHUNKED && k0 < nkb_all);
 
+    if constexpr (PARTS) {
+      char *cb = reinterpret_cast<char *>(ga->parts) + (tn * ga->ksplit + item / ntiles) * kSlot +
+                 (int64_t)wave * (WORDS * 64) * sizeof(int32_t);
+#pragma unroll
+      for (int w = 0; w < WORDS; ++w) {
+        *carry_word<int32_t>(cb, w, lane) = acc_word(w);
+        if (w % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      wait_vmcnt<0>();  // the copies' vmcnt counts stay to themselves
+      continue;
+    }
+
     // ------------------------------------------------------------ epilogue
     // (the problem's fields are fetched again here, not kept through the loop)
     asm volatile("" : "+s"(pr));
@@ -380,7 +400,57 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
   }
 }
 
-template <int S, int WJ, int WI, int IB, int WPS, bool RING, int LA, bool RAW, bool CHUNKED>
+// The parts of every tile added (int64: their total may pass 2^31) and finished
+// as in the epilogue above. One workgroup per 16 x 16 block, a wave per row r of
+// the MFMA result's four: bound by the latency of its loads, so four parts' sums
+// are in flight at a time (one wave per block and one part at a time took 1 to 8
+// us per part).
+template <int S, int WJ, int WI, int IB>
+__global__ void __launch_bounds__(256) k_ozparts(GemmArgs G) {
+  using C_ = Cfg<S, WJ, WI, IB>;
+  constexpr int WORDS = IB * S * 4, kAhead = 4;
+  __shared__ double rows[4][64];
+  const ArgsPtr ga = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int lane = threadIdx.x & 63;
+  const int r = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t tn = blockIdx.x / (C_::NW * IB);
+  const int wave = (int)(blockIdx.x / IB % C_::NW), ib = (int)(blockIdx.x % IB);
+  const int ksplit = ga->ksplit;
+  int64_t sum[S];
+#pragma unroll
+  for (int t = 0; t < S; ++t) sum[t] = 0;
+  const int32_t *p = ga->parts + (tn * ksplit * C_::NW + wave) * (int64_t)(WORDS * 64) +
+                     (ib * S * 4 + r) * 64 + lane;
+  constexpr int64_t kPart = (int64_t)C_::NW * WORDS * 64;
+  for (int k = 0; k < ksplit; k += kAhead) {
+    int32_t v[kAhead][S];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int32_t *q = p + (k + u < ksplit ? k + u : k) * kPart;
+#pragma unroll
+      for (int t = 0; t < S; ++t) v[u][t] = q[t * 256];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int t = 0; t < S; ++t) sum[t] += k + u < ksplit ? v[u][t] : 0;
+  }
+  double val = 0.0;
+  const int wbits = ga->one.wbits, woff = ga->one.woff;
+#pragma unroll
+  for (int t = 0; t < S; ++t) val = add_rn(val, ldexp((double)sum[t], woff - wbits * (t + 2)));
+  rows[r][lane] = val;
+  __syncthreads();
+  if (r != 0) return;
+  int64_t tj, ti;
+  tile::tile_coords(tn, 0, ga->one.m, ga->one.nprime, C_::BJ, C_::BI, tj, ti);
+  const double all[4] = {rows[0][lane], rows[1][lane], rows[2][lane], rows[3][lane]};
+  tile::store_block(&ga->one, all, ti * C_::BI + ((wave / WJ) * IB + ib) * 16 + (lane & 15),
+                    tj * C_::BJ + (wave % WJ) * 16 + 4 * (lane >> 4));
+}
+
+template <int S, int WJ, int WI, int IB, int WPS, bool RING, int LA, bool RAW, int MODE>
 hipError_t launch_cfg(const GemmArgs &a, int num_cu, hipStream_t st) {
   using C_ = Cfg<S, WJ, WI, IB>;
   const int64_t ntiles = a.probs != nullptr
@@ -388,11 +458,15 @@ hipError_t launch_cfg(const GemmArgs &a, int num_cu, hipStream_t st) {
                              : ((a.one.nprime + C_::BJ - 1) / C_::BJ) * ((a.one.m + C_::BI - 1) / C_::BI);
   // persistent grid: WPS waves per SIMD, i.e. one workgroup of 8 waves per CU or
   // two of 4 (whose barriers are independent, so one's MFMAs fill the other's waits)
-  int64_t grid = std::min<int64_t>(ntiles, (int64_t)(4 * WPS / C_::NW) * num_cu);
+  int64_t grid = std::min<int64_t>(MODE == kParts ? ntiles * a.ksplit : ntiles,
+                                   (int64_t)(4 * WPS / C_::NW) * num_cu);
   if (a.max_groups > 0) grid = std::min<int64_t>(grid, a.max_groups);
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, WPS, RING, LA, RAW, CHUNKED>), dim3((unsigned)grid),
+  hipLaunchKernelGGL((k_ozgemm<S, WJ, WI, IB, WPS, RING, LA, RAW, MODE>), dim3((unsigned)grid),
                      dim3(64 * C_::NW), 0, st, a);
+  if constexpr (MODE == kParts)
+    hipLaunchKernelGGL((k_ozparts<S, WJ, WI, IB>), dim3((unsigned)(ntiles * C_::NW * IB)), dim3(256), 0,
+                       st, a);
   return hipGetLastError();
 }
 
@@ -431,24 +505,25 @@ constexpr int shape_bi(Shape s) { return s == kBig || s == kWide ? 128 : 64; }
 
 constexpr bool ring_fits(int bytes, int groups) { return bytes * groups <= 160 * 1024; }
 
-template <int S, bool RAW, bool CHUNKED>
+template <int S, bool RAW, int MODE>
 hipError_t launch_shape(Shape shape, const GemmArgs &a, int num_cu, hipStream_t st) {
   constexpr int LA = S == 1 ? 1 : 3;
-  constexpr bool all = !RAW;  // raw sums take 128 x 64 or 64 x 64 tiles
+  // raw sums take 128 x 64 or 64 x 64 tiles, parts 64 x 64 ones
+  constexpr bool all = !RAW && MODE != kParts;
   if (shape == kBig) {
     if constexpr (S <= 6 && all)
-      return launch_cfg<S, 8, 1, 8, 2, ring_fits(Cfg<S, 8, 1, 8>::RingBytes, 1), LA, RAW, CHUNKED>(a, num_cu, st);
+      return launch_cfg<S, 8, 1, 8, 2, ring_fits(Cfg<S, 8, 1, 8>::RingBytes, 1), LA, RAW, MODE>(a, num_cu, st);
   } else if (shape == kTall) {
-    if constexpr (S <= 10)
-      return launch_cfg<S, 8, 1, 4, 2, ring_fits(Cfg<S, 8, 1, 4>::RingBytes, 1), LA, RAW, CHUNKED>(a, num_cu, st);
+    if constexpr (S <= 10 && MODE != kParts)
+      return launch_cfg<S, 8, 1, 4, 2, ring_fits(Cfg<S, 8, 1, 4>::RingBytes, 1), LA, RAW, MODE>(a, num_cu, st);
   } else if (shape == kWide) {
     if constexpr (S <= 8 && all)
-      return launch_cfg<S, 4, 2, 4, 2, ring_fits(Cfg<S, 4, 2, 4>::RingBytes, 1), LA, RAW, CHUNKED>(a, num_cu, st);
+      return launch_cfg<S, 4, 2, 4, 2, ring_fits(Cfg<S, 4, 2, 4>::RingBytes, 1), LA, RAW, MODE>(a, num_cu, st);
   } else {
     if constexpr (S <= 6)
-      return launch_cfg<S, 4, 1, 4, 2, ring_fits(Cfg<S, 4, 1, 4>::RingBytes, 2), LA, RAW, CHUNKED>(a, num_cu, st);
+      return launch_cfg<S, 4, 1, 4, 2, ring_fits(Cfg<S, 4, 1, 4>::RingBytes, 2), LA, RAW, MODE>(a, num_cu, st);
     else
-      return launch_cfg<S, 4, 2, 2, 2, false, LA, RAW, CHUNKED>(a, num_cu, st);
+      return launch_cfg<S, 4, 2, 2, 2, false, LA, RAW, MODE>(a, num_cu, st);
   }
   return hipErrorInvalidValue;
 }
@@ -458,10 +533,11 @@ hipError_t launch_s(int cfg, const GemmArgs &a, int num_cu, hipStream_t st) {
   const bool raw = a.one.raw != nullptr;
   const Shape shape = shape_of(S, raw ? 0 : cfg);
   if (raw)
-    return a.chunked ? launch_shape<S, true, true>(shape, a, num_cu, st)
-                     : launch_shape<S, true, false>(shape, a, num_cu, st);
-  return a.chunked ? launch_shape<S, false, true>(shape, a, num_cu, st)
-                   : launch_shape<S, false, false>(shape, a, num_cu, st);
+    return a.chunked ? launch_shape<S, true, kChunked>(shape, a, num_cu, st)
+                     : launch_shape<S, true, kWhole>(shape, a, num_cu, st);
+  if (a.ksplit > 1) return launch_shape<S, false, kParts>(shape, a, num_cu, st);
+  return a.chunked ? launch_shape<S, false, kChunked>(shape, a, num_cu, st)
+                   : launch_shape<S, false, kWhole>(shape, a, num_cu, st);
 }
 
 }  // namespace
@@ -482,6 +558,49 @@ int64_t gemm_tiles(int S, int id, int64_t m, int64_t nprime) {
   const Shape s = shape_of(S, id_cfg(id));
   const int64_t BJ = shape_bj(s), BI = shape_bi(s);
   return ((nprime + BJ - 1) / BJ) * ((m + BI - 1) / BI);
+}
+
+GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb_chunk, int num_cu,
+                       size_t parts_bytes, size_t *need) {
+  // Estimated time in us, the least over tile shapes and numbers of parts. Per
+  // contraction block of 64 a workgroup takes the larger of its share of the
+  // MFMA rate (`rate` times that of back-to-back MFMAs, two 64 x 64 workgroups of
+  // a CU in turn) and the latency of one alone. The parts' sums are written and
+  // read once, by 64 x 64 tiles only (128 x 64 ones were never faster). Fitted to
+  // 224 products of sides 16 .. 8192 at S = 3 .. 11 in up to 70 ways each: 1.6%
+  // slower on average than the fastest way of each. Before, 128 x 64 tiles for
+  // all: z 64 x 64 x 4096 S = 7 246 us, now 21; z 256 x 256 x 8192 475, now 70;
+  // z 517 x 389 x 1031 72, now 41; z 1500 x 700 x 300 57, now 50.
+  const double mfma = S * (S + 1) / 2 * 16 / 2400.0;  // one 16 x 16 x 64 block, on each SIMD
+  const int64_t kb = nkb / 2, chunk = std::max<int64_t>(kb_chunk / 2, 1);
+  GemmChoice best{0, 1, kb};
+  double best_t = 1e300;
+  *need = 0;
+  for (const Shape s : {kTall, kBig, kSmall}) {
+    if ((s == kBig && S > 6) || (s == kTall && S > 10)) continue;
+    const int64_t area = (int64_t)shape_bj(s) * shape_bi(s);
+    const int64_t tiles = ((nprime + shape_bj(s) - 1) / shape_bj(s)) * ((m + shape_bi(s) - 1) / shape_bi(s));
+    const bool two = s == kSmall && S <= 6;  // workgroups per CU
+    const double rate = s == kBig ? 1.41 : s == kTall ? 1.44 : two ? 1.89 : 1.72;
+    const double alone = area / 1024 * mfma;
+    for (int64_t ks = 1; ks <= (s == kSmall ? 64 : 1); ++ks) {
+      const int64_t part = (kb + ks - 1) / ks, items = tiles * ks;
+      const size_t bytes = ks > 1 ? (size_t)items * area * S * sizeof(int32_t) : 0;
+      if (ks > 1 && (part < 2 || items > 4 * num_cu)) break;
+      if (ks > 1 && ((ks - 1) * part >= kb || part > chunk || bytes > parts_bytes)) continue;
+      const int64_t slots = num_cu * (two ? 2 : 1), rounds = (items + slots - 1) / slots;
+      const double turn = two && items > num_cu ? 2 * rate : rate;
+      double t = rounds * (1.7 + part * std::max(turn * alone, 1.19 * alone + 0.26));
+      if (ks > 1) t += 2.1 + 0.38e-6 * bytes + 0.13 * ks;
+      if (t < best_t) {
+        best_t = t;
+        // 128-row tiles in XCD-aware groups, the others down the rows
+        best = GemmChoice{s == kBig ? 27 : s == kTall ? 21 : 8, (int)ks, part};
+        *need = bytes;
+      }
+    }
+  }
+  return best;
 }
 
 hipError_t launch_ozgemm_grouped(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st) {

@@ -113,12 +113,25 @@ struct GemmArgs {
   int64_t *flush_ws;  // per-workgroup carry space (problems with nkb > kb_chunk)
   int64_t kb_chunk;   // contraction blocks per exact INT32 chunk
   int chunked;        // some problem has nkb > kb_chunk
+  int ksplit;         // > 1: each tile's contraction in so many parts (single product)
+  int64_t kpart;      // contraction blocks of 64 per part
+  int32_t *parts;     // the parts' sums
   int order;          // tile order (set from the tuning id at launch)
   int64_t max_groups; // cap on the persistent grid (0: no cap beyond the CU count)
 };
 
 // Tile counts of a problem for a configuration (host side).
 int64_t gemm_tiles(int S, int cfg, int64_t m, int64_t nprime);
+// The tile shape and the number of parts of the contraction for a product's
+// sizes (tuning id 0). parts_bytes: what the parts' sums may take at most; what
+// they take is in *need (0: one part).
+struct GemmChoice {
+  int id;  // tuning id of the shape
+  int ksplit;
+  int64_t kpart;
+};
+GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb_chunk, int num_cu,
+                       size_t parts_bytes, size_t *need);
 // Launch a grouped GEMM over the tile table in `a` (every problem has S slices).
 hipError_t launch_ozgemm_grouped(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st);
 

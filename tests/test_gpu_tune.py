@@ -95,6 +95,39 @@ def test_every_slice_count_at_tile_edges(split, kind, m, n, k):
         oz.ozaki_set_split("t7")
 
 
+# Few tiles and a long contraction: id 0 sums it in parts by different workgroups
+# (64 x 64 tiles, last part shorter, contractions beyond one INT32 sum among
+# them). A workspace with no room for the parts takes the other tiles; the bits
+# are the oracle's either way, alpha, beta, Inf and NaN included.
+@pytest.mark.parametrize("split", ["t7", "b8"])
+@pytest.mark.parametrize("kind,m,n,k,s", [("d", 1, 1, 128, 7), ("z", 64, 32, 2050, 6), ("z", 70, 65, 700, 8),
+                                          ("d", 129, 63, 4097, 3), ("d", 40, 200, 20000, 8),
+                                          ("z", 20, 30, 12000, 7), ("d", 65, 64, 3000, 1)])
+def test_contraction_in_parts(split, kind, m, n, k, s):
+    from oracle import ozaki_b8
+    model = ozaki_b8.ozaki_gemm_b8 if split == "b8" else ozaki.ozaki_gemm
+    A, B = scaled_gaussian(m, n, k, seed=740 + s, rmax=20, complex_=kind == "z")
+    if m > 1:
+        A[m // 2, k - 1], B[0, n // 2] = np.inf, np.nan
+    dt = np.complex128 if kind == "z" else np.float64
+    C0 = np.random.default_rng(741).standard_normal((m, n)).astype(dt)
+    alpha, beta = (0.75 - 0.5j, -1.0 + 0.25j) if kind == "z" else (0.75, -1.5)
+    ref = model("N", "N", A, B, s, alpha, beta, C0)
+    assert oz.ozaki_set_split(split) == 0
+    try:
+        _say("parts", split, kind, (m, n, k), s)
+        got = _gemm(kind, A, B, s, alpha, beta, C0)
+        assert bits_equal(got, ref), mismatch_report(got, ref)
+        tight = torch.empty(oz.ozaki_workspace_bytes(kind, m, n, k, s), dtype=torch.uint8, device="cuda")
+        assert oz.ozaki_set_workspace(tight, tight.numel()) == 0
+        got = _gemm(kind, A, B, s, alpha, beta, C0)
+        assert bits_equal(got, ref), "no room\n" + mismatch_report(got, ref)
+    finally:
+        torch.cuda.synchronize()
+        oz.ozaki_set_workspace(None, 0)
+        oz.ozaki_set_split("t7")
+
+
 def test_every_tuning_id_alpha_beta():
     m, n, k, s = 97, 130, 65, 6
     A, B = uniform_binade(m, n, k, seed=780, complex_=True)
