@@ -53,8 +53,8 @@ hipError_t launch_scan_batched(const ScanTask *tasks, const int64_t *start, int 
 hipError_t launch_split_batched(const SplitTask *tasks, const int64_t *start, int ntasks,
                                 int64_t nblocks, hipStream_t st);
 
-// Scan and split of both operands of a product in one kernel, 16 rows per block
-// (codes stored, no zero fill needed), for short contractions.
+// Scan and split of both operands of a product in one kernel (codes stored, no
+// zero fill needed), for short contractions.
 struct PrepTask {
   View v;
   int *code;
@@ -64,12 +64,12 @@ struct PrepTask {
   int cplx;
   int side_b;
 };
-// A short contraction is scanned and split in one kernel, 16 rows per block: one
-// launch instead of three. A block takes 256 packed entries per pass, so a longer
-// contraction would run its passes one after the other on too few blocks.
-// Measured, whole call: z 32^3 17.6 us (23.4 with three launches), d 256^3 (K' =
-// 256) 20.8 (25.3); beyond it z 256^3 (K' = 512) 30.8 (22.0).
-constexpr int64_t kPrepK = 256;  // packed contraction up to which that holds
+// A short contraction is scanned and split in one kernel: one launch instead of
+// three, for a scan per 64 packed entries. Measured, whole call, one kernel /
+// three: z 32^3 12.3 / 16.9 us, d 256^3 (256 packed entries) 14.8 / 19.7, z
+// 1920^2 x 128 60.7 / 65.4; with 512 entries z 256^3 20.8 / 22.2, d 512^3 23.5 /
+// 27.0 (512 blocks of the kernel) but z 1200^2 x 256 53.2 / 51.3 (1280 blocks);
+// with 1024 entries d 1024^3 62 / 45.
 bool prep_fits(const PrepTask &a, const PrepTask &b);
 hipError_t launch_prep(const PrepTask &a, const PrepTask &b, hipStream_t st, bool b8);
 

@@ -433,35 +433,40 @@ __global__ void __launch_bounds__(256) k_split_batched(const SplitTask *tasks, c
 }
 
 // ---------------------------------------------------------------- scan + split
-// Bound by the launches it replaces and by its one chain of loads (scan, then the
-// packed entries out of the caches). Whole call with this kernel and the GEMM / with
-// a fill, two scans and two splits before it: z 32^3 S = 7 16 / 27 us, d 256^3
-// 19 / 25 us.
-// The slices of 16 packed entries of view row vr (see pack_rows): one 16-byte
-// run per slice, or for complex B two, X' rows 2 vr = (Re, -Im) and 2 vr + 1 =
+// Exponent scan and packing of an operand in one kernel: a block of 256 threads
+// scans 16 view rows over the whole contraction and packs one 64-entry fragment
+// of them, one thread per row and four packed entries, so that a wave's stores
+// are contiguous. Every block of a row scans it again; that costs reads of the
+// caches, but one block per row would leave the chip to a few long chains:
+// bound by its launch, two loads in a row and the digits' arithmetic. Whole call
+// z 32^3 S = 7 12.3 us, d 256^3 14.8 (16 entries per thread and the whole
+// contraction per block: 16.1 and 19.5).
+constexpr int kPrepRows = 16;
+
+// The slices of four packed entries (complex: re, im, re, im) of view row vr: one
+// word per slice, or for complex B two, X' rows 2 vr = (Re, -Im) and 2 vr + 1 =
 // (Im, Re), from the same digits: with trunc-7 slices those of -Im are the
 // negated ones of Im, with 8-bit slices -Im is split as it stands.
 __device__ __forceinline__ uint32_t swap_pairs(uint32_t w) {
   return __builtin_amdgcn_perm(0u, w, 0x02030001u);  // bytes 1, 0, 3, 2
 }
 
-template <bool CPLX, bool SIDEB, bool B8, int SC>
-__device__ __forceinline__ void emit_slices(const double (&x)[16], int e, int S, int8_t *dst, int64_t plane) {
-  constexpr bool PAIR = CPLX && SIDEB;
-  Sig sg[16];
+template <bool PAIR, bool B8, int SC>
+__device__ __forceinline__ void emit_slices(const double (&x)[4], int e, int S, int8_t *dst, int64_t plane) {
+  Sig sg[4];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) sg[q] = decompose(x[q], e);
-  auto put = [&](int p, const uint32_t (&a)[4], const uint32_t (&b)[4]) {
+  for (int q = 0; q < 4; ++q) sg[q] = decompose(x[q], e);
+  auto put = [&](int p, uint32_t a, uint32_t b) {
     int8_t *d = dst + (int64_t)(p - 1) * plane;
-    *reinterpret_cast<uint4 *>(d) = make_uint4(a[0], a[1], a[2], a[3]);
-    if constexpr (PAIR) *reinterpret_cast<uint4 *>(d + 16) = make_uint4(b[0], b[1], b[2], b[3]);
+    *reinterpret_cast<uint32_t *>(d) = a;
+    if constexpr (PAIR) *reinterpret_cast<uint32_t *>(d + 16) = b;
   };
   if constexpr (B8) {
     // the bytes of X + 0x80...80, as in split_block
     constexpr uint64_t kBias = 0x8080808080808080ull >> (8 * (8 - SC));
-    uint64_t Y[16], M[8];  // M: -Im
+    uint64_t Y[4], M[2];  // M: -Im
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 4; ++q) {
       const uint64_t u = top_nbits<8 * SC - 2>(sg[q]);
       Y[q] = (sg[q].neg ? 0ull - u : u) + kBias;
       if (PAIR && (q & 1)) M[q >> 1] = (sg[q].neg ? u : 0ull - u) + kBias;
@@ -469,56 +474,40 @@ __device__ __forceinline__ void emit_slices(const double (&x)[16], int e, int S,
 #pragma unroll
     for (int p = SC; p >= 1; --p) {
       const int sh = 8 * (SC - p);
-      uint32_t a[4], b[4];
+      uint32_t w = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) w |= ((uint32_t)(Y[4 * q + k] >> sh) & 0xffu) << (8 * k);
-        w ^= 0x80808080u;
-        a[q] = w;
-        if constexpr (PAIR) {
-          uint32_t m = (((uint32_t)(M[2 * q] >> sh) & 0xffu) << 8) | (((uint32_t)(M[2 * q + 1] >> sh) & 0xffu) << 24);
-          b[q] = swap_pairs(w);
-          a[q] = (w & 0x00ff00ffu) | (m ^ 0x80008000u);
-        }
+      for (int k = 0; k < 4; ++k) w |= ((uint32_t)(Y[k] >> sh) & 0xffu) << (8 * k);
+      w ^= 0x80808080u;
+      if constexpr (PAIR) {
+        const uint32_t m = (((uint32_t)(M[0] >> sh) & 0xffu) << 8) | (((uint32_t)(M[1] >> sh) & 0xffu) << 24);
+        put(p, (w & 0x00ff00ffu) | (m ^ 0x80008000u), swap_pairs(w));
+      } else {
+        put(p, w, 0);
       }
-      put(p, a, b);
     }
   } else {
-    uint64_t T[16];
-    uint32_t neg[4];
+    uint64_t T[4];
+    uint32_t neg = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      uint32_t mk = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if constexpr (SC > 0) T[4 * q + k] = top_bits<SC>(sg[4 * q + k]);
-        mk |= (sg[4 * q + k].neg ? 0xffu : 0u) << (8 * k);
-      }
-      neg[q] = mk;
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (SC > 0) T[k] = top_bits<SC>(sg[k]);
+      neg |= (sg[k].neg ? 0xffu : 0u) << (8 * k);
     }
     auto slice = [&](int p) {
-      uint32_t a[4], b[4];
+      uint32_t w = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          uint32_t d;
-          if constexpr (SC > 0)
-            d = (uint32_t)(T[4 * q + k] >> (kDigitBits * (SC - p))) & 127u;
-          else
-            d = (uint32_t)digit(Sig{sg[4 * q + k].m, sg[4 * q + k].sh0, false}, p);
-          w |= d << (8 * k);
-        }
-        a[q] = neg_bytes(w, neg[q]);
-        if constexpr (PAIR) {
-          b[q] = swap_pairs(a[q]);
-          a[q] = neg_bytes(w, neg[q] ^ 0xff00ff00u);
-        }
+      for (int k = 0; k < 4; ++k) {
+        uint32_t d;
+        if constexpr (SC > 0)
+          d = (uint32_t)(T[k] >> (kDigitBits * (SC - p))) & 127u;
+        else
+          d = (uint32_t)digit(Sig{sg[k].m, sg[k].sh0, false}, p);
+        w |= d << (8 * k);
       }
-      put(p, a, b);
+      if constexpr (PAIR)
+        put(p, neg_bytes(w, neg ^ 0xff00ff00u), swap_pairs(neg_bytes(w, neg)));
+      else
+        put(p, neg_bytes(w, neg), 0);
     };
     if constexpr (SC > 0) {
 #pragma unroll
@@ -530,35 +519,88 @@ __device__ __forceinline__ void emit_slices(const double (&x)[16], int e, int S,
 }
 
 template <bool CPLX, bool SIDEB, bool B8>
-__device__ __forceinline__ void prep_task(const PrepTask &tk, int64_t block, RowsLds &lds) {
-  const int64_t plane = tk.nrb * tk.nkb * kFragBytes;
-  pack_rows<CPLX>(tk.v, block, tk.nkb * 2, tk.code, lds, [&](const double(&x)[16], int e, int64_t vr, int64_t ch) {
-    int8_t *dst = tk.out + frag_offset(0, (CPLX && SIDEB) ? 2 * vr : vr, ch * 16, tk.nrb, tk.nkb);
-    switch (tk.S) {
-#define OZ_EMIT(N) \
-  case N: emit_slices<CPLX, SIDEB, B8, N>(x, e, N, dst, plane); break;
-      OZ_EMIT(1) OZ_EMIT(2) OZ_EMIT(3) OZ_EMIT(4) OZ_EMIT(5) OZ_EMIT(6) OZ_EMIT(7) OZ_EMIT(8)
-      default:
-        if constexpr (!B8) {
-          if (tk.S == 9)
-            emit_slices<CPLX, SIDEB, B8, 9>(x, e, 9, dst, plane);
-          else
-            emit_slices<CPLX, SIDEB, B8, 0>(x, e, tk.S, dst, plane);
-        }
-        break;
-#undef OZ_EMIT
+__device__ __forceinline__ void prep_task(const PrepTask &tk, uint32_t block, int *red) {
+  using E = typename std::conditional<CPLX, double2, double>::type;
+  constexpr int NE = CPLX ? 2 : 4;  // elements per thread
+  constexpr int U = 8;              // scan loads in flight per thread
+  const View &v = tk.v;
+  const E *X = reinterpret_cast<const E *>(v.base);
+  const int tid = threadIdx.x;
+  const uint32_t nfrag = (uint32_t)(tk.nkb / 2), kb = block % nfrag;
+  const int64_t r0 = (int64_t)(block / nfrag) * kPrepRows;
+  const int r = (tid >> 2) & 15;
+  const int64_t vr = r0 + r;
+  const int64_t kk = (int64_t)kb * 64 + (tid >> 6) * 16 + (tid & 3) * 4, l0 = kk / (CPLX ? 2 : 1);
+  E val[NE];  // in flight during the scan
+#pragma unroll
+  for (int x = 0; x < NE; ++x)
+    val[x] = X[(vr < v.R && l0 + x < v.L) ? vr * v.sr + (l0 + x) * v.sl : 0];
+  // codes: 16 threads per row, along the rows where those are contiguous
+  const bool along = v.sl == 1;
+  const int sr = along ? tid >> 4 : tid & 15, sl = along ? tid & 15 : tid >> 4;
+  int c = 0;
+  if (r0 + sr < v.R) {
+    const int64_t base = (r0 + sr) * v.sr;
+    for (int64_t l = sl; l < v.L; l += 16 * U) {
+      int a[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        a[u] = elem_code<CPLX>(v.base, base + (l + 16 * u < v.L ? l + 16 * u : l) * v.sl);
+#pragma unroll
+      for (int u = 0; u < U; ++u) c = max(c, a[u]);
     }
-  });
+  }
+  red[sr * 17 + sl] = c;
+  __syncthreads();
+  if (tid < kPrepRows) {
+    c = 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) c = max(c, red[tid * 17 + u]);
+    red[16 * 17 + tid] = c;
+    if (kb == 0 && r0 + tid < v.R) tk.code[r0 + tid] = c;
+  }
+  __syncthreads();
+  c = red[16 * 17 + r];
+  const bool live = vr < v.R && !code_bad(c);  // rows with Inf or NaN pack zeros
+  double x[4];
+#pragma unroll
+  for (int q = 0; q < NE; ++q) {
+    const bool ok = live && l0 + q < v.L;
+    if constexpr (CPLX) {
+      x[2 * q] = ok ? val[q].x : 0.0;
+      x[2 * q + 1] = ok ? (v.conj ? -val[q].y : val[q].y) : 0.0;
+    } else {
+      x[q] = ok ? val[q] : 0.0;
+    }
+  }
+  constexpr bool PAIR = CPLX && SIDEB;
+  const int e = code_exp(c);
+  const int64_t plane = tk.nrb * tk.nkb * kFragBytes;
+  int8_t *dst = tk.out + frag_offset(0, PAIR ? 2 * vr : vr, kk, tk.nrb, tk.nkb);
+  switch (tk.S) {
+#define OZ_EMIT(N) \
+  case N: emit_slices<PAIR, B8, N>(x, e, N, dst, plane); break;
+    OZ_EMIT(1) OZ_EMIT(2) OZ_EMIT(3) OZ_EMIT(4) OZ_EMIT(5) OZ_EMIT(6) OZ_EMIT(7) OZ_EMIT(8)
+    default:
+      if constexpr (!B8) {
+        if (tk.S == 9)
+          emit_slices<PAIR, B8, 9>(x, e, 9, dst, plane);
+        else
+          emit_slices<PAIR, B8, 0>(x, e, tk.S, dst, plane);
+      }
+      break;
+#undef OZ_EMIT
+  }
 }
 
 template <bool CPLX, bool B8>
 __global__ void __launch_bounds__(256) k_prep(PrepTask a, PrepTask b, int64_t blocks_a) {
-  __shared__ RowsLds lds;
-  const int64_t blk = blockIdx.x;
-  if (blk < blocks_a)
-    prep_task<CPLX, false, B8>(a, blk, lds);
+  __shared__ int red[kPrepRows * 17 + kPrepRows];
+  const uint32_t blk = blockIdx.x, na = (uint32_t)blocks_a;
+  if (blk < na)
+    prep_task<CPLX, false, B8>(a, blk, red);
   else
-    prep_task<CPLX, true, B8>(b, blk - blocks_a, lds);
+    prep_task<CPLX, true, B8>(b, blk - na, red);
 }
 
 template <bool CPLX, bool SIDEB>
@@ -773,12 +815,13 @@ hipError_t launch_split_batched(const SplitTask *tasks, const int64_t *start, in
 
 namespace {
 int64_t prep_task_blocks(const PrepTask &t) {
-  return t.nrb * ((t.cplx && t.side_b) ? 16 : 32) / kRowsBlock;
+  return t.nrb * ((t.cplx && t.side_b) ? 16 : 32) / kPrepRows * (t.nkb / 2);
 }
 }  // namespace
 
 bool prep_fits(const PrepTask &a, const PrepTask &b) {
-  return a.nkb * 32 <= kPrepK && prep_task_blocks(a) + prep_task_blocks(b) <= kMaxBlocks;
+  const int64_t kpad = a.nkb * 32, blocks = prep_task_blocks(a) + prep_task_blocks(b);
+  return kpad <= 256 ? blocks <= kMaxBlocks : kpad <= 512 && blocks <= 1024;
 }
 
 hipError_t launch_prep(const PrepTask &a, const PrepTask &b, hipStream_t st, bool b8) {

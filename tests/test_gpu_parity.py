@@ -178,12 +178,14 @@ def test_gemm_bit_exact(kind, ta, tb, s):
     assert bits_equal(got, ref), mismatch_report(got, ref)
 
 
-# Up to 256 packed entries one kernel scans and splits 16 rows per block, beyond
-# that three do: one entry, one pass and one past it, in every storage order,
-# with Inf and NaN, subnormal and zero rows, for both slice kinds and every way
-# the slices are emitted (up to 8 or 9 in one word, more by digits).
+# Short contractions are scanned and split by one kernel, beyond that by three:
+# one entry, the last of 256 and of 512 packed ones (few blocks) and one past
+# them, in every storage order, with Inf and NaN, subnormal and zero rows, for
+# both slice kinds and every way the slices are emitted (up to 8 or 9 in one
+# word, more by digits).
 @pytest.mark.parametrize("split,s", [("t7", 1), ("t7", 8), ("t7", 9), ("t7", 12), ("b8", 3), ("b8", 8)])
 @pytest.mark.parametrize("kind,m,n,k", [("d", 16, 17, 1), ("d", 33, 15, 256), ("d", 33, 15, 257),
+                                        ("d", 40, 70, 512), ("d", 20, 18, 513),
                                         ("z", 17, 33, 128), ("z", 17, 33, 129), ("z", 1, 1, 65)])
 def test_short_contractions_bit_exact(split, s, kind, m, n, k):
     from oracle import ozaki_b8
