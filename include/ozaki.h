@@ -319,8 +319,8 @@ int ozaki_batched_cache_clear(void);
  * ozaki_zgemm and ozaki_debug_diagonals look their shape up there (default 0).
  * The environment variable OZAKI_GEMM_CONFIG=<id> forces one id for every call;
  * OZAKI_TUNE_CACHE=<file> loads a saved table before the first lookup.
- * The batched path uses id 13 (128 x 128 tiles up to 6 slices, else 128 x 64)
- * unless OZAKI_BATCHED_CONFIG=<id> is set.
+ * The batched path chooses the shape of each slice count's tiles by its
+ * problems' sizes unless OZAKI_BATCHED_CONFIG=<id> is set.
  *
  * ozaki_autotune: times the fused GEMM kernel of every id on an m x n x k
  *   product with `slices` slices on the library's stream: packed operands of

@@ -791,6 +791,7 @@ struct ScaleOp {
 
 struct GroupDesc {
   int S;
+  int tune_id;  // tile configuration
   int64_t ntiles;
   size_t off_tile_prob, off_tile_local;
   bool chunked;
@@ -808,7 +809,6 @@ struct BatchedPlan {
   std::vector<GroupDesc> groups;
   std::vector<ScaleOp> scales;
   std::vector<int> used;  // slices used per problem
-  int tune_id = 0;        // tile configuration of the grouped GEMM
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -870,7 +870,7 @@ int enqueue_plan(const BatchedPlan &pl, hipStream_t st, bool capturing) {
     a.kb_chunk = kb_chunk_for(gd.S);
     a.chunked = gd.chunked ? 1 : 0;
     a.max_groups = g.grid_limit;
-    if ((rc = hip_rc(launch_ozgemm_grouped(gd.S, pl.tune_id, a, g.dev[pl.dev].num_cu, st))))
+    if ((rc = hip_rc(launch_ozgemm_grouped(gd.S, gd.tune_id, a, g.dev[pl.dev].num_cu, st))))
       return rc;
   }
   phase_end(mk, st);
@@ -882,18 +882,16 @@ int enqueue_plan(const BatchedPlan &pl, hipStream_t st, bool capturing) {
 }
 
 // Builds (or finds) the plan of a validated batched call.
-// Tile configuration of the grouped GEMM of batched calls: OZAKI_BATCHED_CONFIG
-// (a tuning id) or the default 13: 128 x 128 tiles up to 6 slices, then 128 x 64,
-// along the columns. 512 problems of sides 32..1024, GEMM at s = 5, 6, 7, 8, 9:
-// 631, 779, 965, 1125, 1362 us, with 64 x 64 tiles 667, 798, 1116, 1270, 1424.
-int batched_tune_id() {
+// Tile configuration of one grouped GEMM of a batched call: OZAKI_BATCHED_CONFIG
+// (a tuning id), or chosen by its problems' sizes.
+int batched_tune_id(int S, const std::vector<GemmSize> &sizes, int num_cu) {
   static int id = -2;
   if (id == -2) {
     const char *e = getenv("OZAKI_BATCHED_CONFIG");
     id = (e != nullptr && *e) ? atoi(e) : -1;
     if (id >= gemm_num_configs()) id = -1;
   }
-  return id >= 0 ? id : 13;
+  return id >= 0 ? id : gemm_choose_grouped(S, sizes, num_cu);
 }
 
 // Lays out one batched plan: problem descriptors, scan and split task tables,
@@ -915,7 +913,6 @@ int build_plan(const char *transa, const char *transb, const int64_t *m, const i
   const bool ext = ext_codeA != nullptr && ext_codeB != nullptr;
   std::vector<int64_t> prob_b;
   pl->used.assign((size_t)batch, 0);
-  pl->tune_id = batched_tune_id();
   std::vector<GemmProblem> probs;
   std::vector<ScanTask> scans;
   std::vector<SplitTask> splits;
@@ -963,16 +960,23 @@ int build_plan(const char *transa, const char *transb, const int64_t *m, const i
   const size_t np = probs.size();
 
   // tile tables, one group per distinct slice count, longest contraction first
+  std::map<int, std::vector<int>> by_slices;
+  for (size_t i = 0; i < np; ++i) by_slices[prob_S[i]].push_back((int)i);
   std::map<int, std::vector<std::pair<int, int>>> tiles;  // S -> (problem, local tile)
-  for (size_t i = 0; i < np; ++i) {
-    const int64_t nt = gemm_tiles(prob_S[i], pl->tune_id, plans[i].m, plans[i].nprime);
-    for (int64_t t = 0; t < nt; ++t) tiles[prob_S[i]].push_back({(int)i, (int)t});
-  }
-  for (auto &kv : tiles)
+  std::map<int, int> tune_id;
+  for (auto &kv : by_slices) {
     std::stable_sort(kv.second.begin(), kv.second.end(),
-                     [&](const std::pair<int, int> &x, const std::pair<int, int> &y) {
-                       return plans[x.first].nkb > plans[y.first].nkb;
-                     });
+                     [&](int x, int y) { return plans[x].nkb > plans[y].nkb; });
+    std::vector<GemmSize> sizes;
+    for (const int i : kv.second) sizes.push_back({plans[i].m, plans[i].nprime, plans[i].nkb});
+    const int id = batched_tune_id(kv.first, sizes, num_cu);
+    tune_id[kv.first] = id;
+    auto &tt = tiles[kv.first];
+    for (const int i : kv.second) {
+      const int64_t nt = gemm_tiles(kv.first, id, plans[i].m, plans[i].nprime);
+      for (int64_t t = 0; t < nt; ++t) tt.push_back({i, (int)t});
+    }
+  }
 
   // device layout
   size_t off = 0;
@@ -991,6 +995,7 @@ int build_plan(const char *transa, const char *transb, const int64_t *m, const i
   for (auto &kv : tiles) {
     GroupDesc gd{};
     gd.S = kv.first;
+    gd.tune_id = tune_id[kv.first];
     gd.ntiles = (int64_t)kv.second.size();
     gd.off_tile_prob = take(kv.second.size() * sizeof(int));
     gd.off_tile_local = take(kv.second.size() * sizeof(int));

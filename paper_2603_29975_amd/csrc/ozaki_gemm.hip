@@ -560,37 +560,45 @@ int64_t gemm_tiles(int S, int id, int64_t m, int64_t nprime) {
   return ((nprime + BJ - 1) / BJ) * ((m + BI - 1) / BI);
 }
 
+namespace {
+// Estimated time in us of one tile over `kb` contraction blocks of 64. Per block a
+// workgroup takes the larger of its share of the MFMA rate (`rate` times that of
+// back-to-back MFMAs, two 64 x 64 workgroups of a CU in turn if `full`) and the
+// latency of one alone.
+constexpr int shape_groups(Shape s, int S) { return s == kSmall && S <= 6 ? 2 : 1; }  // per CU
+double tile_time(Shape s, int S, int64_t kb, bool full) {
+  const double mfma = S * (S + 1) / 2 * 16 / 2400.0;  // one 16 x 16 x 64 block, on each SIMD
+  const double alone = shape_bj(s) * shape_bi(s) / 1024 * mfma;
+  const int groups = shape_groups(s, S);
+  const double rate = s == kBig ? 1.41 : s == kTall ? 1.44 : groups == 2 ? 1.89 : 1.72;
+  return 1.7 + kb * std::max((full ? groups : 1) * rate * alone, 1.19 * alone + 0.26);
+}
+constexpr bool shape_takes(Shape s, int S) { return !(s == kBig && S > 6) && !(s == kTall && S > 10); }
+}  // namespace
+
 GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb_chunk, int num_cu,
                        size_t parts_bytes, size_t *need) {
-  // Estimated time in us, the least over tile shapes and numbers of parts. Per
-  // contraction block of 64 a workgroup takes the larger of its share of the
-  // MFMA rate (`rate` times that of back-to-back MFMAs, two 64 x 64 workgroups of
-  // a CU in turn) and the latency of one alone. The parts' sums are written and
-  // read once, by 64 x 64 tiles only (128 x 64 ones were never faster). Fitted to
-  // 224 products of sides 16 .. 8192 at S = 3 .. 11 in up to 70 ways each: 1.6%
-  // slower on average than the fastest way of each. Before, 128 x 64 tiles for
-  // all: z 64 x 64 x 4096 S = 7 246 us, now 21; z 256 x 256 x 8192 475, now 70;
-  // z 517 x 389 x 1031 72, now 41; z 1500 x 700 x 300 57, now 50.
-  const double mfma = S * (S + 1) / 2 * 16 / 2400.0;  // one 16 x 16 x 64 block, on each SIMD
+  // The least estimate over tile shapes and numbers of parts. The parts' sums are
+  // written and read once, by 64 x 64 tiles only (128 x 64 ones were never
+  // faster). Fitted to 224 products of sides 16 .. 8192 at S = 3 .. 11 in up to
+  // 70 ways each: 1.6% slower on average than the fastest way of each. Before, 128
+  // x 64 tiles for all: z 64 x 64 x 4096 S = 7 246 us, now 21; z 256 x 256 x 8192
+  // 475, now 70; z 517 x 389 x 1031 72, now 41; z 1500 x 700 x 300 57, now 50.
   const int64_t kb = nkb / 2, chunk = std::max<int64_t>(kb_chunk / 2, 1);
   GemmChoice best{0, 1, kb};
   double best_t = 1e300;
   *need = 0;
   for (const Shape s : {kTall, kBig, kSmall}) {
-    if ((s == kBig && S > 6) || (s == kTall && S > 10)) continue;
+    if (!shape_takes(s, S)) continue;
     const int64_t area = (int64_t)shape_bj(s) * shape_bi(s);
     const int64_t tiles = ((nprime + shape_bj(s) - 1) / shape_bj(s)) * ((m + shape_bi(s) - 1) / shape_bi(s));
-    const bool two = s == kSmall && S <= 6;  // workgroups per CU
-    const double rate = s == kBig ? 1.41 : s == kTall ? 1.44 : two ? 1.89 : 1.72;
-    const double alone = area / 1024 * mfma;
     for (int64_t ks = 1; ks <= (s == kSmall ? 64 : 1); ++ks) {
       const int64_t part = (kb + ks - 1) / ks, items = tiles * ks;
       const size_t bytes = ks > 1 ? (size_t)items * area * S * sizeof(int32_t) : 0;
       if (ks > 1 && (part < 2 || items > 4 * num_cu)) break;
       if (ks > 1 && ((ks - 1) * part >= kb || part > chunk || bytes > parts_bytes)) continue;
-      const int64_t slots = num_cu * (two ? 2 : 1), rounds = (items + slots - 1) / slots;
-      const double turn = two && items > num_cu ? 2 * rate : rate;
-      double t = rounds * (1.7 + part * std::max(turn * alone, 1.19 * alone + 0.26));
+      const int64_t slots = num_cu * shape_groups(s, S), rounds = (items + slots - 1) / slots;
+      double t = rounds * tile_time(s, S, part, items > num_cu);
       if (ks > 1) t += 2.1 + 0.38e-6 * bytes + 0.13 * ks;
       if (t < best_t) {
         best_t = t;
@@ -598,6 +606,32 @@ GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb
         best = GemmChoice{s == kBig ? 27 : s == kTall ? 21 : 8, (int)ks, part};
         *need = bytes;
       }
+    }
+  }
+  return best;
+}
+
+int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int num_cu) {
+  // The tiles of the first CU, the longest of each round (the table is sorted by the
+  // contraction), with the estimate above; two workgroups of a CU take their tiles
+  // in turn. Against 128 x 128 (S <= 6) or 128 x 64 tiles for every batch (z, sides
+  // 32 .. 1024): 9 problems S = 8 47 / 77 us, 23 S = 7 47 / 74, 12 S = 6 37 / 89.
+  int best = 0;
+  double best_t = 1e300;
+  for (const Shape s : {kBig, kTall, kSmall}) {
+    // (128 x 64 tiles were never the fastest while 128 x 128 ones are there)
+    if (!shape_takes(s, S) || (s == kTall && shape_takes(kBig, S))) continue;
+    double t = 0.0;
+    int64_t done = 0, next = 0;
+    for (const GemmSize &p : probs) {
+      done += ((p.nprime + shape_bj(s) - 1) / shape_bj(s)) * ((p.m + shape_bi(s) - 1) / shape_bi(s));
+      const int64_t mine = done > next ? (done - next + num_cu - 1) / num_cu : 0;
+      t += mine * tile_time(s, S, p.nkb / 2, false);
+      next += mine * num_cu;
+    }
+    if (t < best_t) {
+      best_t = t;
+      best = s == kBig ? 13 : s == kTall ? 1 : 8;
     }
   }
   return best;

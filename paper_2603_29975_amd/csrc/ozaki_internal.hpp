@@ -2,6 +2,7 @@
 // kernel files of libozaki. Not part of the public C ABI.
 #pragma once
 
+#include <vector>
 #include "ozaki_common.hpp"
 
 namespace oz {
@@ -132,6 +133,11 @@ struct GemmChoice {
 };
 GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb_chunk, int num_cu,
                        size_t parts_bytes, size_t *need);
+// The tile shape of a grouped GEMM: its problems' sizes, longest contraction first.
+struct GemmSize {
+  int64_t m, nprime, nkb;
+};
+int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int num_cu);
 // Launch a grouped GEMM over the tile table in `a` (every problem has S slices).
 hipError_t launch_ozgemm_grouped(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st);
 

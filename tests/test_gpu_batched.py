@@ -105,6 +105,22 @@ def test_batched_bit_exact_mixed_sizes_trans_and_slices():
         assert bits_equal(got[b], ref), f"problem {b}\n" + mismatch_report(got[b], ref)
 
 
+# Enough equal problems for each tile shape of the grouped GEMM: 128 x 128 tiles
+# at 6 slices, 128 x 64 at 7 and 10, 64 x 64 for one problem and beyond 10.
+@pytest.mark.parametrize("s,count,n", [(6, 24, 500), (7, 24, 500), (10, 24, 500), (11, 24, 500), (6, 1, 100)])
+def test_batched_tile_shapes_bit_exact(s, count, n):
+    ms = ns = np.full(2, n)
+    probs, _ = batched_problems(2, 30 + s, max_spread=12.0, sizes=(ms, ns, np.full(2, 70)))
+    probs = [probs[b % 2] for b in range(count)]
+    C0s = [np.full((n, n), np.nan, dtype=np.complex128)] * count
+    bt = Batch(probs, [("N", "N")] * count, [1.0] * count, [0.0] * count, C0s, [s] * count)
+    _say("batched tile shapes", s, count, n)
+    got = bt.run()
+    refs = [bt.reference(b) for b in range(min(count, 2))]
+    for b in range(count):
+        assert bits_equal(got[b], refs[b % 2]), f"problem {b}\n" + mismatch_report(got[b], refs[b % 2])
+
+
 def test_batched_graph_replays_match_eager():
     bt = _small_batch(seed=12, count=16)
     refs = [bt.reference(b) for b in range(len(bt.probs))]
