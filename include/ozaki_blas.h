@@ -47,7 +47,7 @@ void zgemm_(const char *transa, const char *transb, const int *m, const int *n, 
  * Ozaki-II; both 0 returns to the environment variables. Returns 0, or -1 / -2
  * for a slice / moduli count out of range. */
 int ozaki_blas_config(int slices, int moduli);
-/* Frees the interposer's device staging buffers. */
+/* Frees the interposer's device and pinned staging buffers and copy streams. */
 int ozaki_blas_release(void);
 
 #ifdef __cplusplus

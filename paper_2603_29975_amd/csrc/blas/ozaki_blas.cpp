@@ -4,10 +4,14 @@
 // HBM around each call. See include/ozaki_blas.h for the contract.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
 #include <cctype>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
+#include <thread>
 
 #include "../../../include/ozaki_blas.h"
 
@@ -18,6 +22,7 @@ struct Staging {
   size_t cap[3] = {0, 0, 0};
 };
 Staging g_stage;
+std::mutex g_mutex;  // one call at a time: the buffers, lanes and libozaki's state are shared
 int g_slices = 0, g_moduli = 0;
 
 char up(char c) { return (char)std::toupper((unsigned char)c); }
@@ -45,25 +50,169 @@ void *stage(int which, size_t bytes, const char *routine) {
   return g_stage.buf[which];
 }
 
+// ---------------------------------------------------------------- copies
+// A host operand is pageable memory. hipMemcpy moves it through the runtime's own
+// pinned buffers on one thread, 23 GB/s on a link that does more than twice that,
+// so a large operand goes through pinned buffers here: several threads, each with
+// a stream and two buffers, take the next chunk in turn and copy it while their
+// last one is on the link. Threads live for one copy only; buffers and streams are
+// kept until ozaki_blas_release. Whole ZGEMM calls, 7 slices, here / hipMemcpy:
+// 2048^3 4.9 / 9.1 ms, 1000^3 1.40 / 2.02, 730^3 (8.5 MB operands) 0.89 / 1.10,
+// but 600^3 (5.8 MB) 0.75 / 0.77 and 512^3 0.60 / 0.57. With 2, 8 and 12 lanes
+// 2048^3 took 5.3, 5.2 and 5.4 ms, with chunks of 1 and 4 MiB 5.1 and 5.2. A
+// pitched block of any size goes this way too (a small one on one lane): a pitched
+// copy of pageable memory goes row by row, 2000^3 with ld = 2001 57 ms, here 4.7.
+constexpr int kLanes = 4;
+constexpr size_t kChunk = (size_t)2 << 20;
+constexpr size_t kLaneBytes = (size_t)6 << 20;  // smaller operands: one hipMemcpy
+
+struct Lane {
+  hipStream_t st = nullptr;
+  char *pin[2] = {nullptr, nullptr};
+  hipEvent_t ev[2] = {nullptr, nullptr};
+};
+Lane g_lane[kLanes];
+int g_lane_dev = -1;  // device of the streams, -1: none
+
+int release_lanes() {
+  int rc = 0;
+  for (Lane &l : g_lane) {
+    for (int b = 0; b < 2; ++b) {
+      if (l.ev[b] != nullptr && hipEventDestroy(l.ev[b]) != hipSuccess) rc = OZAKI_ERR_HIP;
+      if (l.pin[b] != nullptr && hipHostFree(l.pin[b]) != hipSuccess) rc = OZAKI_ERR_HIP;
+    }
+    if (l.st != nullptr && hipStreamDestroy(l.st) != hipSuccess) rc = OZAKI_ERR_HIP;
+    l = Lane{};
+  }
+  g_lane_dev = -1;
+  return rc;
+}
+
+// The lanes on the current device; false if they cannot be had.
+bool lanes_ready() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (g_lane_dev == dev) return true;
+  (void)release_lanes();
+  for (int i = 0; i < kLanes; ++i) {
+    Lane &l = g_lane[i];
+    bool ok = hipStreamCreateWithFlags(&l.st, hipStreamNonBlocking) == hipSuccess;
+    for (int b = 0; b < 2 && ok; ++b)
+      ok = hipHostMalloc(reinterpret_cast<void **>(&l.pin[b]), kChunk, hipHostMallocDefault) == hipSuccess &&
+           hipEventCreateWithFlags(&l.ev[b], hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      (void)hipGetLastError();
+      (void)release_lanes();
+      return false;
+    }
+  }
+  g_lane_dev = dev;
+  return true;
+}
+
+struct Job {
+  char *dev;        // packed column-major block on the device
+  char *host;       // its first element in host memory
+  size_t col, ldb;  // bytes of a column and from one column to the next
+  size_t bytes;
+  bool up;
+  std::atomic<size_t> next{0};
+  std::atomic<int> err{0};
+};
+
+// Bytes [off, off + len) of the packed block from host memory to p, or back.
+void pack(const Job &j, size_t off, size_t len, char *p) {
+  while (len > 0) {
+    const size_t in = off % j.col, n = j.ldb == j.col ? len : std::min(len, j.col - in);
+    char *h = j.host + off / j.col * j.ldb + in;
+    std::memcpy(j.up ? p : h, j.up ? h : p, n);
+    off += n;
+    p += n;
+    len -= n;
+  }
+}
+
+void run_lane(Job &j, Lane &l) {
+  size_t off[2] = {0, 0}, len[2] = {0, 0};  // chunk on the link of either buffer
+  auto landed = [&](int b) {
+    if (len[b] == 0) return true;
+    const hipError_t e = hipEventSynchronize(l.ev[b]);
+    if (e == hipSuccess && !j.up) pack(j, off[b], len[b], l.pin[b]);
+    len[b] = 0;
+    return e == hipSuccess;
+  };
+  bool ok = true;
+  int b = 0;
+  for (; ok; b ^= 1) {
+    ok = landed(b);
+    const size_t o = j.next.fetch_add(kChunk);
+    if (!ok || j.err.load() != 0 || o >= j.bytes) break;
+    const size_t n = std::min(kChunk, j.bytes - o);
+    if (j.up) pack(j, o, n, l.pin[b]);
+    ok = hipMemcpyAsync(j.up ? j.dev + o : l.pin[b], j.up ? l.pin[b] : j.dev + o, n,
+                        j.up ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, l.st) == hipSuccess &&
+         hipEventRecord(l.ev[b], l.st) == hipSuccess;
+    off[b] = o;
+    len[b] = n;
+  }
+  // the other buffer's last chunk; nothing may stay on the link
+  ok = landed(b ^ 1) && ok;
+  if (hipStreamSynchronize(l.st) != hipSuccess) ok = false;
+  if (!ok) j.err.store(1);
+}
+
+bool lane_copy(Job &j) {
+  const int dev = g_lane_dev;
+  std::thread th[kLanes];
+  const int lanes = (int)std::min<size_t>(kLanes, (j.bytes + kChunk - 1) / kChunk);
+  for (int i = 1; i < lanes; ++i) {
+    try {
+      th[i] = std::thread([&j, dev, i] {
+        if (hipSetDevice(dev) == hipSuccess) run_lane(j, g_lane[i]);
+        else j.err.store(1);
+      });
+    } catch (...) {  // no more threads: the others take the chunks
+      break;
+    }
+  }
+  run_lane(j, g_lane[0]);
+  for (std::thread &t : th)
+    if (t.joinable()) t.join();
+  return j.err.load() == 0;
+}
+
 // Copy the rows x cols column-major block at host (leading dimension ld) into
-// a packed device buffer, or back: one linear copy when the columns are
-// contiguous (ld == rows), else a pitched copy of exactly the block (the rows
-// between `rows` and `ld` are neither read nor written).
+// a packed device buffer, or back. Exactly the block: the rows between `rows`
+// and `ld` are neither read nor written.
+bool copy_block(void *dev, void *host, int64_t rows, int64_t cols, int64_t ld, size_t esz, bool up) {
+  const size_t col = (size_t)rows * esz, ldb = (size_t)ld * esz, bytes = col * (size_t)cols;
+  const bool pitched = ld != rows && cols > 1;
+  if ((bytes >= kLaneBytes || pitched) && lanes_ready()) {
+    Job j;
+    j.dev = static_cast<char *>(dev);
+    j.host = static_cast<char *>(host);
+    j.col = col;
+    j.ldb = pitched ? ldb : col;
+    j.bytes = bytes;
+    j.up = up;
+    return lane_copy(j);
+  }
+  const hipMemcpyKind kind = up ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost;
+  void *dst = up ? dev : host, *src = up ? host : dev;
+  return (!pitched ? hipMemcpy(dst, src, bytes, kind)
+                   : hipMemcpy2D(dst, up ? col : ldb, src, up ? ldb : col, col, cols, kind)) == hipSuccess;
+}
 void to_device(void *dst, const void *src, int64_t rows, int64_t cols, int64_t ld, size_t esz,
                const char *routine) {
   if (rows == 0 || cols == 0) return;
-  const hipError_t e =
-      ld == rows ? hipMemcpy(dst, src, rows * cols * esz, hipMemcpyHostToDevice)
-                 : hipMemcpy2D(dst, rows * esz, src, ld * esz, rows * esz, cols, hipMemcpyHostToDevice);
-  if (e != hipSuccess) fail(routine, "copy to device", OZAKI_ERR_HIP);
+  if (!copy_block(dst, const_cast<void *>(src), rows, cols, ld, esz, true))
+    fail(routine, "copy to device", OZAKI_ERR_HIP);
 }
 void to_host(void *dst, const void *src, int64_t rows, int64_t cols, int64_t ld, size_t esz,
              const char *routine) {
   if (rows == 0 || cols == 0) return;
-  const hipError_t e =
-      ld == rows ? hipMemcpy(dst, src, rows * cols * esz, hipMemcpyDeviceToHost)
-                 : hipMemcpy2D(dst, ld * esz, src, rows * esz, rows * esz, cols, hipMemcpyDeviceToHost);
-  if (e != hipSuccess) fail(routine, "copy to host", OZAKI_ERR_HIP);
+  if (!copy_block(const_cast<void *>(src), dst, rows, cols, ld, esz, false))
+    fail(routine, "copy to host", OZAKI_ERR_HIP);
 }
 
 // Reference-BLAS argument checks; returns the number of the first illegal
@@ -97,6 +246,7 @@ void gemm(bool cplx, const char *routine, char ta, char tb, int m, int n, int k,
     return;
   }
   if (m == 0 || n == 0 || ((alpha_zero || k == 0) && beta_one)) return;
+  const std::lock_guard<std::mutex> lock(g_mutex);
   const size_t esz = sizeof(T);
   ta = up(ta);
   tb = up(tb);
@@ -160,7 +310,8 @@ int ozaki_blas_config(int slices, int moduli) {
 }
 
 int ozaki_blas_release(void) {
-  int rc = 0;
+  const std::lock_guard<std::mutex> lock(g_mutex);
+  int rc = release_lanes();
   for (int w = 0; w < 3; ++w) {
     if (g_stage.buf[w] != nullptr && hipFree(g_stage.buf[w]) != hipSuccess) rc = OZAKI_ERR_HIP;
     g_stage.buf[w] = nullptr;

@@ -81,3 +81,26 @@ def test_interposer_environment_and_beta_zero(monkeypatch):
     blas.zgemm_("N", "N", m, n, k, 1.0, np.asfortranarray(A), m, np.asfortranarray(B), k, 0.0, C, m)
     assert bits_equal(C, ozaki2.ozaki2_gemm("N", "N", A, B, 12))
     assert blas.ozaki_blas_release() == 0
+
+
+# Operands on both sides of 6 MiB, above which the copies are threaded in chunks of
+# 2 MiB: packed and padded leading dimensions, one long column, a last chunk of a
+# few bytes; the padding stays, and the buffers can be given back and had again.
+@pytest.mark.parametrize("kind,m,n,k,pad", [("z", 700, 640, 640, 0), ("z", 620, 800, 650, 3), ("d", 1000, 787, 999, 1),
+                                            ("z", 1, 3, 500000, 0), ("d", 900000, 1, 2, 5)])
+def test_large_operands_by_threads(kind, m, n, k, pad):
+    from paper_2603_29975_amd import blas
+    A, B = uniform_binade(m, n, k, seed=1230 + n, complex_=kind == "z")
+    C0 = np.random.default_rng(1231).standard_normal((m, n)).astype(A.dtype)
+    alpha, beta = (0.75 - 0.5j, 1.5 + 0.25j) if kind == "z" else (0.75, -1.5)
+    assert blas.ozaki_blas_config(2, 0) == 0
+    ref = ozaki.ozaki_gemm("N", "N", A, B, 2, alpha, beta, C0)
+    for _ in range(2):
+        Af, Bf, Cf = _fortran(A, m + pad), _fortran(B, k + pad), _fortran(C0, m + pad)
+        print("threaded copies", kind, (m, n, k), pad, flush=True)
+        fn = blas.zgemm_ if kind == "z" else blas.dgemm_
+        fn("N", "N", m, n, k, alpha, Af, m + pad, Bf, k + pad, beta, Cf, m + pad)
+        got = np.ascontiguousarray(Cf[:m])
+        assert bits_equal(got, ref), mismatch_report(got, ref)
+        assert np.all(Cf[m:] == 7.25) and np.all(Af[m:] == 7.25)
+        assert blas.ozaki_blas_release() == 0
