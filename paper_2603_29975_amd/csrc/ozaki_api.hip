@@ -891,7 +891,7 @@ int batched_tune_id(int S, const std::vector<GemmSize> &sizes, int num_cu) {
     id = (e != nullptr && *e) ? atoi(e) : -1;
     if (id >= gemm_num_configs()) id = -1;
   }
-  return id >= 0 ? id : gemm_choose_grouped(S, sizes, num_cu);
+  return id >= 0 ? id : gemm_choose_grouped(S, sizes, kb_chunk_for(S), num_cu);
 }
 
 // Lays out one batched plan: problem descriptors, scan and split task tables,

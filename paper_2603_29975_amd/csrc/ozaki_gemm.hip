@@ -478,11 +478,14 @@ hipError_t launch_cfg(const GemmArgs &a, int num_cu, hipStream_t st) {
 //   64 x 128: 8 waves, 4 x 2, each 16 x 64; S <= 8 (LDS)
 //   64 x 64: 4 waves of 16 x 64, two workgroups per CU, while two fit the LDS (S
 //     <= 6); else 8 waves, 4 x 2, each 16 x 32
+//   32 x 32: 4 waves, 2 x 2, each 16 x 16; 4 <= S (ring LDS plan), no chunks: four
+//     times the workgroups and a quarter of the chain per block of 64 x 64, for
+//     products that do not fill the chip
 // With 32 x 64 (B' halves in turn, S = 6) or 32 x 32 per wave the LDS reads were
 // fewer, but one needed a few registers too many and the other larger copies:
 // 4096^3 complex S = 6 5264 and 4207 us against 3627, 4096^3 real S = 7 1260
 // against 1230; 128 x 96 tiles 3776 and 1279.
-enum Shape { kBig, kTall, kWide, kSmall };
+enum Shape { kBig, kTall, kWide, kSmall, kTiny };
 
 // Tile configurations 0 .. 6 (the autotuner's candidates): 6 is 128 x 128, 1 is
 // 64 x 128, 4 and 5 are 64 x 64, the others 128 x 64; the shapes a slice count
@@ -492,16 +495,20 @@ enum Shape { kBig, kTall, kWide, kSmall };
 // tile order 2, ids 21 .. 27 with the XCD-aware order 3 (see tile_coords and
 // xcd_major).
 constexpr int kNumCfg = 7;
-constexpr int id_cfg(int id) { return id < 2 * kNumCfg ? id >> 1 : (id - 2 * kNumCfg) % kNumCfg; }
-constexpr int id_order(int id) { return id < 2 * kNumCfg ? (id & 1) : 2 + (id - 2 * kNumCfg) / kNumCfg; }
+constexpr int kTinyId = 4 * kNumCfg;  // beyond the autotuner's: 32 x 32, chosen by sizes only
+constexpr int id_cfg(int id) {
+  return id == kTinyId ? kNumCfg : id < 2 * kNumCfg ? id >> 1 : (id - 2 * kNumCfg) % kNumCfg;
+}
+constexpr int id_order(int id) { return id == kTinyId ? 0 : id < 2 * kNumCfg ? (id & 1) : 2 + (id - 2 * kNumCfg) / kNumCfg; }
 
 constexpr Shape shape_of(int S, int cfg) {
-  if (S >= 11 || cfg == 4 || cfg == 5) return kSmall;
+  if (cfg == kNumCfg && S >= 4) return kTiny;
+  if (S >= 11 || cfg == 4 || cfg == 5 || cfg == kNumCfg) return kSmall;
   if (cfg == 6 && S <= 6) return kBig;
   return cfg == 1 && S <= 8 ? kWide : kTall;
 }
-constexpr int shape_bj(Shape s) { return s == kBig || s == kTall ? 128 : 64; }
-constexpr int shape_bi(Shape s) { return s == kBig || s == kWide ? 128 : 64; }
+constexpr int shape_bj(Shape s) { return s == kTiny ? 32 : s == kBig || s == kTall ? 128 : 64; }
+constexpr int shape_bi(Shape s) { return s == kTiny ? 32 : s == kBig || s == kWide ? 128 : 64; }
 
 constexpr bool ring_fits(int bytes, int groups) { return bytes * groups <= 160 * 1024; }
 
@@ -519,6 +526,9 @@ hipError_t launch_shape(Shape shape, const GemmArgs &a, int num_cu, hipStream_t 
   } else if (shape == kWide) {
     if constexpr (S <= 8 && all)
       return launch_cfg<S, 4, 2, 4, 2, ring_fits(Cfg<S, 4, 2, 4>::RingBytes, 1), LA, RAW, MODE>(a, num_cu, st);
+  } else if (shape == kTiny) {
+    if constexpr (S >= 4 && !RAW && MODE != kChunked)
+      return launch_cfg<S, 2, 2, 1, 1, true, LA, RAW, MODE>(a, num_cu, st);
   } else {
     if constexpr (S <= 6)
       return launch_cfg<S, 4, 1, 4, 2, ring_fits(Cfg<S, 4, 1, 4>::RingBytes, 2), LA, RAW, MODE>(a, num_cu, st);
@@ -569,41 +579,50 @@ constexpr int shape_groups(Shape s, int S) { return s == kSmall && S <= 6 ? 2 : 
 double tile_time(Shape s, int S, int64_t kb, bool full) {
   const double mfma = S * (S + 1) / 2 * 16 / 2400.0;  // one 16 x 16 x 64 block, on each SIMD
   const double alone = shape_bj(s) * shape_bi(s) / 1024 * mfma;
+  if (s == kTiny) return 2.4 + kb * std::max(2.13 * alone, 1.19 * alone + 0.38);
   const int groups = shape_groups(s, S);
   const double rate = s == kBig ? 1.41 : s == kTall ? 1.44 : groups == 2 ? 1.89 : 1.72;
   return 1.7 + kb * std::max((full ? groups : 1) * rate * alone, 1.19 * alone + 0.26);
 }
-constexpr bool shape_takes(Shape s, int S) { return !(s == kBig && S > 6) && !(s == kTall && S > 10); }
+constexpr bool shape_takes(Shape s, int S) {
+  return s == kBig ? S <= 6 : s == kTall ? S <= 10 : s == kTiny ? S >= 4 : true;
+}
+int64_t shape_tiles(Shape s, int64_t m, int64_t nprime) {
+  return ((nprime + shape_bj(s) - 1) / shape_bj(s)) * ((m + shape_bi(s) - 1) / shape_bi(s));
+}
 }  // namespace
 
 GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb_chunk, int num_cu,
                        size_t parts_bytes, size_t *need) {
   // The least estimate over tile shapes and numbers of parts. The parts' sums are
-  // written and read once, by 64 x 64 tiles only (128 x 64 ones were never
-  // faster). Fitted to 224 products of sides 16 .. 8192 at S = 3 .. 11 in up to
-  // 70 ways each: 1.6% slower on average than the fastest way of each. Before, 128
-  // x 64 tiles for all: z 64 x 64 x 4096 S = 7 246 us, now 21; z 256 x 256 x 8192
-  // 475, now 70; z 517 x 389 x 1031 72, now 41; z 1500 x 700 x 300 57, now 50.
+  // written and read once, by 64 x 64 and 32 x 32 tiles only (128 x 64 ones were
+  // never faster). Fitted to 260 products of sides 16 .. 8192 at S = 3 .. 12 in up
+  // to 70 ways each: about 1.5% slower on average than the fastest way of each.
+  // Before, 128 x 64 tiles for all: z 64 x 64 x 4096 S = 7 246 us, now 17; z 256 x
+  // 256 x 8192 475, now 70; z 517 x 389 x 1031 72, now 41; z 1500 x 700 x 300 57,
+  // now 50. 64 x 64 / 32 x 32 tiles: d 256^3 12.2 / 8.8, z 256^3 15.6 / 10.8, d
+  // 512^3 16.7 / 11.3, but z 700 x 700 x 128 14.1 / 20.9.
   const int64_t kb = nkb / 2, chunk = std::max<int64_t>(kb_chunk / 2, 1);
   GemmChoice best{0, 1, kb};
   double best_t = 1e300;
   *need = 0;
-  for (const Shape s : {kTall, kBig, kSmall}) {
+  for (const Shape s : {kTall, kBig, kSmall, kTiny}) {
     if (!shape_takes(s, S)) continue;
-    const int64_t area = (int64_t)shape_bj(s) * shape_bi(s);
-    const int64_t tiles = ((nprime + shape_bj(s) - 1) / shape_bj(s)) * ((m + shape_bi(s) - 1) / shape_bi(s));
-    for (int64_t ks = 1; ks <= (s == kSmall ? 64 : 1); ++ks) {
+    const int64_t area = (int64_t)shape_bj(s) * shape_bi(s), tiles = shape_tiles(s, m, nprime);
+    for (int64_t ks = 1; ks <= (s == kSmall || s == kTiny ? 64 : 1); ++ks) {
       const int64_t part = (kb + ks - 1) / ks, items = tiles * ks;
       const size_t bytes = ks > 1 ? (size_t)items * area * S * sizeof(int32_t) : 0;
       if (ks > 1 && (part < 2 || items > 4 * num_cu)) break;
-      if (ks > 1 && ((ks - 1) * part >= kb || part > chunk || bytes > parts_bytes)) continue;
+      if (ks > 1 && ((ks - 1) * part >= kb || bytes > parts_bytes)) continue;
+      if ((ks > 1 || s == kTiny) && part > chunk) continue;  // (32 x 32 tiles carry no chunks)
       const int64_t slots = num_cu * shape_groups(s, S), rounds = (items + slots - 1) / slots;
       double t = rounds * tile_time(s, S, part, items > num_cu);
+      if (s != kTiny) t += 1.3;
       if (ks > 1) t += 2.1 + 0.38e-6 * bytes + 0.13 * ks;
       if (t < best_t) {
         best_t = t;
         // 128-row tiles in XCD-aware groups, the others down the rows
-        best = GemmChoice{s == kBig ? 27 : s == kTall ? 21 : 8, (int)ks, part};
+        best = GemmChoice{s == kBig ? 27 : s == kTall ? 21 : s == kSmall ? 8 : kTinyId, (int)ks, part};
         *need = bytes;
       }
     }
@@ -611,27 +630,28 @@ GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb
   return best;
 }
 
-int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int num_cu) {
+int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int64_t kb_chunk, int num_cu) {
   // The tiles of the first CU, the longest of each round (the table is sorted by the
   // contraction), with the estimate above; two workgroups of a CU take their tiles
   // in turn. Against 128 x 128 (S <= 6) or 128 x 64 tiles for every batch (z, sides
   // 32 .. 1024): 9 problems S = 8 47 / 77 us, 23 S = 7 47 / 74, 12 S = 6 37 / 89.
   int best = 0;
   double best_t = 1e300;
-  for (const Shape s : {kBig, kTall, kSmall}) {
+  for (const Shape s : {kBig, kTall, kSmall, kTiny}) {
     // (128 x 64 tiles were never the fastest while 128 x 128 ones are there)
     if (!shape_takes(s, S) || (s == kTall && shape_takes(kBig, S))) continue;
-    double t = 0.0;
+    if (s == kTiny && !probs.empty() && probs[0].nkb > kb_chunk) continue;  // carries no chunks
+    double t = s == kTiny ? 0.0 : 1.3;
     int64_t done = 0, next = 0;
     for (const GemmSize &p : probs) {
-      done += ((p.nprime + shape_bj(s) - 1) / shape_bj(s)) * ((p.m + shape_bi(s) - 1) / shape_bi(s));
+      done += shape_tiles(s, p.m, p.nprime);
       const int64_t mine = done > next ? (done - next + num_cu - 1) / num_cu : 0;
       t += mine * tile_time(s, S, p.nkb / 2, false);
       next += mine * num_cu;
     }
     if (t < best_t) {
       best_t = t;
-      best = s == kBig ? 13 : s == kTall ? 1 : 8;
+      best = s == kBig ? 13 : s == kTall ? 1 : s == kSmall ? 8 : kTinyId;
     }
   }
   return best;

@@ -137,7 +137,7 @@ GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb
 struct GemmSize {
   int64_t m, nprime, nkb;
 };
-int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int num_cu);
+int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int64_t kb_chunk, int num_cu);
 // Launch a grouped GEMM over the tile table in `a` (every problem has S slices).
 hipError_t launch_ozgemm_grouped(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st);
 

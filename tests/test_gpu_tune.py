@@ -71,8 +71,8 @@ def test_every_tuning_id_chunked_contraction(kind, s, k):
         assert bits_equal(got, ref), f"id {tid}\n" + mismatch_report(got, ref)
 
 
-# Every slice count of both kinds in each tile shape (ids 0: 128 x 64, 2: 64 x
-# 128, 8: 64 x 64, 12: 128 x 128), at the edges of tiles and of 64-entry
+# Every slice count of both kinds in each tile shape (ids 0: by sizes, here mostly
+# 32 x 32, 2: 64 x 128, 4: 128 x 64, 8: 64 x 64, 12: 128 x 128), at the edges of tiles and of 64-entry
 # contraction blocks: one entry, one tile, one row, column or block past it.
 @pytest.mark.parametrize("split", ["t7", "b8"])
 @pytest.mark.parametrize("kind,m,n,k", [("d", 1, 1, 1), ("d", 64, 128, 64), ("d", 65, 129, 65),
@@ -85,7 +85,7 @@ def test_every_slice_count_at_tile_edges(split, kind, m, n, k):
     try:
         for s in range(1, (8 if split == "b8" else 12) + 1):
             ref = model("N", "N", A, B, s)
-            for tid in (0, 2, 8, 12):
+            for tid in (0, 2, 4, 8, 12):
                 assert oz.ozaki_tune_set(kind, m, n, k, s, tid) == 0
                 _say("tile edges", split, kind, (m, n, k), s, "tuning id", tid)
                 got = _gemm(kind, A, B, s)
@@ -96,7 +96,7 @@ def test_every_slice_count_at_tile_edges(split, kind, m, n, k):
 
 
 # Few tiles and a long contraction: id 0 sums it in parts by different workgroups
-# (64 x 64 tiles, last part shorter, contractions beyond one INT32 sum among
+# (64 x 64 or 32 x 32 tiles, last part shorter, contractions beyond one INT32 sum among
 # them). A workspace with no room for the parts takes the other tiles; the bits
 # are the oracle's either way, alpha, beta, Inf and NaN included.
 @pytest.mark.parametrize("split", ["t7", "b8"])
