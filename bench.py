@@ -462,8 +462,8 @@ def run_single(args):
     pairs = s if ozaki2 else s * (s + 1) // 2
     int8_ops = pairs * flops
     if ozaki2:
-        kernel = (f"fused INT8 modular products over {s} moduli + CRT rebuild + FP64 epilogue "
-                  "(k_oz2gemm); the residue kernels are timed in phases_ms")
+        kernel = (f"INT8 modular products over {s} moduli + CRT rebuild + FP64 epilogue "
+                  "(k_oz2mod, k_oz2rebuild); the residue kernels are timed in phases_ms")
         traffic = None
     else:
         kernel = ("fused INT8 slice-pair GEMM + FP64 recombination (k_ozgemm, tuning id "

@@ -9,13 +9,11 @@
 // Why two kernels: with the digits of all moduli in registers (ozaki2_gemm.hip)
 // a wave holds one or two 32 x 32 blocks, so every residue fragment read from
 // LDS feeds one or two MFMAs and the LDS bounds the kernel. Here a wave holds
-// only the INT32 sums of one modulus, eight blocks (128 x 64): a fragment feeds
-// 2.7 MFMAs, and the moduli are further independent work items, so small
-// products fill the chip too. The price is one byte written and read per output
-// entry and modulus. At 2048^3 complex, 14 moduli: products 486 us (1.98 POP/s)
-// and rebuild 57 us, where the one kernel took 897; the MFMAs alone, on operands
-// left in LDS, take 343 us at the clock the chip holds under them, the operand
-// copies cost 70 of the rest and the LDS reads 50.
+// only the INT32 sums of one modulus, 32 blocks of 16 x 16 (128 x 64), and the
+// moduli are further independent work items, so small products fill the chip
+// too. The price is one byte written and read per output entry and modulus. At
+// 2048^3 complex, 14 moduli, the whole call takes 570 us (626 with 32 x 32 x 32
+// MFMAs, whose products alone took 486), with the one kernel 1048.
 #include "ozaki2_crt.hpp"
 #include "ozaki_gemm_tile.hpp"
 
