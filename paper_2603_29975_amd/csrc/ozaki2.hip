@@ -125,21 +125,74 @@ __device__ __forceinline__ uint32_t neg_odd(uint32_t w) {
 // What bounds it is the arithmetic, about 8 operations per entry and modulus
 // (two dot products, conversion, quotient, remainder, packing; 13-bit pieces
 // with 24-bit products took 15), and the writes: 2048^3 complex, 14 moduli, A
-// 40 us and B 74 us (2.9 and 3.2 TB/s written), before 57 and 77. Rows and
-// entries beyond the operand give zero residues.
-template <bool CPLX, bool SIDEB, bool STAGED, bool BIG>
-__global__ void __launch_bounds__(256) k_residues(View v, const int *code, int n, int beta,
-                                                  int8_t *out, int64_t nrb, int64_t nkb,
-                                                  int64_t plane) {
+// 40 us and B 74 us (2.9 and 3.2 TB/s written), before 57 and 77; both operands
+// share a launch, which a small product gains most from (z 64^3, whole call, 21.5
+// us). Rows and entries beyond the operand give zero residues.
+struct ResSide {
+  View v;
+  int *code;
+  int8_t *out;
+  int64_t nrb;
+};
+
+// Codes of the block's 64 view rows into sc (and, from one block per row group,
+// into code): 16 threads per row, along the rows where those are contiguous.
+template <bool CPLX>
+__device__ __forceinline__ void scan_rows(const ResSide &s, int64_t bx, bool store, int *red, int *sc) {
+  const View &v = s.v;
+  const int tid = threadIdx.x;
+  const int sr = v.sl == 1 ? tid >> 4 : tid & 15, sl = v.sl == 1 ? tid & 15 : tid >> 4;
+  int c[4] = {0, 0, 0, 0};
+  for (int64_t l = sl; l < v.L; l += 32) {
+    int a[4][2];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int64_t r = bx * 64 + 16 * g + sr, ll = l + 16 * u < v.L ? l + 16 * u : l;
+        const int64_t off = r < v.R ? r * v.sr + ll * v.sl : 0;
+        if constexpr (CPLX) {
+          const double2 z = reinterpret_cast<const double2 *>(v.base)[off];
+          a[g][u] = max(expo_code(z.x), expo_code(z.y));
+        } else {
+          a[g][u] = expo_code(reinterpret_cast<const double *>(v.base)[off]);
+        }
+      }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) c[g] = max(c[g], max(a[g][0], a[g][1]));
+  }
+#pragma unroll
+  for (int g = 0; g < 4; ++g) red[(16 * g + sr) * 17 + sl] = c[g];
+  __syncthreads();
+  if (tid < 64) {
+    int m = 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) m = max(m, red[tid * 17 + u]);
+    sc[tid] = m;
+    if (store && bx * 64 + tid < v.R) s.code[bx * 64 + tid] = m;
+  }
+  __syncthreads();
+}
+
+template <bool CPLX, bool SIDEB, bool STAGED, bool BIG, bool SCAN>
+__device__ __forceinline__ void residues_block(const ResSide &s, int n, int beta, int64_t nkb,
+                                               int64_t bx, int64_t by, double *tile, int *red) {
   using T = SplitTile<CPLX, false>;
   using E = typename std::conditional<CPLX, double2, double>::type;
-  __shared__ __attribute__((aligned(16))) double tile[STAGED ? T::TR * T::PITCH : 2];
-  const int64_t bx = blockIdx.x, by = blockIdx.y;
+  const View &v = s.v;
+  int8_t *out = s.out;
+  const int64_t nrb = s.nrb, plane = nrb * nkb * kFragBytes;
   if constexpr (STAGED) load_split_tile<CPLX, false>(v, bx, by, tile);
   const int tid = threadIdx.x;
   const int64_t vr = bx * 64 + (tid & 63);
   const int64_t kk = (by * 4 + (tid >> 6)) * 16;
-  const int c = vr < v.R ? code[vr] : 0;
+  int c;
+  if constexpr (SCAN) {
+    scan_rows<CPLX>(s, bx, by == 0, red, red + 64 * 17);
+    c = vr < v.R ? red[64 * 17 + (tid & 63)] : 0;
+  } else {
+    c = vr < v.R ? s.code[vr] : 0;
+  }
   const bool live = vr < v.R && !code_bad(c);
   const int e = code_exp(c);
 
@@ -189,6 +242,31 @@ __global__ void __launch_bounds__(256) k_residues(View v, const int *code, int n
   }
 }
 
+// Both operands in one launch: blocks [0, na) take the first, `groups` row groups
+// each. SCAN: the blocks find their rows' exponents themselves (each row group's
+// blocks scan it again, out of the caches) instead of a launch before.
+template <bool CPLX, bool BIG, bool SCAN>
+__global__ void __launch_bounds__(256) k_residues(ResSide a, ResSide b, int64_t na, int n, int beta,
+                                                  int64_t nkb) {
+  using T = SplitTile<CPLX, false>;
+  __shared__ __attribute__((aligned(16))) double tile[T::TR * T::PITCH];
+  __shared__ int red[SCAN ? 64 * 18 : 1];
+  const uint32_t first = (uint32_t)na;
+  if (blockIdx.x < first) {
+    const uint32_t groups = (uint32_t)(a.nrb / 2), blk = blockIdx.x;
+    if (split_staged(a.v))
+      residues_block<CPLX, false, true, BIG, SCAN>(a, n, beta, nkb, blk % groups, blk / groups, tile, red);
+    else
+      residues_block<CPLX, false, false, BIG, SCAN>(a, n, beta, nkb, blk % groups, blk / groups, tile, red);
+  } else {
+    const uint32_t groups = (uint32_t)(CPLX ? b.nrb / 4 : b.nrb / 2), blk = blockIdx.x - first;
+    if (split_staged(b.v))
+      residues_block<CPLX, true, true, BIG, SCAN>(b, n, beta, nkb, blk % groups, blk / groups, tile, red);
+    else
+      residues_block<CPLX, true, false, BIG, SCAN>(b, n, beta, nkb, blk % groups, blk / groups, tile, red);
+  }
+}
+
 }  // namespace crt
 
 // ---------------------------------------------------------------- host side
@@ -220,35 +298,43 @@ int crt_beta(int n, int64_t kprime) {
   return b > 63 ? 63 : b;
 }
 
-hipError_t launch_residues(const View &v, bool cplx, bool side_b, const int *code, int n, int beta,
-                           int8_t *out, int64_t nrb, int64_t nkb, hipStream_t st) {
+hipError_t launch_residues(const View &va, int *ca, int8_t *oa, int64_t nrba, const View &vb, int *cb,
+                           int8_t *ob, int64_t nrbb, bool cplx, int n, int beta, int64_t nkb, bool scan,
+                           hipStream_t st) {
   // 64 contraction entries (two blocks) per workgroup; view rows up to the
   // padded X' rows (complex B: two X' rows per view row)
-  if (v.R <= 0 || nrb <= 0 || nrb % 4 != 0 || nkb <= 0 || nkb % 4 != 0) return hipErrorInvalidValue;
-  const int64_t view_rows = (cplx && side_b) ? nrb * 16 : nrb * 32;
-  if (view_rows < v.R) return hipErrorInvalidValue;
-  const int64_t plane = nrb * nkb * kFragBytes;
-  const dim3 grid((unsigned)(view_rows / 64), (unsigned)(nkb / 2));
-  const bool staged = split_staged(v);
-#define OZ_RES2(C, B, T, G)                                                                          \
-  hipLaunchKernelGGL((crt::k_residues<C, B, T, G>), grid, dim3(256), 0, st, v, code, n, beta, out, \
-                     nrb, nkb, plane)
-#define OZ_RES(C, B, T) \
-  do {                  \
-    if (beta > 62)      \
-      OZ_RES2(C, B, T, true);  \
-    else                       \
-      OZ_RES2(C, B, T, false); \
+  const int64_t rowsb = cplx ? nrbb * 16 : nrbb * 32;
+  if (va.R <= 0 || vb.R <= 0 || nrba <= 0 || nrbb <= 0 || nrba % 4 != 0 || nrbb % 4 != 0 || nkb <= 0 ||
+      nkb % 4 != 0 || nrba * 32 < va.R || rowsb < vb.R)
+    return hipErrorInvalidValue;
+  const int64_t na = nrba / 2 * (nkb / 2), nb = rowsb / 64 * (nkb / 2);
+  const crt::ResSide a{va, ca, oa, nrba}, b{vb, cb, ob, nrbb};
+  // one launch, or one per operand where both together are too many blocks
+  auto go = [&](int64_t n0, int64_t blocks, const crt::ResSide &x) {
+    const dim3 grid((unsigned)blocks);
+#define OZ_RES(C, G, S) \
+  hipLaunchKernelGGL((crt::k_residues<C, G, S>), grid, dim3(256), 0, st, x, b, n0, n, beta, nkb)
+#define OZ_RES2(C, G) \
+  do {                \
+    if (scan)         \
+      OZ_RES(C, G, true);  \
+    else                   \
+      OZ_RES(C, G, false); \
   } while (0)
-  if (cplx && side_b) {
-    if (staged) OZ_RES(true, true, true); else OZ_RES(true, true, false);
-  } else if (cplx) {
-    if (staged) OZ_RES(true, false, true); else OZ_RES(true, false, false);
-  } else {
-    if (staged) OZ_RES(false, false, true); else OZ_RES(false, false, false);
-  }
+    if (cplx) {
+      if (beta > 62) OZ_RES2(true, true); else OZ_RES2(true, false);
+    } else {
+      if (beta > 62) OZ_RES2(false, true); else OZ_RES2(false, false);
+    }
 #undef OZ_RES2
 #undef OZ_RES
+  };
+  if (na + nb <= kMaxBlocks) {
+    go(na, na + nb, a);
+  } else {
+    go(na, na, a);
+    go(0, nb, a);
+  }
   return hipGetLastError();
 }
 

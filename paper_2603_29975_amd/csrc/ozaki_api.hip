@@ -608,17 +608,23 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   const View vb = view_opB(B, transb, k, n, ldb, cplx);
   hipStream_t st = g.stream;
 
-  int mk = phase_begin(OZAKI_PHASE_SCAN, st);
-  if ((rc = hip_rc(launch_fill_i32(codeA, (int64_t)((p.off_codeB - p.off_codeA) / sizeof(int)) + n,
-                                   0, st))))
-    return rc;
-  if ((rc = hip_rc(launch_scan(va, codeA, vb, codeB, cplx, st)))) return rc;
-  phase_end(mk, st);
-
+  // Up to 128 packed contraction entries the residue kernel finds the exponents
+  // itself, without a fill and a scan before it. 14 moduli, whole call, with the scan
+  // inside / before: z 64^3 18.5 / 21.5 us, d 128^3 18.6 / 20.6, no gain at 256
+  // entries (d 256^3 21.7 / 21.5) and a loss at 512 (z 256^3 28.7 / 25.7).
+  const bool fused = p.nkb * 32 <= 128;
+  int mk;
+  if (!fused) {
+    mk = phase_begin(OZAKI_PHASE_SCAN, st);
+    if ((rc = hip_rc(launch_fill_i32(codeA, (int64_t)((p.off_codeB - p.off_codeA) / sizeof(int)) + n,
+                                     0, st))))
+      return rc;
+    if ((rc = hip_rc(launch_scan(va, codeA, vb, codeB, cplx, st)))) return rc;
+    phase_end(mk, st);
+  }
   mk = phase_begin(OZAKI_PHASE_SPLIT, st);
-  if ((rc = hip_rc(launch_residues(va, cplx, false, codeA, moduli, p.beta, RA, p.nrbQ, p.nkb, st))))
-    return rc;
-  if ((rc = hip_rc(launch_residues(vb, cplx, true, codeB, moduli, p.beta, RB, p.nrbP, p.nkb, st))))
+  if ((rc = hip_rc(launch_residues(va, codeA, RA, p.nrbQ, vb, codeB, RB, p.nrbP, cplx, moduli, p.beta,
+                                   p.nkb, fused, st))))
     return rc;
   phase_end(mk, st);
 

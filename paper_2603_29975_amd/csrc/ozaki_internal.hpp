@@ -9,6 +9,9 @@ namespace oz {
 
 // Exponent step: code[r] = max over row r of expo_code (code must hold zeros
 // on entry; launch_fill_i32 provides them).
+// Blocks of 256 threads in one launch (fewer than 2^32 threads along x).
+constexpr int64_t kMaxBlocks = (1 << 24) - 1;
+
 hipError_t launch_fill_i32(int *p, int64_t n, int value, hipStream_t st);
 // Pseudo-random digits in [-127, 127] (timing data of the autotuner).
 hipError_t launch_fill_digits(int8_t *p, int64_t n, uint64_t seed, hipStream_t st);
@@ -263,12 +266,14 @@ int crt_log2_floor(int n);
 // beta = min(63, floor((floor(log2 M) - 1 - ceil(log2 K')) / 2)); below 1
 // means too few moduli for the contraction length.
 int crt_beta(int n, int64_t kprime);
-// Residues of X' (rows of op(A), or of B' for side_b) into n planes in the
-// packed fragment layout of the slices (nrb 32-row blocks, nkb 32-entry
-// contraction blocks, nkb a multiple of 4; plane k at out + k nrb nkb KiB);
-// padded rows and contraction entries hold zero residues.
-hipError_t launch_residues(const View &v, bool cplx, bool side_b, const int *code, int n, int beta,
-                           int8_t *out, int64_t nrb, int64_t nkb, hipStream_t st);
+// Residues of A' and B' into n planes each in the packed fragment layout of the
+// slices (nrb 32-row blocks, nkb 32-entry contraction blocks, nkb a multiple of 4;
+// plane k at out + k nrb nkb KiB); padded rows and contraction entries hold zero
+// residues. scan: the rows' exponent codes are found too and stored, else they
+// are read.
+hipError_t launch_residues(const View &va, int *ca, int8_t *oa, int64_t nrba, const View &vb, int *cb,
+                           int8_t *ob, int64_t nrbb, bool cplx, int n, int beta, int64_t nkb, bool scan,
+                           hipStream_t st);
 // Fused Ozaki-II product: per output tile the n modular INT8 products, each
 // reduced at once to its Garner digit, then the rebuilt integer rounded to
 // FP64, scaled by 2^(e_i + f_j - 2 beta) and alpha/beta applied.

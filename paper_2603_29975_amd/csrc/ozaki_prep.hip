@@ -658,9 +658,6 @@ __global__ void __launch_bounds__(256) k_scale(int64_t m, int64_t n, double br, 
   }
 }
 
-// Blocks of 256 threads in one launch (fewer than 2^32 threads along x).
-constexpr int64_t kMaxBlocks = (1 << 24) - 1;
-
 inline unsigned grid1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace

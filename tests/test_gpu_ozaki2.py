@@ -214,3 +214,21 @@ def test_ozaki2_rounding_at_ties(nmod):
     got = _run("d", "N", "N", A, B, nmod)
     ref = ozaki2.ozaki2_gemm("N", "N", A, B, nmod)
     assert bits_equal(got, ref), mismatch_report(got, ref)
+
+
+# Up to 128 packed contraction entries the residue kernel scans its rows itself: one entry, the
+# limit and one past it, in every storage order, with Inf and NaN, for both digit forms (20 moduli
+# take the unsigned one)
+@pytest.mark.parametrize("nmod", [9, 20])
+@pytest.mark.parametrize("kind,m,n,k", [("d", 65, 17, 1), ("d", 33, 130, 128), ("d", 33, 130, 129),
+                                        ("z", 66, 31, 64), ("z", 66, 31, 65), ("z", 1, 1, 40)])
+def test_ozaki2_short_contractions(nmod, kind, m, n, k):
+    for ta, tb in (("N", "N"), ("T", "N"), ("N", "T"), ("C", "C")):
+        for bad in (False, True):
+            A, B = _operands(kind, m, n, k, seed=990 + k, nasty=m > 1)
+            if bad:
+                A[m // 2, k - 1], B[0, n // 2] = np.nan, -np.inf
+            _say("ozaki2 short", kind, (m, n, k), nmod, ta, tb, bad)
+            got = _run(kind, ta, tb, A, B, nmod)
+            ref = ozaki2.ozaki2_gemm("N", "N", A, B, nmod)
+            assert bits_equal(got, ref), mismatch_report(got, ref)
