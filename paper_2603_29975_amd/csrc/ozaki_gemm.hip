@@ -49,9 +49,9 @@
 //
 // INT32 range: a diagonal of S pairs over 64 * kb contraction entries is bounded
 // by S * 64 * kb * 127^2. Past that bound the contraction is cut into chunks
-// whose INT32 sums go to workgroup-private memory (as they are, for up to three
-// chunks, else added up in int64); the epilogue adds them in int64. At 16384^3
-// complex, S = 6, that is 25.8 GB of traffic, 2% of the time, where splitting
+// whose INT32 sums go to workgroup-private memory (as they are, for two chunks,
+// else added up in int64); the epilogue adds them in int64. At 16384^3
+// complex, S = 6, that is 52 GB of traffic, about 4% of the time, where splitting
 // each diagonal over two INT32 sets needed the smaller tile. The FP64 epilogue
 // converts every S_t exactly (|S_t| < 2^53) and adds them largest weight first,
 // one rounding per addition, then scales by 2^(e_i + f_j) and applies alpha/beta
@@ -75,7 +75,7 @@ typedef const __attribute__((address_space(4))) GemmArgs *ArgsPtr;
 typedef const __attribute__((address_space(4))) GemmProblem *ProblemPtr;
 typedef const __attribute__((address_space(4))) int *IntPtr;
 
-constexpr int kInt32Chunks = 3;  // up to so many chunks each keeps its own INT32 sums
+constexpr int kInt32Chunks = 2;  // up to so many chunks each keeps its own INT32 sums
 
 // f(0), ..., f(N - 1) with constant arguments.
 template <typename F, int... N>
@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
       // every wave is done reading LDS before the next chunk or tile refills it
       barrier_only();
 
-      if (CHUNKED && k0 + chunk < nkb_all) {
+      if (CHUNKED) {
         char *cb = carry_base();
         if (!wide) {
           cb += slots * kSlot;
@@ -352,16 +352,19 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
     const int64_t j0 = tj * C_::BJ + wj * 16 + 4 * (lane >> 4);
     unrolled(std::make_integer_sequence<int, IB>{}, [&](auto ibc) {
       constexpr int ib = decltype(ibc)::value;
-      // The block with its chunk sums: none, one or two INT32 ones, or int64.
+      // The block from the accumulators (K 0), or from its chunk sums: one or two INT32
+      // ones (1, 2) or int64 (3). The last chunk's go to memory like the others', which ends
+      // the accumulators' life there: kept for the epilogue they made the chunk loop
+      // spill 1096 bytes a lane (652 now; 16384^3 complex, S = 6, 1.8% slower).
       auto finish = [&](auto kind) {
         constexpr int K = decltype(kind)::value;
         auto total = [&](int t, int r) -> int64_t {
           const int w = (ib * S + t) * 4 + r;
-          int64_t v = acc[ib][t][r];
+          int64_t v = K == 0 ? acc[ib][t][r] : 0;
           if constexpr (K == 3)
-            v += __hip_atomic_load(carry_word<int64_t>(carry_base(), w, lane), __ATOMIC_RELAXED,
+            v = __hip_atomic_load(carry_word<int64_t>(carry_base(), w, lane), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-          if constexpr (K == 1 || K == 2)
+          if constexpr (K == 2 || K == 1)
 #pragma unroll
             for (int c = 0; c < K; ++c)
               v += __hip_atomic_load(carry_word<int32_t>(carry_base() + c * kSlot, w, lane),
@@ -386,7 +389,7 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
           tile::store_block(pr, val, i0 + ib * 16, j0);
         }
       };
-      if (!CHUNKED || slots == 0)
+      if constexpr (!CHUNKED)
         finish(std::integral_constant<int, 0>{});
       else if (wide)
         finish(std::integral_constant<int, 3>{});
@@ -560,7 +563,7 @@ size_t gemm_flush_bytes(int S, int num_cu) {
   // one int64 per accumulator word of one 128 x 128 tile per CU (the other
   // shapes need no more, so that a plan is valid whichever configuration runs);
   // two INT32 sums per word take the same space
-  static_assert(kInt32Chunks - 1 <= 2, "INT32 chunk sums fit the int64 space");
+  static_assert(kInt32Chunks <= 2, "INT32 chunk sums fit the int64 space");
   return (size_t)num_cu * 128 * 128 * (size_t)S * sizeof(int64_t);
 }
 
