@@ -35,7 +35,8 @@
  *     owned by the caller; the library never frees them. Scratch memory comes
  *     from the workspace given to ozaki_set_workspace, or else from a
  *     grow-only device buffer the library allocates and frees in
- *     ozaki_finalize.
+ *     ozaki_finalize. That buffer moves only when a call needs more than it
+ *     holds (its ozaki_workspace_bytes or ozaki2_workspace_bytes).
  *   - Work is enqueued on the stream given to ozaki_set_stream (default: the
  *     null stream) and is asynchronous: the call returns before the result is
  *     ready, the caller synchronises.
@@ -165,11 +166,11 @@ int ozaki_get_split(void);
  * OZAKI2_MODULI_MAX, and -14 also when beta < 1: too few moduli for K').
  * K' above OZAKI2_K_MAX (exact INT32 sums) returns -5. The workspace holds
  * the residue planes (see ozaki2_workspace_bytes). Where it goes on behind them
- * (the library's own does: one byte per modulus and output entry, at most 1
- * GiB or one strip of 256 columns), the modular products leave the chip there
- * as residue bytes, a strip of columns at a time, and a second kernel rebuilds
- * C; a caller's workspace of just ozaki2_workspace_bytes takes one fused kernel
- * that is about half as fast. The results are the same bit for bit.
+ * (the library's own does when it grows for the call: one byte per modulus and
+ * output entry, at most 1 GiB or one strip of 256 columns), the modular products
+ * leave the chip there as residue bytes, a strip of columns at a time, and a
+ * second kernel rebuilds C; a workspace of just ozaki2_workspace_bytes takes one
+ * fused kernel that is about half as fast. The results are the same bit for bit.
  */
 #define OZAKI2_MODULI_MIN 2
 #define OZAKI2_MODULI_MAX 20

@@ -162,10 +162,11 @@ int get_workspace(size_t bytes, void **out) {
   return OZAKI_OK;
 }
 
-// Workspace of at least `bytes` and, where it can be had, `want`: *got is what
-// there is. The caller's buffer is taken as it is; the library's own buffer
-// grows to `want`, except that nothing is allocated while the stream captures
-// or where only `bytes` can be allocated.
+// Workspace of at least `bytes` and, where that costs nothing, `want`: *got is
+// what there is. The caller's buffer is taken as it is. The library's own moves
+// only when it does not hold `bytes`, since graphs that a caller captured keep
+// its address: then it grows to `want`, except while the stream captures or
+// where only `bytes` can be allocated.
 int get_workspace_up_to(size_t bytes, size_t want, void **out, size_t *got) {
   int rc;
   if (g.user_ws != nullptr) {
@@ -175,7 +176,9 @@ int get_workspace_up_to(size_t bytes, size_t want, void **out, size_t *got) {
   }
   int dev = 0;
   if ((rc = current_device(&dev))) return rc;
-  if (g.own_ws_bytes[dev] >= bytes && g.own_ws_bytes[dev] < want) {
+  if (g.own_ws_bytes[dev] >= bytes) {
+    want = bytes;
+  } else {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(g.stream, &cs) != hipSuccess) {
       (void)hipGetLastError();

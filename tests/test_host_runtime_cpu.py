@@ -1,0 +1,113 @@
+"""Host runtime of libozaki and its BLAS interposer without a GPU: child processes load
+fake_hip.cpp (device memory as a budget, kernels and copies recorded) in front of the HIP
+runtime, make library calls and print what these asked of it."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+_PRELUDE = r"""
+import ctypes, sys
+sys.path.insert(0, %(root)r)
+fake = ctypes.CDLL(%(fake)r, mode=ctypes.RTLD_GLOBAL)
+fake.fake_log.restype = ctypes.c_char_p
+fake.fake_used.restype = ctypes.c_size_t
+fake.fake_pinned.restype = ctypes.c_void_p
+fake.fake_pinned.argtypes = fake.fake_budget.argtypes = [ctypes.c_size_t]
+import paper_2603_29975_amd as oz
+lib = oz.library()
+P = 1 << 40                                   # operands: addresses that no kernel reads
+MIB = 1 << 20
+
+def log():
+    return [l.split() for l in fake.fake_log().decode().splitlines()]
+
+def of(lines, *what):
+    return [l for l in lines if l[0] in what]
+
+def dgemm(m, n, k, s=7):
+    return lib.ozaki_dgemm(b"N", b"N", m, n, k, 1.0, P, m, P, k, 0.0, P, m, s)
+
+def crt(kind, m, n, k, moduli):
+    one, zero = (1.0, 0.0) if kind == "d" else (oz.ozaki_z(1.0, 0.0), oz.ozaki_z(0.0, 0.0))
+    f = lib.ozaki2_dgemm if kind == "d" else lib.ozaki2_zgemm
+    return f(b"N", b"N", m, n, k, one, P, m, P, k, zero, P, m, moduli)
+
+def need2(kind, m, n, k, moduli):
+    return lib.ozaki2_workspace_bytes(kind.encode(), m, n, k, moduli)
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", out],
+                   check=True, timeout=300)
+    return out
+
+
+@pytest.fixture
+def child(fake):
+    def run(script):
+        r = subprocess.run([sys.executable, "-c", _PRELUDE % {"root": ROOT, "fake": fake} + script],
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.strip().endswith("ok"), (r.returncode, r.stdout, r.stderr)
+    return run
+
+
+def test_workspace_moves_only_for_a_call_that_does_not_fit(child):
+    # 2048^3 complex at 14 moduli: 352 MiB of residue planes and 112 MiB for the products' residue
+    # bytes; a buffer in between holds the call, so its address, which captured graphs keep, stays
+    child(r"""
+case = ("z", 2048, 2048, 2048, 14)
+need = need2(*case)
+assert dgemm(3072, 4096, 4096, 12) == 0       # needs a little more
+made = of(log(), "malloc")
+assert len(made) == 1 and need < int(made[0][1]) < need + 32 * MIB, (need, made)
+for _ in range(2):
+    assert crt(*case) == 0
+    assert not of(log(), "malloc", "free", "nomem")
+print("ok")
+""")
+
+
+def test_workspace_of_a_first_ozaki2_call_holds_the_residue_bytes(child):
+    child(r"""
+case = ("z", 2048, 2048, 2048, 14)
+assert crt(*case) == 0
+made = log()
+assert int(of(made, "malloc")[0][1]) >= need2(*case) + 14 * 2048 * 4096
+assert any("k_oz2mod" in l[1] for l in of(made, "launch"))
+for _ in range(2):
+    assert crt(*case) == 0
+    assert not of(log(), "malloc", "free")
+print("ok")
+""")
+
+
+def test_workspace_without_room_for_the_residue_bytes_is_asked_for_once(child):
+    child(r"""
+case = ("z", 2048, 2048, 2048, 14)
+fake.fake_budget(need2(*case) + MIB)
+assert crt(*case) == 0
+assert len(of(log(), "malloc")) == 1
+for _ in range(3):
+    assert crt(*case) == 0
+    assert not of(log(), "malloc", "free", "nomem")
+print("ok")
+""")
+
+
+def test_capture_allocates_no_optional_space(child):
+    child(r"""
+case = ("z", 2048, 2048, 2048, 14)
+fake.fake_capture(1)
+assert crt(*case) == 0
+made = of(log(), "malloc")
+assert len(made) == 1 and int(made[0][1]) == need2(*case), made
+print("ok")
+""")
