@@ -149,14 +149,19 @@ int get_workspace(size_t bytes, void **out) {
       g.own_ws[dev] = nullptr;
       g.own_ws_bytes[dev] = 0;
     }
-    const size_t grow = std::max(bytes, (size_t)256 << 20);
-    void *p = nullptr;
-    if (hipMalloc(&p, grow) != hipSuccess) {
+    // at least 256 MiB, so that it seldom moves, or what a full device still has
+    for (const size_t least : {(size_t)256 << 20, (size_t)64 << 20, (size_t)0}) {
+      if (least != 0 && bytes >= least) continue;
+      const size_t grow = std::max(bytes, least);
+      void *p = nullptr;
+      if (hipMalloc(&p, grow) == hipSuccess) {
+        g.own_ws[dev] = p;
+        g.own_ws_bytes[dev] = grow;
+        break;
+      }
       (void)hipGetLastError();
-      return OZAKI_ERR_ALLOC;
     }
-    g.own_ws[dev] = p;
-    g.own_ws_bytes[dev] = grow;
+    if (g.own_ws[dev] == nullptr) return OZAKI_ERR_ALLOC;
   }
   *out = g.own_ws[dev];
   return OZAKI_OK;

@@ -111,3 +111,19 @@ made = of(log(), "malloc")
 assert len(made) == 1 and int(made[0][1]) == need2(*case), made
 print("ok")
 """)
+
+
+@pytest.mark.parametrize("mib", [100, 20])
+def test_small_product_on_a_nearly_full_device(child, mib):
+    # less free memory than the buffer's usual first size
+    child(r"""
+fake.fake_budget(%d * MIB)
+assert dgemm(64, 64, 64) == 0
+assert crt("z", 64, 64, 64, 14) == 0
+log()
+assert dgemm(64, 64, 64) == 0
+assert not of(log(), "malloc", "free", "nomem")
+fake.fake_budget(0)
+assert dgemm(4096, 4096, 4096) == 2           # OZAKI_ERR_ALLOC
+print("ok")
+""" % mib)
