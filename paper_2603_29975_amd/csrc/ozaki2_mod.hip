@@ -397,8 +397,9 @@ __device__ __forceinline__ double combine_rn(const float (&v)[NG]) {
 template <int N>
 __global__ void __launch_bounds__(256) k_oz2rebuild(Oz2ModArgs G) {
   constexpr int NW = (N + 3) / 4, NG = (N + 2) / 3;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t jq = blockIdx.y;
+  const uint32_t nti = (uint32_t)((G.m + 255) / 256);
+  const int64_t i = (int64_t)(blockIdx.x % nti) * 256 + threadIdx.x;
+  const int64_t jq = G.jq0 + blockIdx.x / nti;
   if (i >= G.m) return;
   const uint32_t *in = reinterpret_cast<const uint32_t *>(G.planes) + jq * G.ldq + i;
   uint32_t w[N];
@@ -489,14 +490,20 @@ hipError_t launch_oz2mod(const Oz2ModArgs &a, int num_cu, hipStream_t st) {
   else
     e = launch_mod<2, 2, 2, 2, 2>(a, num_cu, st);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)((a.m + 255) / 256), (unsigned)((a.jn + 3) / 4));
-  switch (a.n) {
+  // blocks of 256 rows of one group of four j', the rows first, in one launch
+  // unless that is too many blocks
+  Oz2ModArgs r = a;
+  const int64_t nti = (a.m + 255) / 256, ngroups = (a.jn + 3) / 4, most = std::max<int64_t>(kMaxBlocks / nti, 1);
+  for (r.jq0 = 0; r.jq0 < ngroups; r.jq0 += most) {
+    const dim3 grid((unsigned)(nti * std::min(most, ngroups - r.jq0)));
+    switch (a.n) {
 #define OZ_N(N) \
-  case N: hipLaunchKernelGGL(k_oz2rebuild<N>, grid, dim3(256), 0, st, a); break;
-    OZ_N(2) OZ_N(3) OZ_N(4) OZ_N(5) OZ_N(6) OZ_N(7) OZ_N(8) OZ_N(9) OZ_N(10) OZ_N(11)
-    OZ_N(12) OZ_N(13) OZ_N(14) OZ_N(15) OZ_N(16) OZ_N(17) OZ_N(18) OZ_N(19) OZ_N(20)
+  case N: hipLaunchKernelGGL(k_oz2rebuild<N>, grid, dim3(256), 0, st, r); break;
+      OZ_N(2) OZ_N(3) OZ_N(4) OZ_N(5) OZ_N(6) OZ_N(7) OZ_N(8) OZ_N(9) OZ_N(10) OZ_N(11)
+      OZ_N(12) OZ_N(13) OZ_N(14) OZ_N(15) OZ_N(16) OZ_N(17) OZ_N(18) OZ_N(19) OZ_N(20)
 #undef OZ_N
-    default: return hipErrorInvalidValue;
+      default: return hipErrorInvalidValue;
+    }
   }
   return hipGetLastError();
 }

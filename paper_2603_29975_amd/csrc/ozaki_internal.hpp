@@ -299,6 +299,7 @@ struct Oz2ModArgs {
   int64_t nrbQ, nrbP, nkb;
   int64_t m;
   int64_t jrb, jn;
+  int64_t jq0;  // first group of four j' of a rebuild launch (set there)
   int n;
   int beta;
   int8_t *planes;

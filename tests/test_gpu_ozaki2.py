@@ -232,3 +232,16 @@ def test_ozaki2_short_contractions(nmod, kind, m, n, k):
             got = _run(kind, ta, tb, A, B, nmod)
             ref = ozaki2.ozaki2_gemm("N", "N", A, B, nmod)
             assert bits_equal(got, ref), mismatch_report(got, ref)
+
+
+# More groups of four columns than a grid has blocks along y (65535), in one strip
+@pytest.mark.parametrize("kind,m,n,k,nmod", [("d", 32, 262149, 8, 8), ("z", 17, 131075, 5, 14)])
+def test_ozaki2_wide_products(kind, m, n, k, nmod):
+    A, B = _operands(kind, m, n, k, seed=995)
+    _say("ozaki2 wide", kind, (m, n, k), nmod)
+    got = _run(kind, "N", "N", A, B, nmod)
+    cols = np.concatenate([np.arange(40), np.arange(n // 2, n // 2 + 9), np.arange(n - 40, n),
+                           np.random.default_rng(996).choice(n, 200, replace=False)])
+    ref = ozaki2.ozaki2_gemm("N", "N", A, B[:, cols], nmod)
+    assert bits_equal(got[:, cols], ref), mismatch_report(got[:, cols], ref)
+    assert np.all(np.isfinite(got.view(np.float64)))

@@ -127,3 +127,20 @@ fake.fake_budget(0)
 assert dgemm(4096, 4096, 4096) == 2           # OZAKI_ERR_ALLOC
 print("ok")
 """ % mib)
+
+
+@pytest.mark.parametrize("kind,m,n,moduli", [("d", 32, 262145, 8), ("d", 1, 2000000, 2), ("z", 16, 131073, 14),
+                                             ("z", 300, 200000, 3), ("d", 500000, 700000, 2)])
+def test_wide_ozaki2_products_stay_within_the_grid_limits(child, kind, m, n, moduli):
+    # in the library's own workspace, and in one that holds the residue bytes of every column
+    child(r"""
+case = (%r, %d, %d, 8, %d)
+fake.fake_budget(1 << 46)
+for ws in (0, need2(*case) + (1 << 43)):
+    assert lib.ozaki_set_workspace(P if ws else None, ws) == 0
+    assert crt(*case) == 0, fake.fake_log()
+    made = log()
+    assert of(made, "launch") and not of(made, "refused")
+    assert any("k_oz2rebuild" in l[1] for l in made)
+print("ok")
+""" % (kind, m, n, moduli))
