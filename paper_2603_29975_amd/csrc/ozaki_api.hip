@@ -572,10 +572,18 @@ size_t oz2_strip_bytes(const Plan2 &p, int64_t j) {
   return (size_t)p.N * (size_t)round_up(p.m, kOz2RowPad) * (size_t)round_up(j, 4);
 }
 
-// j' per strip that `bytes` hold: all of them, a multiple of the tile, or 0.
+// j' per strip that `bytes` hold: all of them, a multiple of the tile, or 0 (the
+// fused kernel). Several strips are worth their launches from about 10 us of
+// products each. Whole call, us, strips of 256 columns / the fused kernel: z
+// 2048^3 at 8 / 13 / 14 moduli (1.7, 2.8, 3.0e10 products) 608 / 495, 816 / 819,
+// 863 / 1064, d 2000^3 at 8 (0.8e10) 192 / 164, z 64 x 4096 x 64 at 14 275 / 55;
+// of 1024: z 2048^3 at 8 (6.9e10) 375 / 495, z 512 x 4096 x 512 at 18 (1e10) 288 / 259.
+constexpr double kOz2StripProducts = 2.5e10;
+
 int64_t oz2_strip(const Plan2 &p, size_t bytes) {
   if (oz2_strip_bytes(p, p.nprime) <= bytes) return p.nprime;
-  return (int64_t)(bytes / oz2_strip_bytes(p, kOz2StripJ)) * kOz2StripJ;
+  const int64_t strip = (int64_t)(bytes / oz2_strip_bytes(p, kOz2StripJ)) * kOz2StripJ;
+  return (double)p.N * p.m * strip * (p.nkb * 32) >= kOz2StripProducts ? strip : 0;
 }
 
 size_t oz2_plane_bytes(const Plan2 &p) {

@@ -144,3 +144,24 @@ for ws in (0, need2(*case) + (1 << 43)):
     assert any("k_oz2rebuild" in l[1] for l in made)
 print("ok")
 """ % (kind, m, n, moduli))
+
+
+# strips: how many the two-kernel path is cut into, 0 for the fused kernel
+@pytest.mark.parametrize("kind,m,n,k,moduli,columns,strips", [
+    ("z", 64, 4096, 64, 14, 256, 0),          # many small strips: the fused kernel is faster
+    ("d", 100, 8000, 100, 8, 1024, 0),
+    ("z", 512, 4096, 512, 18, 1024, 0),
+    ("d", 4096, 4096, 4096, 8, 256, 16),      # strips that fill the chip for long enough
+    ("z", 2048, 2048, 2048, 14, 1024, 4),
+    ("z", 64, 4096, 64, 14, 8192, 1)])        # every column at once
+def test_ozaki2_strips_in_a_limited_workspace(child, kind, m, n, k, moduli, columns, strips):
+    child(r"""
+case = (%r, %d, %d, %d, %d)
+ws = need2(*case) + case[4] * %d * ((case[1] + 31) // 32 * 32)
+assert lib.ozaki_set_workspace(P, ws) == 0
+assert crt(*case) == 0
+names = [l[1] for l in of(log(), "launch")]
+assert sum("k_oz2mod" in x for x in names) == %d, names
+assert sum("k_oz2gemm" in x for x in names) == %d, names
+print("ok")
+""" % (kind, m, n, k, moduli, columns, strips, strips == 0))
