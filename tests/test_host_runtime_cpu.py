@@ -165,3 +165,50 @@ assert sum("k_oz2mod" in x for x in names) == %d, names
 assert sum("k_oz2gemm" in x for x in names) == %d, names
 print("ok")
 """ % (kind, m, n, k, moduli, columns, strips, strips == 0))
+
+
+_BLAS = r"""
+from paper_2603_29975_amd import blas
+import numpy as np
+b = blas.library()
+def zgemm(n, A, ld, B, C):
+    i, z = (lambda v: ctypes.byref(ctypes.c_int(v))), (lambda v: ctypes.byref(oz.ozaki_z(v, 0.0)))
+    b.zgemm_(b"N", b"N", i(n), i(n), i(n), z(1.0), A, i(ld), B, i(ld), z(0.0), C, i(ld))
+def copies():
+    return [l for l in log() if l[0] in ("copy", "copy2d", "copyasync", "pinned")]
+"""
+
+
+def test_interposer_takes_memory_known_to_the_runtime_straight_over_the_link(child):
+    # 1000 x 1000 complex (16 MB): pinned arrays in one copy each, packed or pitched, no staging;
+    # device memory, which the host may not touch (here: not at all), the same way
+    child(_BLAS + r"""
+n, size = 1000, 16 * 1000 * 1000
+pinned = [fake.fake_pinned(size + 16 * 1000 * 8) for _ in range(3)]
+device = []
+for _ in range(3):
+    p = ctypes.c_void_p()
+    assert fake.hipMalloc(ctypes.byref(p), ctypes.c_size_t(size + 16 * 1000 * 8)) == 0
+    device.append(p.value)
+for A, B, C in (pinned, device, [x + 16 for x in pinned]):
+    log()
+    zgemm(n, A, n, B, C)
+    assert copies() == [["copy", str(size), "1"]] * 2 + [["copy", str(size), "2"]]
+    zgemm(n, A, n + 8, B, C)
+    assert copies() == [["copy2d", str(16 * n), str(n), "1"]] * 2 + [["copy2d", str(16 * n), str(n), "2"]]
+print("ok")
+""")
+
+
+def test_interposer_stages_large_or_pitched_pageable_arrays(child):
+    child(_BLAS + r"""
+def arrays(n, ld):
+    return [np.zeros((n, ld), dtype=np.complex128) for _ in range(3)]
+for n, ld, staged in ((1000, 1000, True), (100, 100, False), (100, 101, True)):
+    X = arrays(n, ld)
+    log()
+    zgemm(n, X[0].ctypes.data, ld, X[1].ctypes.data, X[2].ctypes.data)
+    got = {l[0] for l in copies()}
+    assert ("copyasync" in got) == staged and ("copy" in got) != staged and "copy2d" not in got, (n, ld, got)
+print("ok")
+""")
