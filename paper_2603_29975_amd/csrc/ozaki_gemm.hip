@@ -319,7 +319,13 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
 #pragma unroll
           for (int w = 0; w < WORDS; ++w) {
             int64_t *p = carry_word<int64_t>(cb, w, lane);
-            const int64_t v = acc_word(w);
+            // (asm: the compiler extended all words ahead of the branch, which
+            // spilled 99 registers at S = 9 and 356 at S = 6: z 4096 x 1024 x
+            // 16384 S = 9 11.9 ms, now 9.3; 2048^2 x 20000 S = 9 13.3, 11.4, S = 6
+            // 5.42, 5.30)
+            int32_t a = acc_word(w);
+            asm volatile("" : "+v"(a));
+            const int64_t v = a;
             if (slots == 0)
               __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else
@@ -354,8 +360,8 @@ __global__ void __launch_bounds__(64 * WJ * WI, WPS) k_ozgemm(GemmArgs G) {
       constexpr int ib = decltype(ibc)::value;
       // The block from the accumulators (K 0), or from its chunk sums: one or two INT32
       // ones (1, 2) or int64 (3). The last chunk's go to memory like the others', which ends
-      // the accumulators' life there: kept for the epilogue they made the chunk loop
-      // spill 1096 bytes a lane (652 now; 16384^3 complex, S = 6, 1.8% slower).
+      // the accumulators' life there: kept for the epilogue they took registers from the
+      // chunk loop (16384^3 complex, S = 6, 1.8% slower).
       auto finish = [&](auto kind) {
         constexpr int K = decltype(kind)::value;
         auto total = [&](int t, int r) -> int64_t {
