@@ -69,11 +69,21 @@ struct PrepTask {
   int side_b;
 };
 // A short contraction is scanned and split in one kernel: one launch instead of
-// three, for a scan per 64 packed entries. Measured, whole call, one kernel /
-// three: z 32^3 12.3 / 16.9 us, d 256^3 (256 packed entries) 14.8 / 19.7, z
-// 1920^2 x 128 60.7 / 65.4; with 512 entries z 256^3 20.8 / 22.2, d 512^3 23.5 /
-// 27.0 (512 blocks of the kernel) but z 1200^2 x 256 53.2 / 51.3 (1280 blocks);
-// with 1024 entries d 1024^3 62 / 45.
+// three, for a scan per 64 packed entries, which costs more than the launches
+// once the operands are large. Measured, whole call, one kernel / three, S = 7: z
+// 32^3 12.3 / 16.9 us, d 256^3 (256 packed entries) 14.8 / 19.7, z 1920^2 x 128
+// 60.7 / 65.4. By packed entries and blocks of the kernel:
+//    64: z 64 x 100000 (6250) 94 / 113, d 68 / 87: always
+//   128: d 64 x 100000 (12500) 103 / 122, z 64 x 30000 (3750) 53 / 59 but z
+//        100000 x 64 145 / 130
+//   192: d 64 x 8000 (1524) 21.3 / 27.0, d 30000 x 64 (5649) 53 / 47
+//   256: z 64 x 2000 (532) 17.1 / 20.5, z 64 x 8000 (2032) 31.1 / 31.1, z 64 x
+//        100000 325 / 289, d 30000 x 64 73 / 56
+//        from 10 slices on, where the split is slower, z 64 x 100000 436 / 478
+//        but z 100000 x 64 388 / 359, d 299 / 290: one kernel up to 256 entries
+//   512: z 256^3 20.8 / 22.2, d 512^3 (512) 23.5 / 27.0, z 1200^2 x 256 (1280)
+//        53.2 / 51.3
+//   1024: d 1024^3 62 / 45.
 bool prep_fits(const PrepTask &a, const PrepTask &b);
 hipError_t launch_prep(const PrepTask &a, const PrepTask &b, hipStream_t st, bool b8);
 

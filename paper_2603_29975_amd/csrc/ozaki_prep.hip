@@ -818,7 +818,8 @@ int64_t prep_task_blocks(const PrepTask &t) {
 
 bool prep_fits(const PrepTask &a, const PrepTask &b) {
   const int64_t kpad = a.nkb * 32, blocks = prep_task_blocks(a) + prep_task_blocks(b);
-  return kpad <= 256 ? blocks <= kMaxBlocks : kpad <= 512 && blocks <= 1024;
+  if (kpad <= 64 || (kpad <= 128 && !a.cplx) || (kpad <= 256 && a.S >= 10)) return blocks <= kMaxBlocks;
+  return kpad <= 512 && blocks <= (kpad <= 128 ? 4096 : kpad <= 256 ? 1536 : 1024);
 }
 
 hipError_t launch_prep(const PrepTask &a, const PrepTask &b, hipStream_t st, bool b8) {

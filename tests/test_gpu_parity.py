@@ -318,3 +318,25 @@ def test_kkr_2048_sampled_bit_exact_and_accuracy():
     err = metrics.err_comp(sub.ravel(), hi, lo, den)
     _say("kkr 2048 s=7 err_comp (sampled)", err)
     assert err <= 1e-12
+
+
+# Short contractions of operands too large for the one scan-and-split kernel
+@pytest.mark.parametrize("kind,m,n,k,ta,tb", [("d", 30011, 33, 200, "N", "N"), ("d", 30011, 33, 200, "T", "T"),
+                                              ("z", 35, 30011, 97, "N", "N"), ("z", 35, 30011, 97, "C", "T")])
+def test_short_contractions_of_large_operands(kind, m, n, k, ta, tb):
+    s = 6
+    A, B = uniform_binade(m, n, k, seed=1300 + k, complex_=kind == "z")
+    A[5], B[:, 7] = 0.0, 0.0
+    A[m // 2, k - 1] = np.nan
+    store = {"N": lambda X: X, "T": lambda X: np.ascontiguousarray(X.T), "C": lambda X: np.ascontiguousarray(X.conj().T)}
+    Ad, lda = dev(store[ta](A))
+    Bd, ldb = dev(store[tb](B))
+    Cd, ldc = dev(np.full((m, n), np.nan, dtype=A.dtype))
+    print("large operands", kind, (m, n, k), ta, tb, flush=True)
+    fn = oz.ozaki_zgemm if kind == "z" else oz.ozaki_dgemm
+    assert fn(ta, tb, m, n, k, 1.0, Ad, lda, Bd, ldb, 0.0, Cd, ldc, s) == 0
+    got = host(Cd, m, n)
+    pick = lambda x: np.unique(np.concatenate([np.arange(min(20, x)), [x // 2], np.arange(max(0, x - 20), x)]))
+    r, c = pick(m), pick(n)
+    ref = ozaki.ozaki_gemm("N", "N", A[r], B[:, c], s)
+    assert bits_equal(got[np.ix_(r, c)], ref), mismatch_report(got[np.ix_(r, c)], ref)

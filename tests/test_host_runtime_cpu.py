@@ -212,3 +212,24 @@ for n, ld, staged in ((1000, 1000, True), (100, 100, False), (100, 101, True)):
     assert ("copyasync" in got) == staged and ("copy" in got) != staged and "copy2d" not in got, (n, ld, got)
 print("ok")
 """)
+
+
+# One scan-and-split kernel for operands up to so many blocks, by the packed contraction (k, or 2k
+# complex, up to 64, 128, 256, 512); beyond, a scan and a split of both operands
+@pytest.mark.parametrize("kind,m,n,k,fused", [
+    ("d", 64, 500000, 64, True), ("z", 64, 500000, 32, True),
+    ("d", 64, 100000, 128, True), ("z", 64, 30000, 64, True), ("z", 64, 100000, 64, False),
+    ("z", 100000, 64, 64, False),
+    ("d", 8000, 64, 192, True), ("d", 30000, 64, 192, False), ("z", 64, 8000, 96, True),
+    ("d", 2000, 2000, 256, True), ("d", 64, 30000, 256, False), ("z", 64, 100000, 128, False),
+    ("d", 512, 512, 512, True), ("z", 1200, 1200, 256, False), ("d", 64, 64, 513, False)])
+def test_scan_and_split_kernels_by_size(child, kind, m, n, k, fused):
+    child(r"""
+kind, m, n, k, fused = %r, %d, %d, %d, %r
+assert dgemm(m, n, k) == 0 if kind == "d" else lib.ozaki_zgemm(
+    b"N", b"N", m, n, k, oz.ozaki_z(1.0, 0.0), P, m, P, k, oz.ozaki_z(0.0, 0.0), P, m, 7) == 0
+names = [l[1] for l in of(log(), "launch")]
+assert any("k_prep" in x for x in names) == fused, names
+assert any("k_scan" in x for x in names) != fused and any("k_split" in x for x in names) != fused, names
+print("ok")
+""" % (kind, m, n, k, fused))
