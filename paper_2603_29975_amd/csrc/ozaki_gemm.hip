@@ -611,12 +611,15 @@ GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb
   // 256 x 8192 475, now 70; z 517 x 389 x 1031 72, now 41; z 1500 x 700 x 300 57,
   // now 50. 64 x 64 / 32 x 32 tiles: d 256^3 12.2 / 8.8, z 256^3 15.6 / 10.8, d
   // 512^3 16.7 / 11.3, but z 700 x 700 x 128 14.1 / 20.9.
+  // Up to 64 rows 128 x 64 tiles read B' no less often than 64 x 64 ones, of which a
+  // CU runs two up to S = 6 (z 64 x 100000 x 128 S = 6 264 / 246, z 16 x 40000 x 700
+  // S = 5 435 / 417, z 64 x 12500 x 100 S = 5 38.0 / 36.4).
   const int64_t kb = nkb / 2, chunk = std::max<int64_t>(kb_chunk / 2, 1);
   GemmChoice best{0, 1, kb};
   double best_t = 1e300;
   *need = 0;
   for (const Shape s : {kTall, kBig, kSmall, kTiny}) {
-    if (!shape_takes(s, S)) continue;
+    if (!shape_takes(s, S) || (s == kTall && m <= 64 && S <= 6)) continue;
     const int64_t area = (int64_t)shape_bj(s) * shape_bi(s), tiles = shape_tiles(s, m, nprime);
     for (int64_t ks = 1; ks <= (s == kSmall || s == kTiny ? 64 : 1); ++ks) {
       const int64_t part = (kb + ks - 1) / ks, items = tiles * ks;
@@ -630,8 +633,13 @@ GemmChoice gemm_choose(int S, int64_t m, int64_t nprime, int64_t nkb, int64_t kb
       if (ks > 1) t += 2.1 + 0.38e-6 * bytes + 0.13 * ks;
       if (t < best_t) {
         best_t = t;
-        // 128-row tiles in XCD-aware groups, the others down the rows
-        best = GemmChoice{s == kBig ? 27 : s == kTall ? 21 : s == kSmall ? 8 : kTinyId, (int)ks, part};
+        // 128-row tiles in XCD-aware groups, but down the rows where a tall product is
+        // much wider still (z 5000 x 40000 x 16 S = 7 1590 / 1351, x 400 7720 / 7380;
+        // z 8000^2 x 64 S = 6 475 / 500, z 700 x 5000 x 100 S = 7 69 / 76); the others
+        // down the rows
+        const bool wide = m >= 4096 && nprime >= 8 * m;
+        best = GemmChoice{s == kBig ? (wide ? 12 : 27) : s == kTall ? (wide ? 4 : 21) : s == kSmall ? 8 : kTinyId,
+                          (int)ks, part};
         *need = bytes;
       }
     }

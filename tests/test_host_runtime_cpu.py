@@ -233,3 +233,17 @@ assert any("k_prep" in x for x in names) == fused, names
 assert any("k_scan" in x for x in names) != fused and any("k_split" in x for x in names) != fused, names
 print("ok")
 """ % (kind, m, n, k, fused))
+
+
+# k_ozgemm<S, WJ, WI, IB, ...> of a product without a table entry: 64 x 64 tiles are <S, 4, 1, 4>,
+# 128 x 64 ones <S, 8, 1, 4>
+@pytest.mark.parametrize("m,n,k,s,tile", [(64, 100000, 128, 6, "4ELi1ELi4"), (16, 40000, 700, 5, "4ELi1ELi4"),
+                                          (64, 100000, 128, 7, "8ELi1ELi4"), (65, 100000, 128, 7, "8ELi1ELi4")])
+def test_tiles_of_thin_products(child, m, n, k, s, tile):
+    child(r"""
+m, n, k, s = %d, %d, %d, %d
+assert lib.ozaki_zgemm(b"N", b"N", m, n, k, oz.ozaki_z(1.0, 0.0), P, m, P, k, oz.ozaki_z(0.0, 0.0), P, m, s) == 0
+names = [l[1] for l in of(log(), "launch")]
+assert any("k_ozgemmILi%%dELi%s" %% s in x for x in names), names
+print("ok")
+""" % (m, n, k, s, tile))
