@@ -245,3 +245,22 @@ def test_ozaki2_wide_products(kind, m, n, k, nmod):
     ref = ozaki2.ozaki2_gemm("N", "N", A, B[:, cols], nmod)
     assert bits_equal(got[:, cols], ref), mismatch_report(got[:, cols], ref)
     assert np.all(np.isfinite(got.view(np.float64)))
+
+
+def test_ozaki2_residue_bytes_beside_the_workspace():
+    # a workspace that a real product left, with room for the residue planes but not for the
+    # products' residue bytes behind them, gives the bits of one that grew for the call
+    m = n = k = 2048
+    A, B = kkr_operands(64, seed=1002)
+    assert oz.ozaki_finalize() == 0
+    ref = _run("z", "N", "N", A, B, 14)
+    assert oz.ozaki_finalize() == 0
+    X = torch.zeros((4096, 4096), dtype=torch.float64, device="cuda")
+    assert oz.ozaki_dgemm("N", "N", 3072, 4096, 4096, 1.0, X, 3072, X, 4096, 0.0, torch.empty_like(X), 3072, 12) == 0
+    need = oz.ozaki2_workspace_bytes("z", m, n, k, 14)
+    assert need <= oz.ozaki_workspace_bytes("d", 3072, 4096, 4096, 12) < need + 14 * m * 2 * n
+    for _ in range(2):
+        _say("ozaki2 beside the workspace")
+        got = _run("z", "N", "N", A, B, 14)
+        assert bits_equal(got, ref), mismatch_report(got, ref)
+    assert oz.ozaki_finalize() == 0

@@ -68,9 +68,14 @@ need = need2(*case)
 assert dgemm(3072, 4096, 4096, 12) == 0       # needs a little more
 made = of(log(), "malloc")
 assert len(made) == 1 and need < int(made[0][1]) < need + 32 * MIB, (need, made)
-for _ in range(2):
+for call in range(3):
     assert crt(*case) == 0
-    assert not of(log(), "malloc", "free", "nomem")
+    made = log()
+    assert not of(made, "free", "nomem")
+    # the residue bytes go to 256 MiB of their own, asked for once
+    assert of(made, "malloc") == ([["malloc", str(256 * MIB)]] if call == 0 else [])
+    assert any("k_oz2mod" in l[1] for l in of(made, "launch"))
+assert lib.ozaki_finalize() == 0 and fake.fake_used() == 0
 print("ok")
 """)
 
@@ -94,7 +99,8 @@ def test_workspace_without_room_for_the_residue_bytes_is_asked_for_once(child):
 case = ("z", 2048, 2048, 2048, 14)
 fake.fake_budget(need2(*case) + MIB)
 assert crt(*case) == 0
-assert len(of(log(), "malloc")) == 1
+made = log()
+assert len(of(made, "malloc")) == 1 and any("k_oz2gemm" in l[1] for l in of(made, "launch"))
 for _ in range(3):
     assert crt(*case) == 0
     assert not of(log(), "malloc", "free", "nomem")
@@ -109,6 +115,8 @@ fake.fake_capture(1)
 assert crt(*case) == 0
 made = of(log(), "malloc")
 assert len(made) == 1 and int(made[0][1]) == need2(*case), made
+fake.fake_capture(0)
+assert crt(*case) == 0 and len(of(log(), "malloc")) == 1
 print("ok")
 """)
 
