@@ -480,12 +480,15 @@ hipError_t launch_oz2mod(const Oz2ModArgs &a, int num_cu, hipStream_t st) {
   // 14 moduli: z 4096^3 3903 / 4787 / 8487 (7168 items of 256), d 1024^3 63.9 /
   // 69.7 / 80.9 (224), z 4096 x 128 x 4096 357 / 395 / 533 (224), z 512 x 512 x
   // 4096 173 / 145 / 192 (112; 448 of 128), z 256^3 44.7 / 38.6 / 36.9 (28;
-  // 112), z 128^3 38.6 / 35.3 / 31.8 (14; 28).
+  // 112), z 128^3 38.6 / 35.3 / 31.8 (14; 28). No tile is twice as long as the
+  // shorter side of C: z 100 x 40000 x 16 232 / 183 / 246, x 700 1074 / 1028 / 1256,
+  // z 16 x 40000 x 16 202 / 143 / 138, z 40000 x 8 x 100 145 / 111 / 107.
   auto items = [&](int64_t t) { return ((a.m + t - 1) / t) * ((a.jn + t - 1) / t) * a.n; };
+  const int64_t side = std::min(a.m, a.jn);
   hipError_t e;
-  if (items(256) * 4 >= 3 * (int64_t)num_cu)
+  if (side > 128 && items(256) * 4 >= 3 * (int64_t)num_cu)
     e = launch_mod<2, 4, 8, 4, 2>(a, num_cu, st);
-  else if (items(128) >= num_cu)
+  else if (side > 64 && items(128) >= num_cu)
     e = launch_mod<2, 2, 4, 4, 2>(a, num_cu, st);
   else
     e = launch_mod<2, 2, 2, 2, 2>(a, num_cu, st);
