@@ -2,8 +2,8 @@
 // an output tile and the Chinese-remainder rebuild in one kernel.
 //
 // The form that needs no scratch beyond the residue planes: taken where the
-// workspace ends with them (ozaki2_mod.hip is about twice as fast and is taken
-// everywhere else).
+// workspace ends with them, and for the thin products of oz2gemm_preferred
+// (ozaki2_mod.hip is up to twice as fast elsewhere).
 //
 // Section 2.2 of the paper: the integer operands are multiplied modulo
 // several pairwise-coprime moduli on the integer matrix cores, and the Chinese
@@ -271,20 +271,35 @@ hipError_t launch_v(const Oz2Args &a, int num_cu, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Two A' blocks per wave while the digits of 2 x 16 entries fit the
+// registers (N <= 16: 4 words per entry), else one. Measured at 2048^3
+// complex (GEMM per launch): 13 moduli 0.687 ms with two blocks, 0.824 with
+// one; 15 moduli 0.762 against 0.958; at 14 moduli the compiler spills 79
+// registers in the main loop with two blocks (1.010 ms) and one block is
+// faster (0.900 ms). A five-stage ring (160 KiB) and an eight-stage ring of
+// two-block stages were no faster at 13 moduli.
+constexpr int a_blocks(int n) { return (n <= 16 && n != 14) ? 2 : 1; }
+
 template <int N>
 hipError_t launch_n(const Oz2Args &a, int num_cu, hipStream_t st) {
-  // two A' blocks per wave while the digits of 2 x 16 entries fit the
-  // registers (N <= 16: 4 words per entry), else one. Measured at 2048^3
-  // complex (GEMM per launch): 13 moduli 0.687 ms with two blocks, 0.824 with
-  // one; 15 moduli 0.762 against 0.958; at 14 moduli the compiler spills 79
-  // registers in the main loop with two blocks (1.010 ms) and one block is
-  // faster (0.900 ms). A five-stage ring (160 KiB) and an eight-stage ring of
-  // two-block stages were no faster at 13 moduli.
-  constexpr int IB = (N <= 16 && N != 14) ? 2 : 1;
+  constexpr int IB = a_blocks(N);
   return launch_v<N, IB, kRing, kStep>(a, num_cu, st);
 }
 
 }  // namespace
+
+// Up to 64 rows a tile of one A' block per wave reads B' once for all moduli, as
+// the kernels of ozaki2_mod.hip do, and writes no residue bytes. Taken while the
+// last round of tiles leaves at most a fifth of the CUs idle. Whole call, us, the
+// two kernels / this one: 14 moduli z 64 x 16000 x 700 (250 tiles) 414 / 392, z 16
+// x 32000 x 100 (500) 178 / 153, z 64 x 100000 x 700 2434 / 2270, but z 64 x 25000
+// x 16 (391) 96 / 100, z 64 x 10000 x 16 (157) 51 / 60; 18 moduli z 64 x 60000 x
+// 16 301 / 258. With two blocks, of whose 128 rows half are padding: 13 moduli z 64
+// x 40000 x 100 220 / 320.
+bool oz2gemm_preferred(int n, int64_t m, int64_t nprime, int num_cu) {
+  const int64_t tiles = (nprime + 32 * kWJ - 1) / (32 * kWJ), rounds = (tiles + num_cu - 1) / num_cu;
+  return a_blocks(n) == 1 && m <= 32 * kWI && 5 * tiles >= 4 * rounds * num_cu;
+}
 
 hipError_t launch_oz2gemm(int n, const Oz2Args &a, int num_cu, hipStream_t st) {
   if (a.m <= 0 || a.nprime <= 0) return hipSuccess;

@@ -634,7 +634,9 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   if ((rc = current_device(&dev))) return rc;
   void *wsv = nullptr;
   size_t ws_bytes = 0;
-  if ((rc = get_workspace_up_to(p.total, p.total + oz2_plane_bytes(p), &wsv, &ws_bytes))) return rc;
+  const bool fused_products = oz2gemm_preferred(moduli, m, p.nprime, g.dev[dev].num_cu);
+  const size_t plane_bytes = fused_products ? 0 : oz2_plane_bytes(p);
+  if ((rc = get_workspace_up_to(p.total, p.total + plane_bytes, &wsv, &ws_bytes))) return rc;
   char *ws = static_cast<char *>(wsv);
   int *codeA = reinterpret_cast<int *>(ws + p.off_codeA);
   int *codeB = reinterpret_cast<int *>(ws + p.off_codeB);
@@ -687,11 +689,11 @@ int ozaki2_gemm_impl(bool cplx, char transa, char transb, int64_t m, int64_t n, 
   ga.ldc = ldc;
   char *planes = ws + p.total;
   size_t room = ws_bytes - p.total;
-  if (g.user_ws == nullptr && room < kOz2AuxBytes && room < oz2_plane_bytes(p) && oz2_aux(dev) != nullptr) {
+  if (g.user_ws == nullptr && room < std::min(plane_bytes, kOz2AuxBytes) && oz2_aux(dev) != nullptr) {
     planes = static_cast<char *>(g.own_aux[dev]);
     room = kOz2AuxBytes;
   }
-  const int64_t strip = oz2_strip(p, room);
+  const int64_t strip = fused_products ? 0 : oz2_strip(p, room);
   if (strip == 0) {
     rc = hip_rc(launch_oz2gemm(moduli, ga, g.dev[dev].num_cu, st));
   } else {

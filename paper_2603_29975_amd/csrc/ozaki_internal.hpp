@@ -300,6 +300,8 @@ struct Oz2Args {
   int64_t ldc;
 };
 hipError_t launch_oz2gemm(int n, const Oz2Args &a, int num_cu, hipStream_t st);
+// Whether it is the faster one also where there is room for launch_oz2mod.
+bool oz2gemm_preferred(int n, int64_t m, int64_t nprime, int num_cu);
 // The same product by one residue byte per output entry and modulus (see
 // ozaki2_mod.hip), over the j' of one strip of columns: the 32-row blocks of B'
 // from jrb on, jn of their j'. planes: n planes of plane_words words, word

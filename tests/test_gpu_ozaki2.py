@@ -235,7 +235,7 @@ def test_ozaki2_short_contractions(nmod, kind, m, n, k):
 
 
 # More groups of four columns than a grid has blocks along y (65535), in one strip
-@pytest.mark.parametrize("kind,m,n,k,nmod", [("d", 32, 262149, 8, 8), ("z", 17, 131075, 5, 14)])
+@pytest.mark.parametrize("kind,m,n,k,nmod", [("d", 32, 262149, 8, 8), ("z", 17, 131075, 5, 16)])
 def test_ozaki2_wide_products(kind, m, n, k, nmod):
     A, B = _operands(kind, m, n, k, seed=995)
     _say("ozaki2 wide", kind, (m, n, k), nmod)
@@ -264,3 +264,17 @@ def test_ozaki2_residue_bytes_beside_the_workspace():
         got = _run("z", "N", "N", A, B, 14)
         assert bits_equal(got, ref), mismatch_report(got, ref)
     assert oz.ozaki_finalize() == 0
+
+
+# Wide products on both sides of 64 rows, where the fused kernel gives way to residue bytes
+@pytest.mark.parametrize("nmod", [14, 19])
+@pytest.mark.parametrize("kind,m,n,k", [("d", 1, 32700, 70), ("d", 64, 32765, 33), ("z", 64, 16383, 20),
+                                        ("d", 65, 32765, 33)])
+def test_ozaki2_thin_products(nmod, kind, m, n, k):
+    A, B = _operands(kind, m, n, k, seed=1010 + m, nasty=m > 1)
+    _say("ozaki2 thin", kind, (m, n, k), nmod)
+    got = _run(kind, "N", "N", A, B, nmod)
+    cols = np.unique(np.concatenate([np.arange(70), np.arange(n - 70, n),
+                                     np.random.default_rng(1011).choice(n, 100, replace=False)]))
+    ref = ozaki2.ozaki2_gemm("N", "N", A, B[:, cols], nmod)
+    assert bits_equal(got[:, cols], ref), mismatch_report(got[:, cols], ref)

@@ -137,7 +137,7 @@ print("ok")
 """ % mib)
 
 
-@pytest.mark.parametrize("kind,m,n,moduli", [("d", 32, 262145, 8), ("d", 1, 2000000, 2), ("z", 16, 131073, 14),
+@pytest.mark.parametrize("kind,m,n,moduli", [("d", 32, 262145, 8), ("d", 1, 2000000, 2), ("z", 16, 131073, 16),
                                              ("z", 300, 200000, 3), ("d", 500000, 700000, 2)])
 def test_wide_ozaki2_products_stay_within_the_grid_limits(child, kind, m, n, moduli):
     # in the library's own workspace, and in one that holds the residue bytes of every column
@@ -255,3 +255,20 @@ names = [l[1] for l in of(log(), "launch")]
 assert any("k_ozgemmILi%%dELi%s" %% s in x for x in names), names
 print("ok")
 """ % (m, n, k, s, tile))
+
+
+# The kernel of the modular products: k_oz2gemm (fused), or k_oz2mod by its tile, <2, 4, 8, 4> 256 x
+# 256, <2, 2, 4, 4> 128 x 128, <2, 2, 2, 2> 64 x 64
+@pytest.mark.parametrize("kind,m,n,k,moduli,kernel", [
+    ("z", 16, 40000, 16, 8, "k_oz2modILi2ELi2ELi2E"), ("z", 100, 40000, 16, 14, "k_oz2modILi2ELi2ELi4E"),
+    ("z", 40000, 8, 100, 14, "k_oz2modILi2ELi2ELi2E"), ("z", 200, 40000, 16, 14, "k_oz2modILi2ELi4ELi8E"),
+    ("z", 64, 16000, 700, 14, "k_oz2gemm"), ("z", 65, 16000, 700, 14, "k_oz2mod"),
+    ("z", 64, 25000, 16, 14, "k_oz2mod"), ("z", 64, 40000, 100, 13, "k_oz2mod"),
+    ("d", 64, 200000, 200, 18, "k_oz2gemm")])
+def test_ozaki2_kernels_of_thin_products(child, kind, m, n, k, moduli, kernel):
+    child(r"""
+assert crt(%r, %d, %d, %d, %d) == 0
+names = [l[1] for l in of(log(), "launch")]
+assert any("%s" in x for x in names), names
+print("ok")
+""" % (kind, m, n, k, moduli, kernel))
