@@ -228,3 +228,71 @@ def test_automatic_slices_constant_twelve():
                                 bt.alphas, bt.Ad, bt.lda, bt.Bd, bt.ldb, bt.betas, bt.Cd, bt.ldc, nb,
                                 None, used)
     assert rc == 0 and used == [12] * nb
+
+
+# Contractions of one, two and more INT32 chunks in one launch (s = 6: up to 11088 complex
+# entries in a chunk, s = 7: 9504): three workgroups walk all tiles, so that the space of the
+# chunks' sums goes from problem to problem and from INT32 to int64 sums (64 x 64 tiles; 32 x 32
+# ones carry no chunks).
+@pytest.mark.parametrize("s", [6, 7])
+@pytest.mark.parametrize("m,n", [(150, 90), (33, 20)])
+def test_batched_chunked_and_short_contractions(s, m, n):
+    ks = [70, {6: 11200, 7: 9600}[s], 70, {6: 23000, 7: 20000}[s], 129]
+    count = len(ks)
+    probs, _ = batched_problems(count, 40 + s, max_spread=12.0,
+                                sizes=(np.full(count, m), np.full(count, n), np.array(ks)))
+    rng = np.random.default_rng(41)
+    C0s = [rng.standard_normal((m, n)) + 1j * rng.standard_normal((m, n)) for _ in ks]
+    bt = Batch(probs, [("N", "N"), ("T", "N"), ("N", "C"), ("N", "T"), ("C", "N")],
+               [1.0, 0.5 - 1j, 1.0, -0.25 + 2j, 1.0], [0.0, 1j, 0.5, 0.0, 1.0], C0s, [s] * count)
+    refs = [bt.reference(b) for b in range(count)]
+    for limit in (3, 0):
+        assert oz.ozaki_set_grid_limit(limit) == 0
+        oz.ozaki_batched_cache_clear()
+        bt.reset_c()
+        _say("batched chunked", s, (m, n), "grid limit", limit)
+        try:
+            got = bt.run()
+        finally:
+            oz.ozaki_set_grid_limit(0)
+        for b in range(count):
+            assert bits_equal(got[b], refs[b]), f"problem {b} (k = {ks[b]})\n" + mismatch_report(got[b], refs[b])
+
+
+# The same with enough tiles for the 128 x 128 shape (6 slices) and the 128 x 64 one (7), checked on
+# some rows and columns
+@pytest.mark.parametrize("s", [6, 7])
+def test_batched_chunked_large_tiles(s):
+    k = {6: 11200, 7: 9600}[s]
+    sizes = [(900, 900, k), (40, 30, 129), (900, 900, 70), (900, 900, k)]
+    probs, _ = batched_problems(4, 60 + s, max_spread=12.0, sizes=tuple(np.array(x) for x in zip(*sizes)))
+    C0s = [np.full((m, n), np.nan, dtype=np.complex128) for m, n, _ in sizes]
+    bt = Batch(probs, [("N", "N")] * 4, [1.0] * 4, [0.0] * 4, C0s, [s] * 4)
+    for limit in (5, 0):
+        assert oz.ozaki_set_grid_limit(limit) == 0
+        oz.ozaki_batched_cache_clear()
+        _say("batched chunked, large tiles", s, "grid limit", limit)
+        try:
+            got = bt.run()
+        finally:
+            oz.ozaki_set_grid_limit(0)
+        for b, (A, B) in enumerate(probs):
+            r, c = (np.unique(np.r_[0, x // 3, x // 2 - 1:x // 2 + 2, x - 2:x]) for x in got[b].shape)
+            ref = ozaki.ozaki_gemm("N", "N", A[r], B[:, c], s)
+            assert bits_equal(got[b][np.ix_(r, c)], ref), f"problem {b}\n" + mismatch_report(got[b][np.ix_(r, c)], ref)
+            assert np.all(np.isfinite(got[b].view(np.float64)))
+
+
+# The 64 x 64 tiles of two workgroups per CU, which the shape by size takes up to 6 slices
+@pytest.mark.parametrize("s,count,n,k", [(6, 16, 100, 70), (5, 8, 300, 270)])
+def test_batched_64_tiles_bit_exact(s, count, n, k):
+    ms = ns = np.full(2, n)
+    probs, _ = batched_problems(2, 50 + s, max_spread=12.0, sizes=(ms, ns, np.full(2, k)))
+    probs = [probs[b % 2] for b in range(count)]
+    C0s = [np.full((n, n), np.nan, dtype=np.complex128)] * count
+    bt = Batch(probs, [("N", "N")] * count, [1.0] * count, [0.0] * count, C0s, [s] * count)
+    _say("batched 64 x 64 tiles", s, count, n)
+    got = bt.run()
+    refs = [bt.reference(b) for b in range(2)]
+    for b in range(count):
+        assert bits_equal(got[b], refs[b % 2]), f"problem {b}\n" + mismatch_report(got[b], refs[b % 2])

@@ -272,3 +272,33 @@ names = [l[1] for l in of(log(), "launch")]
 assert any("%s" in x for x in names), names
 print("ok")
 """ % (kind, m, n, k, moduli, kernel))
+
+
+# The grouped GEMM of a batch, k_ozgemm<S, WJ, WI, IB, ...>: the sizes of test_gpu_batched.py and the
+# shapes that they are there for
+@pytest.mark.parametrize("s,sizes,tile", [
+    (6, [(500, 500, 70)] * 24, "8ELi1ELi8"), (7, [(500, 500, 70)] * 24, "8ELi1ELi4"),
+    (10, [(500, 500, 70)] * 24, "8ELi1ELi4"), (11, [(500, 500, 70)] * 24, "4ELi2ELi2"),
+    (6, [(100, 100, 70)], "2ELi2ELi1"), (6, [(100, 100, 70)] * 16, "4ELi1ELi4"),
+    (5, [(300, 300, 270)] * 8, "4ELi1ELi4"),
+    (6, [(150, 90, 70), (150, 90, 11200), (150, 90, 23000)], "4ELi1ELi4"),
+    (7, [(33, 20, 9600), (33, 20, 20000), (33, 20, 129)], "4ELi2ELi2"),
+    (6, [(900, 900, 11200), (40, 30, 129), (900, 900, 70), (900, 900, 11200)], "8ELi1ELi8"),
+    (7, [(900, 900, 9600), (40, 30, 129), (900, 900, 70), (900, 900, 9600)], "8ELi1ELi4")])
+def test_tiles_of_batches(child, s, sizes, tile):
+    child(r"""
+import numpy as np
+s, sizes, tile = %d, %r, "%s"
+n = len(sizes)
+lib.ozaki_batched_graphs(0)
+m, nn, k = (np.array(x, dtype=np.int64) for x in zip(*sizes))
+one, zero = np.ones(n, dtype=np.complex128), np.zeros(n, dtype=np.complex128)
+at, N = np.full(n, P, dtype=np.uint64), np.full(n, ord("N"), dtype=np.uint8)
+sl, used = np.full(n, s, dtype=np.int32), np.zeros(n, dtype=np.int32)
+p = lambda x: x.ctypes.data_as(ctypes.c_void_p)
+assert lib.ozaki_zgemm_batched(p(N), p(N), p(m), p(nn), p(k), p(one), p(at), p(m), p(at), p(k), p(zero), p(at),
+                               p(m), n, p(sl), p(used)) == 0
+names = [l[1] for l in of(log(), "launch")]
+assert any("k_ozgemmILi%%dELi%%s" %% (s, tile) in x for x in names), names
+print("ok")
+""" % (s, sizes, tile))
