@@ -18,7 +18,6 @@ struct Tables {
   int inv[kModMax];          // (P_k)^-1 mod m_k, P_k = m_0 ... m_{k-1} (balanced)
   int g[kModMax][kModMax];   // g[j][q] = P_j (P_q)^-1 mod m_q for j < q (balanced)
   int ng[(kModMax + 3) / 4][kModMax];  // -g[4 h + b][q] as bytes b of a word (0 for 4 h + b >= q)
-  int pw[kModMax][5];        // 2^(13 t) mod m_k (balanced)
   int c13[kModMax][3];       // 2^(13 t) (P_k)^-1 mod m_k (balanced)
   int P[kModMax][kLimbs];    // 16-bit limbs of P_k
   int nl[kModMax];           // nonzero limbs of P_k
@@ -61,9 +60,8 @@ constexpr Tables make_tables() {
       t.ng[h][k] = (int)w;
     }
     int w = 1;
-    for (int s = 0; s < 5; ++s) {
-      t.pw[k][s] = bal_c(w, mk);
-      if (s < 3) t.c13[k][s] = bal_c(w * x, mk);
+    for (int s = 0; s < 3; ++s) {
+      t.c13[k][s] = bal_c(w * x, mk);
       for (int b = 0; b < 13; ++b) w = (w * 2) % mk;
     }
   }

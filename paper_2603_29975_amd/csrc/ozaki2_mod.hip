@@ -327,14 +327,14 @@ constexpr float group_off(int h) {
   return s;
 }
 
-// a + b = s + e exactly, for |a| >= |b| or a = 0.
+// a + b = s + e exactly, for |a| >= |b| or a = 0 (Dekker 1971, Fast2Sum).
 __device__ __forceinline__ void fast_two_sum(double a, double b, double &s, double &e) {
   s = add_rn(a, b);
   e = sub_rn(b, sub_rn(s, a));
 }
 // a + b rounded to odd (an inexact sum takes the neighbour with an odd last
 // bit), for |a| >= |b| or a = 0: added to a much larger number, the sum then
-// rounds as the exact one would.
+// rounds as the exact one would (Boldo and Melquiond 2008).
 __device__ __forceinline__ double add_odd(double a, double b) {
   double s, e;
   fast_two_sum(a, b, s, e);

@@ -920,7 +920,7 @@ int enqueue_plan(const BatchedPlan &pl, hipStream_t st, bool capturing) {
     a.kb_chunk = kb_chunk_for(gd.S);
     a.chunked = gd.chunked ? 1 : 0;
     a.max_groups = g.grid_limit;
-    if ((rc = hip_rc(launch_ozgemm_grouped(gd.S, gd.tune_id, a, g.dev[pl.dev].num_cu, st))))
+    if ((rc = hip_rc(launch_ozgemm(gd.S, gd.tune_id, a, g.dev[pl.dev].num_cu, st))))
       return rc;
   }
   phase_end(mk, st);

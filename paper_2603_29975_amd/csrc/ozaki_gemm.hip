@@ -674,10 +674,6 @@ int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int64_t kb_ch
   return best;
 }
 
-hipError_t launch_ozgemm_grouped(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st) {
-  return launch_ozgemm(S, cfg, a, num_cu, st);
-}
-
 hipError_t launch_ozgemm(int S, int tune_id, const GemmArgs &a0, int num_cu, hipStream_t st) {
   GemmArgs a = a0;
   a.order = id_order(tune_id);

@@ -7,15 +7,15 @@
 
 namespace oz {
 
-// Exponent step: code[r] = max over row r of expo_code (code must hold zeros
-// on entry; launch_fill_i32 provides them).
 // Blocks of 256 threads in one launch (fewer than 2^32 threads along x).
 constexpr int64_t kMaxBlocks = (1 << 24) - 1;
 
 hipError_t launch_fill_i32(int *p, int64_t n, int value, hipStream_t st);
 // Pseudo-random digits in [-127, 127] (timing data of the autotuner).
 hipError_t launch_fill_digits(int8_t *p, int64_t n, uint64_t seed, hipStream_t st);
-// Both operands in one launch (a view without rows takes no part).
+// Exponent step: code[r] = max over row r of expo_code (code must hold zeros
+// on entry; launch_fill_i32 provides them). Both operands in one launch (a view
+// without rows takes no part).
 hipError_t launch_scan(const View &va, int *ca, const View &vb, int *cb, bool cplx, hipStream_t st);
 
 // Slicing step: writes all nrb*32 x nkb*32 packed rows/entries of S slices.
@@ -151,8 +151,6 @@ struct GemmSize {
   int64_t m, nprime, nkb;
 };
 int gemm_choose_grouped(int S, const std::vector<GemmSize> &probs, int64_t kb_chunk, int num_cu);
-// Launch a grouped GEMM over the tile table in `a` (every problem has S slices).
-hipError_t launch_ozgemm_grouped(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st);
 
 // Contraction blocks (of 32) that one INT32 accumulation may cover for S
 // slices: S * 32 * kb * 127^2 < 2^31 (8-bit slices: 128^2).
@@ -163,6 +161,7 @@ int gemm_num_configs();
 // Bytes of carry space the GEMM needs when nkb > kb_chunk (valid for
 // every configuration).
 size_t gemm_flush_bytes(int S, int num_cu);
+// One product, or the problems of the tile table in `a` (all of S slices).
 hipError_t launch_ozgemm(int S, int cfg, const GemmArgs &a, int num_cu, hipStream_t st);
 
 // Selector features and MLP (see ozaki_selector.hip).
