@@ -169,8 +169,11 @@ int ozaki_get_split(void);
  * (the library's own does when it grows for the call: one byte per modulus and
  * output entry, at most 1 GiB or one strip of 256 columns), the modular products
  * leave the chip there as residue bytes, a strip of columns at a time, and a
- * second kernel rebuilds C; a workspace of just ozaki2_workspace_bytes takes one
- * fused kernel that is about half as fast. The results are the same bit for bit.
+ * second kernel rebuilds C. The library's workspace without that room has 256 MiB
+ * beside it for them, allocated by the first such call outside of a capture. A
+ * caller's workspace of just ozaki2_workspace_bytes takes one fused kernel that is
+ * up to twice as slow, and so do products of at most 64 rows on which it is the
+ * faster one. The results are the same bit for bit.
  */
 #define OZAKI2_MODULI_MIN 2
 #define OZAKI2_MODULI_MAX 20

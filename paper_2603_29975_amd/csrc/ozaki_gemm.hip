@@ -22,7 +22,8 @@
 // stalls lowers the clock further, so the energy per product decides.
 //  - The 16x16x64 form keeps half as many accumulators per product as 32x32x32:
 //    bare MFMA loops on random operands run at 4.02 against 3.43 POP/s.
-//  - The copies into LDS are the largest other share (13%), so the tile is as
+//  - The copies into LDS are the largest other share (13% in a timed loop without
+//    them, as the 6% of the LDS reads below), so the tile is as
 //    large as the accumulators allow (128 x 128 up to S = 6, else 128 x 64),
 //    then the LDS reads (6%): each wave holds the B' fragments of all S slices
 //    of its 16 columns in registers and streams the A' fragments past them.
