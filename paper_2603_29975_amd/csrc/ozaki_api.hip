@@ -595,9 +595,10 @@ size_t oz2_plane_bytes(const Plan2 &p) {
 // Room for the residue bytes of a product that the library's workspace holds only
 // without them, from the first such call on (none is taken while the stream
 // captures). One size, so that it never moves and captured graphs may keep its
-// address; where it cannot be had it is not asked for again. Its strips / all
-// columns at once, 14 moduli: z 2048^3 569 / 563 us (fused kernel 1064), z 4096^3
-// 3682 / 3585, d 8192^3 7114 / 6992.
+// address; where it cannot be had it is not asked for again. Residue bytes here, in
+// strips where they are more / all behind the planes in the workspace, 14 moduli: z
+// 2048^3 (one strip) 569 / 563 us (fused kernel 1064), z 4096^3 3682 / 3585, d 8192^3
+// 7114 / 6992.
 constexpr size_t kOz2AuxBytes = (size_t)256 << 20;
 
 void *oz2_aux(int dev) {

@@ -193,6 +193,20 @@ def test_ozaki2_residue_planes_and_fused_kernel_agree(kind, m, n, k, nmod):
     assert bits_equal(got[r, c], ref), mismatch_report(got[r, c], ref)
 
 
+# Strips with enough products each for the residue planes (2.5e10): several of 1024 and 512
+# columns, the last one ragged
+@pytest.mark.parametrize("kind,m,n,k,nmod,columns", [("d", 1100, 2501, 2100, 14, 1024),
+                                                     ("z", 1030, 650, 1500, 17, 512)])
+def test_ozaki2_several_strips(kind, m, n, k, nmod, columns):
+    A, B, got, strips = _planes(kind, m, n, k, nmod, nmod * columns * ((m + 31) // 32 * 32))
+    assert bits_equal(got, strips), mismatch_report(got, strips)
+    fused = _planes(kind, m, n, k, nmod, 0)[3]
+    assert bits_equal(got, fused), mismatch_report(got, fused)
+    c = np.r_[0:3, n // 2:n // 2 + 3, n - 3:n]
+    ref = ozaki2.ozaki2_gemm("N", "N", A[-5:], B[:, c], nmod)
+    assert bits_equal(got[-5:, c], ref), mismatch_report(got[-5:, c], ref)
+
+
 @pytest.mark.parametrize("nmod", [14, 16, 17, 18, 20])
 def test_ozaki2_rounding_at_ties(nmod):
     # sums 2^p (1 + 2^-53) and neighbours, alone and moved off the tie by a term 2^-q below: the

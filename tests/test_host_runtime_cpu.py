@@ -160,6 +160,8 @@ print("ok")
     ("d", 100, 8000, 100, 8, 1024, 0),
     ("z", 512, 4096, 512, 18, 1024, 0),
     ("d", 4096, 4096, 4096, 8, 256, 16),      # strips that fill the chip for long enough
+    ("d", 1100, 2501, 2100, 14, 1024, 3),
+    ("z", 1030, 650, 1500, 17, 512, 3),
     ("z", 2048, 2048, 2048, 14, 1024, 4),
     ("z", 64, 4096, 64, 14, 8192, 1)])        # every column at once
 def test_ozaki2_strips_in_a_limited_workspace(child, kind, m, n, k, moduli, columns, strips):
